@@ -38,20 +38,50 @@ __device__ __forceinline__ uint32_t funnel(uint32_t hi, uint32_t lo, uint32_t sh
     return __builtin_amdgcn_alignbit(hi, lo, sh);
 }
 
-// The word of a staged row that holds bit position pos: pos >> 5.  On the
-// GPU the shift is opaque to the compiler, so a row address q * STRIDE +
-// base stays one shift-add; seen through, (pos >> 5) << 11 is rewritten as
-// a shift and a mask, one instruction more per window read.  The host build
-// of this header (CPU tests) takes the plain shift.
-__device__ __forceinline__ uint32_t word_of(uint32_t pos)
+// Issue cost of vector instructions on gfx950, cycles per wave64 instruction
+// and SIMD (measured with 8 waves a SIMD, independent instructions): 2 for
+// the 4-byte forms of add, sub, and, or, xor, not, right shifts, 16-bit
+// shifts, mov and FP32 add, mul and fmac on VGPRs and inline constants; 3 for
+// those with a literal and for bitop3 on VGPRs; 4 for every other one (left
+// shifts of 32 bits, bfe, bfi, perm, alignbit, SDWA, compares, conversions,
+// three-operand adds, FP64) and for any of them that reads an SGPR.  The
+// decoder is bound by these cycles, so its constants sit in VGPRs and its
+// fields are where right shifts and plain adds reach them.
+
+// The constant c in a VGPR, set where the call stands.
+__device__ __forceinline__ uint32_t vgpr_const(uint32_t c)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
-    uint32_t q;
-    asm("v_lshrrev_b32 %0, 5, %1" : "=v"(q) : "v"(pos));
-    return q;
+    uint32_t r;
+    asm volatile("v_mov_b32 %0, %1" : "=v"(r) : "i"(c));
+    return r;
 #else
-    return pos >> 5;
+    return c;
 #endif
+}
+
+// (a & m) | (b & ~m)
+__device__ __forceinline__ uint32_t select_bits(uint32_t m, uint32_t a, uint32_t b)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    return __builtin_amdgcn_bitop3_b32(a, b, m, 0xE4);
+#else
+    return (a & m) | (b & ~m);
+#endif
+}
+
+// v << D.  For D == 1 the sum v + v, which issues in half a shift's time.
+template <int D>
+__device__ __forceinline__ uint32_t shift_left(uint32_t v)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    if constexpr (D == 1) {
+        uint32_t r;
+        asm("v_add_u32 %0, %1, %1" : "=v"(r) : "v"(v));
+        return r;
+    }
+#endif
+    return v << D;
 }
 
 __device__ __forceinline__ uint32_t asr1(uint32_t v) { return (uint32_t)((int32_t)v >> 1); }
@@ -114,191 +144,145 @@ __device__ __forceinline__ void fwd_xform(uint32_t (&v)[16])
 }
 
 // ------------------------------------------------------ bit-matrix transpose
-// A[q] holds plane q in bits 0..15 and plane q+16 in bits 16..31 (bit s of a
-// plane = coefficient s).  Afterwards A[s] is coefficient s: bit p = its bit
-// in plane p.  Both 16x16 halves are transposed at once (the masks repeat in
-// each 16-bit half, and every shifted bit that crosses a half is masked off).
-// One stage: rows i and i + D (i & D == 0) exchange their D-wide column
-// blocks; M selects the low D columns of every 2D-wide group.  Templates keep
+// G[q] holds plane p0 + q of 16 planes in bits 0..15 and plane p0 + 8 + q in
+// bits 16..31 (bit s of a plane = coefficient s).  Three stages of exchanges
+// between registers trade the register number q for the low three bits of s:
+// afterwards bytes 0 and 2 of G[t] are coefficient t's bits in the planes
+// p0..p0+7 and p0+8..p0+15, bytes 1 and 3 those of coefficient t + 8.  Bytes
+// are then put together by byte permutes (assemble_coeffs), so no stage moves
+// bits by 8 or 16, and 16 planes take half the work of 32: blocks whose code
+// ends above plane 16 transpose one half only.
+// One stage: registers i and i + D (i & D == 0) exchange their D-wide column
+// blocks; m selects the low D columns of every 2D-wide group.  Templates keep
 // every index a compile-time constant (no register indexing, no loop).
-template <int D, uint32_t M, int I>
-__device__ __forceinline__ void transpose_pairs(uint32_t (&A)[16])
-{
-    if constexpr (I < 16) {
-        if constexpr ((I & D) == 0) {
-            const uint32_t a = A[I], b = A[I + D];
-            A[I] = (a & M) | ((b << D) & ~M);
-            A[I + D] = ((a >> D) & M) | (b & ~M);
-        }
-        transpose_pairs<D, M, I + 1>(A);
-    }
-}
-
-// The first stage (8-wide blocks) moves whole bytes: each output register
-// takes two bytes from each input, one byte permute per register.
-template <int I>
-__device__ __forceinline__ void transpose_bytes(uint32_t (&A)[16])
+template <int D, int I>
+__device__ __forceinline__ void transpose_pairs(uint32_t (&G)[8], uint32_t m)
 {
     if constexpr (I < 8) {
-        const uint32_t a = A[I], b = A[I + 8];
-        // selector bytes index (a: 0..3, b: 4..7), low output byte first
-        A[I] = __builtin_amdgcn_perm(b, a, 0x06020400u);     // a.b0 b.b0 a.b2 b.b2
-        A[I + 8] = __builtin_amdgcn_perm(b, a, 0x07030501u); // a.b1 b.b1 a.b3 b.b3
-        transpose_bytes<I + 1>(A);
+        if constexpr ((I & D) == 0) {
+            const uint32_t a = G[I], b = G[I + D];
+            G[I] = select_bits(m, a, shift_left<D>(b));
+            G[I + D] = select_bits(m, a >> D, b);
+        }
+        transpose_pairs<D, I + 1>(G, m);
     }
 }
 
-__device__ __forceinline__ void transpose_planes(uint32_t (&A)[16])
+__device__ __forceinline__ void transpose_half(uint32_t (&G)[8])
 {
-    transpose_bytes<0>(A);
-    transpose_pairs<4, 0x0F0F0F0Fu, 0>(A);
-    transpose_pairs<2, 0x33333333u, 0>(A);
-    transpose_pairs<1, 0x55555555u, 0>(A);
+    transpose_pairs<4, 0>(G, vgpr_const(0x0F0F0F0Fu));
+    transpose_pairs<2, 0>(G, vgpr_const(0x33333333u));
+    transpose_pairs<1, 0>(G, vgpr_const(0x55555555u));
+}
+
+// Complements the odd planes of a half (p0 is even): together with the
+// transpose this yields n ^ 0xAAAAAAAA for each negabinary coefficient n, the
+// first half of its conversion to two's complement.
+__device__ __forceinline__ void complement_odd_planes(uint32_t (&G)[8])
+{
+#pragma unroll
+    for (int q = 1; q < 8; q += 2)
+        G[q] = ~G[q];
+}
+
+// The transform coefficients (two's complement, at their block positions
+// 4r + c) from the two transposed halves, H of planes 31..16 and L of planes
+// 15..0: (n ^ 0xAAAAAAAA) - 0xAAAAAAAA modulo 2^32.
+__device__ __forceinline__ void assemble_coeffs(const uint32_t (&H)[8], const uint32_t (&L)[8], uint32_t (&cf)[16])
+{
+    const uint32_t plus = vgpr_const(0u - kNega);
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+        cf[order_of(t)] = __builtin_amdgcn_perm(H[t], L[t], 0x06040200u) + plus;     // L.b0 L.b2 H.b0 H.b2
+        cf[order_of(t + 8)] = __builtin_amdgcn_perm(H[t], L[t], 0x07050301u) + plus; // L.b1 L.b3 H.b1 H.b3
+    }
 }
 
 // --------------------------------------------------------------- decoding
-// Group-test sections are decoded with a lookup table of 8 stream bits at a
+// Group-test sections are decoded with a lookup table of 9 stream bits at a
 // time.  A section (after the verbatim bits of a plane) is a sequence of
-// tokens: "0" (next coefficient stays insignificant), "11" (it becomes
-// significant, another group follows), "10" (it becomes significant, the
-// plane ends); a group bit 0 at the start ends the plane at once, and when
-// the scan reaches coefficient 15 inside a run its 1 is implied.
+// tokens: "0" (the plane ends), "1" followed by a run: zeros (coefficients
+// that stay insignificant) up to a 1 (the next one becomes significant,
+// another token follows); when a run reaches coefficient 15 its 1 is implied,
+// and once all are significant the plane ends.
 //
-// Table entry for (nsig, state, 8 bits), state 0 = at a group bit, 1 =
-// inside a run; index nsig * kSecRow + (state << 8) + bits.  The row stride
-// kSecRow = 513 is odd on purpose: the decoder carries ns = nsig * kSecRow
-// instead of nsig, and since 513 = 16 * 32 + 1, ns's low byte (and its low
-// five bits, all that v_bfe reads of an offset or a width) is nsig itself.
-// The first lookup's address is then one add of ns and the 8 bits.  The
-// fields sit where the decoder can take them without masking:
+// Table entry for (nsig, 9 bits), at index (nsig << 9) + bits:
 //   bits  0..15  coefficients that became significant, at their absolute
-//                positions (the table is indexed by nsig), including
-//                coefficient 15's implied 1; they OR straight into the plane
-//                word's low half
-//   bits 16..19  stream bits consumed (0..8); bits 20..23 are zero, so the
-//                whole byte is the count
-//   bit  24      state to continue in when the section did not end
-//   bits 25..28  coefficients passed (nsig advances by this much, 0..9)
-//   bit  31      the section ended: the sign bit, tested without a mask
-// (e >> 16) & 0x8100 puts the state at index bit 8 and the ended flag at bit
-// 15, past every index of the table.  One more entry, kSecDone, is "ended,
-// nothing consumed": a lane whose section has ended reads it, so every step
-// runs unpredicated.
-constexpr int kSecBits = 8;
+//                positions, including coefficient 15's implied 1
+//   bits 16..31  what the decoder's state (below) advances by: the
+//                coefficients passed in bits 16..20, the bits passed in bits
+//                23..27
+//   bit  31      the section is open: it goes on past the 9 bits.  The entry
+//                then stops inside a run, in front of the last bit that
+//                belongs to the run's part already read: the next lookup
+//                takes that bit as the 1 that opens a run, so every lookup
+//                starts at a token and the table needs no second state
+//                (a section that stands between two runs is taken back to
+//                just in front of its last 1)
+// The bits passed count from the plane's start, verbatim bits included.  An
+// open entry's count is reduced by the new nsig, so that the next lookup,
+// which adds that many verbatim bits again, reads at the right place.
+constexpr int kSecBits = 9;
 constexpr int kSecN = 17; // nsig 0..16
-constexpr int kSecRow = 2 * (1 << kSecBits) + 1;
-constexpr int kSecDone = kSecN * kSecRow;
-constexpr int kSecEntries = kSecDone + 1;
-constexpr uint32_t kEntState = 1u << 24, kEntDone = 1u << 31;
-static_assert(kSecDone <= (int)(kEntDone >> 16), "the done flag must lift an index past the table");
-static_assert((kSecRow & 0x1FF) == 1 && (kSecN - 1) * kSecRow + 2 * (1 << kSecBits) <= kSecDone,
-              "ns = nsig * kSecRow keeps nsig in its low byte, and rows do not overlap");
-// nsig from ns = nsig * kSecRow (nsig <= 16)
-__host__ __device__ __forceinline__ constexpr uint32_t ns_nsig(uint32_t ns) { return ns & 0xFFu; }
+constexpr int kSecRow = 1 << kSecBits;
+constexpr int kSecEntries = kSecN * kSecRow;
 
-// a + nsig for ns = nsig * kSecRow.  On the GPU one SDWA add reads ns's low
-// byte; written plainly the compiler masks first and adds in a second
-// instruction.
-__device__ __forceinline__ uint32_t add_nsig(uint32_t a, uint32_t ns)
+// The decoder's state: S = (pos - 2) << 7 | nsig, pos the next bit to read,
+// coefficients 0..nsig-1 significant.  Shift amounts and bit-field widths
+// read the low five bits of a register, so S serves as nsig there as it is;
+// pos - 2 because a window read from two bits early holds the section's bits
+// at the byte offset of their table entry; << 7 because bits 12 and up then
+// are the byte offset of the window's word in a staged row of 1024 lanes.
+constexpr uint32_t kPosShift = 7;
+constexpr uint32_t kEntOpen = 1u << 31;
+__host__ __device__ __forceinline__ constexpr uint32_t state_at(uint32_t pos) { return (pos - 2u) << kPosShift; }
+__host__ __device__ __forceinline__ constexpr bool ent_open(uint32_t e) { return (int32_t)e < 0; }
+
+__host__ __device__ constexpr uint32_t section_entry(int nsig, int bits)
 {
-#if defined(__HIP_DEVICE_COMPILE__)
-    uint32_t r;
-    asm("v_add_u32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_0 src1_sel:DWORD"
-        : "=v"(r)
-        : "v"(ns), "v"(a));
-    return r;
-#else
-    return a + ns_nsig(ns);
-#endif
-}
-
-// tab[ns + bits] (tab in LDS).  On the GPU the byte address is one
-// v_add_lshl; written plainly the compiler scales both terms apart.
-__device__ __forceinline__ uint32_t sec_lookup(const uint32_t* tab, uint32_t ns, uint32_t bits)
-{
-#if defined(__HIP_DEVICE_COMPILE__)
-    uint32_t off;
-    asm("v_add_lshl_u32 %0, %1, %2, 2" : "=v"(off) : "v"(ns), "v"(bits));
-    return *(const uint32_t*)((const char*)tab + off);
-#else
-    return tab[ns + bits];
-#endif
-}
-
-// a + (b & 0xFF).  On the GPU one SDWA add reads b's low byte.
-__device__ __forceinline__ uint32_t add_byte0(uint32_t a, uint32_t b)
-{
-#if defined(__HIP_DEVICE_COMPILE__)
-    uint32_t r;
-    asm("v_add_u32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_0 src1_sel:DWORD"
-        : "=v"(r)
-        : "v"(b), "v"(a));
-    return r;
-#else
-    return a + (b & 0xFFu);
-#endif
-}
-
-// tab[min(i + j, kSecDone)] (tab in LDS).  On the GPU the byte offset is one
-// v_add_lshl and the clamp one v_min on it; written plainly the compiler adds,
-// clamps and then scales.
-__device__ __forceinline__ uint32_t sec_lookup_clamped(const uint32_t* tab, uint32_t i, uint32_t j)
-{
-#if defined(__HIP_DEVICE_COMPILE__)
-    uint32_t off;
-    asm("v_add_lshl_u32 %0, %1, %2, 2" : "=v"(off) : "v"(i), "v"(j));
-    off = __builtin_elementwise_min(off, 4u * (uint32_t)kSecDone);
-    return *(const uint32_t*)((const char*)tab + off);
-#else
-    return tab[__builtin_elementwise_min(i + j, (uint32_t)kSecDone)];
-#endif
-}
-
-__host__ __device__ __forceinline__ constexpr uint32_t ent_used(uint32_t e) { return (e >> 16) & 0xFFu; }
-__host__ __device__ __forceinline__ constexpr uint32_t ent_adv(uint32_t e) { return (e >> 25) & 15u; }
-__host__ __device__ __forceinline__ constexpr bool ent_open(uint32_t e) { return (int32_t)e >= 0; }
-// the entry's part of the next index: state at bit 8, ended flag at bit 15
-__host__ __device__ __forceinline__ constexpr uint32_t ent_next(uint32_t e) { return (e >> 16) & 0x8100u; }
-
-__host__ __device__ constexpr uint32_t section_entry(int state, int nsig, int bits)
-{
-    int used = 0, adv = 0, done = 0, st = state;
+    int used = 0, adv = 0;
     uint32_t ones = 0;
+    bool run = false, open = false;
     for (;;) {
-        if (st == 0) {
-            if (nsig + adv >= 16) { // every coefficient significant: no group bit
-                done = 1;
+        if (!run) {
+            if (nsig + adv == 16) // every coefficient significant: no group bit
+                break;
+            if (used == kSecBits) { // between runs: back to in front of the last 1
+                open = true;
+                used -= 2;
+                --adv;
+                ones &= ~(1u << (nsig + adv));
                 break;
             }
-            if (used == kSecBits)
-                break;
             const int g = (bits >> used) & 1;
             ++used;
-            if (!g) {
-                done = 1;
+            if (!g)
                 break;
-            }
-            st = 1;
+            run = true;
         } else {
             if (nsig + adv == 15) { // coefficient 15: its 1 is implied, not read
                 ones |= 1u << 15;
                 ++adv;
-                done = 1;
                 break;
             }
-            if (used == kSecBits)
+            if (used == kSecBits) { // inside a run: its last bit opens the next lookup
+                open = true;
+                --used;
                 break;
+            }
             const int b = (bits >> used) & 1;
             ++used;
             if (b) {
                 ones |= 1u << (nsig + adv);
-                st = 0;
+                run = false;
             }
             ++adv;
+            if (!b)
+                continue;
         }
     }
-    return ones | (uint32_t)used << 16 | (done ? 0u : (uint32_t)st << 24) | (uint32_t)adv << 25 |
-           (done ? kEntDone : 0u);
+    const uint32_t passed = (uint32_t)(open ? used - adv : nsig + used);
+    return ones | ((uint32_t)adv | passed << kPosShift) << 16 | (open ? kEntOpen : 0u);
 }
 
 struct SectionTable {
@@ -306,118 +290,176 @@ struct SectionTable {
     constexpr SectionTable() : e()
     {
         for (int n = 0; n < kSecN; ++n)
-            for (int st = 0; st < 2; ++st)
-                for (int b = 0; b < (1 << kSecBits); ++b)
-                    e[n * kSecRow + (st << 8) + b] = section_entry(st, n, b);
-        e[kSecDone] = kEntDone;
+            for (int b = 0; b < kSecRow; ++b)
+                e[n * kSecRow + b] = section_entry(n, b);
     }
 };
 
-// A[q] starts as plane q | plane q+16 << 16 with every odd plane
-// complemented: the transpose then yields n ^ 0xAAAAAAAA for each negabinary
-// coefficient n, the first half of the conversion to two's complement.  (The
-// variable-rate decoder keeps this form; the fixed-rate one stores the planes
-// as they are and converts after the transpose.)
-__host__ __device__ constexpr uint32_t kOddPlanes(int q) { return (q & 1) ? 0xFFFFFFFFu : 0u; }
+// What the decoder reads the section table with: the table (in LDS) and two
+// masks that stay in VGPRs for the kernel's life.
+struct SectionReader {
+    const uint32_t* tab;
+    uint32_t bits_mask; // a table entry's byte offset in its row
+    uint32_t word_mask; // the byte offset of a window's word in S
+};
 
-// Negabinary n -> two's complement (n ^ 0xAAAAAAAA) - 0xAAAAAAAA, modulo
-// 2^32: one v_xad on the GPU.
-__device__ __forceinline__ uint32_t nega_to_int(uint32_t n)
+__device__ __forceinline__ SectionReader section_reader(const uint32_t* tab)
+{
+    return SectionReader{tab, vgpr_const(4u * (kSecRow - 1)), vgpr_const(0x3F000u)};
+}
+
+// Byte offset of the table's row for state S: nsig << 11 (a 16-bit left
+// shift drops the position and issues in half the time of a 32-bit one).
+__device__ __forceinline__ uint32_t sec_row(uint32_t S)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
     uint32_t r;
-    // one SGPR operand at most (constant bus): the addend comes in a VGPR
-    asm("v_xad_u32 %0, %1, %2, %3" : "=v"(r) : "v"(n), "s"(kNega), "v"(0u - kNega));
+    asm("v_lshlrev_b16 %0, 11, %1" : "=v"(r) : "v"(S));
     return r;
 #else
-    return (n ^ kNega) - kNega;
+    return (S & 31u) << 11;
 #endif
 }
 
-// Plane P's word, (acc & 0xFFFF) | xv (disjoint bits), into A: plane P >= 16
-// as the high half of A[P - 16] (low half zero); plane P < 16 as the low half
-// of A[P], whose high half already holds plane P + 16.  One instruction each:
-// an SDWA or writing one half of its destination (the other half zeroed, or
-// kept).
+// The entry for state S whose window (from two bits early) is w: the section
+// starts nsig bits behind the window's first two.  FIRST: the plane's first
+// lookup; the later ones take the section's first bit as 1.
+template <bool FIRST>
+__device__ __forceinline__ uint32_t sec_lookup(const SectionReader& sec, uint32_t S, uint32_t w)
+{
+    uint32_t off = (w >> (S & 31u)) & sec.bits_mask;
+    if constexpr (!FIRST)
+        off |= 4u;
+    return *(const uint32_t*)((const char*)sec.tab + (off + sec_row(S)));
+}
+
+// 32 bits of the block staged at lw[word * STRIDE], from two bits in front of
+// state S's position.
+template <int STRIDE>
+__device__ __forceinline__ uint32_t state_window(const uint32_t* lw, const SectionReader& sec, uint32_t S)
+{
+    const uint32_t* p;
+    if constexpr (STRIDE == 1024 || STRIDE == 512 || STRIDE == 256) {
+        // the word's byte offset, from its place in S
+        const uint32_t off = (S & sec.word_mask) / (1024 / STRIDE);
+        p = (const uint32_t*)((const char*)lw + off);
+    } else {
+        p = lw + (S >> 12) * STRIDE;
+    }
+    return funnel(p[STRIDE], p[0], S >> kPosShift);
+}
+
+// Plane P's word, the low halves of ones | xv, into its half: the planes p0 +
+// 8.. come first and go to the high halves (low halves zero), p0.. to the low
+// ones.  One instruction each: an SDWA or writing one half of its destination
+// (the other half zeroed, or kept).
 template <int P>
-__device__ __forceinline__ void store_plane(uint32_t (&A)[16], uint32_t acc, uint32_t xv)
+__device__ __forceinline__ void store_plane(uint32_t (&G)[8], uint32_t ones, uint32_t xv)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
-    if constexpr (P >= 16)
+    if constexpr (P & 8)
         asm("v_or_b32_sdwa %0, %1, %2 dst_sel:WORD_1 dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:DWORD"
-            : "=v"(A[P - 16])
-            : "v"(acc), "v"(xv));
+            : "=v"(G[P & 7])
+            : "v"(ones), "v"(xv));
     else
         asm("v_or_b32_sdwa %0, %1, %2 dst_sel:WORD_0 dst_unused:UNUSED_PRESERVE src0_sel:DWORD src1_sel:DWORD"
-            : "+v"(A[P])
-            : "v"(acc), "v"(xv));
+            : "+v"(G[P & 7])
+            : "v"(ones), "v"(xv));
 #else
-    const uint32_t x = (acc & 0xFFFFu) | xv;
-    if constexpr (P >= 16)
-        A[P - 16] = x << 16;
+    const uint32_t x = (ones | xv) & 0xFFFFu;
+    if constexpr (P & 8)
+        G[P & 7] = x << 16;
     else
-        A[P] = (A[P] & 0xFFFF0000u) | x;
+        G[P & 7] = (G[P & 7] & 0xFFFF0000u) | x;
 #endif
 }
 
-// One bit plane of the embedded code (plane P, decoded in lockstep by all
-// lanes of the wave; P is a template argument so A[] is indexed at compile
-// time).  Every step is straight-line code for all lanes.  A lane whose budget
-// is spent keeps stepping over zero bits: a zero group bit ends each section
-// at once, so its plane words stay zero and its significance count is
-// unchanged.
-//
-// Bits past the end of the block read as zero.  That gives the exact result
-// everywhere except when the bit budget runs out inside a run: there the
-// zero bits walk on to coefficient 15, where the code instead sets the
-// coefficient the run had reached when the budget ended.  The number of
-// zeros read past the end says which one that was.  Only planes in which
-// some lane of the wave is past its budget pay for that correction.
+// Planes P and below of a half are zero: the high planes from P down were
+// never written.
+template <int P>
+__device__ __forceinline__ void clear_planes(uint32_t (&G)[8])
+{
+    if constexpr (P & 8) {
+#pragma unroll
+        for (int q = 0; q <= (P & 7); ++q)
+            G[q] = 0u;
+    }
+}
+
+// One bit plane of the embedded code (decoded in lockstep by all lanes of
+// the wave) in `rd`, whose window(sec, S) reads 32 bits from two bits in front
+// of S's position.  Returns the plane word in its low half as two parts: the
+// significant coefficients' verbatim bits in xv, and the new ones.
+template <typename Bits>
+__device__ __forceinline__ uint32_t plane_bits(const Bits& rd, const SectionReader& sec, uint32_t& S, uint32_t& xv)
+{
+    // the window holds the verbatim bits (nsig <= 16) and the first 9 section
+    // bits (v_bfe takes the width modulo 32: nsig)
+    const uint32_t w = rd.window(sec, S);
+    xv = __builtin_amdgcn_ubfe(w, 2u, S);
+    uint32_t e = sec_lookup<true>(sec, S, w);
+    uint32_t ones = e;
+    S += e >> 16;
+    while (ent_open(e)) { // the lanes whose section goes on
+        S -= kEntOpen >> 16;
+        e = sec_lookup<false>(sec, S, rd.window(sec, S));
+        S += e >> 16;
+        ones |= e;
+    }
+    return ones;
+}
+
+template <int STRIDE>
+struct RowBits {
+    const uint32_t* lw;
+    __device__ __forceinline__ uint32_t window(const SectionReader& sec, uint32_t S) const
+    {
+        return state_window<STRIDE>(lw, sec, S);
+    }
+};
+
+// Planes that no block of NW words can run past its end in: P planes take at
+// most 25 + 17 P bits with the header (16 verbatim bits a plane after the
+// first, one ending group bit a plane, and over all planes 16 run-opening
+// bits and 16 run bits).
+template <int NW>
+constexpr int kSafePlanes = 32 * NW < 25 ? 0 : (32 * NW - 25) / 17;
+
+// Plane P of a fixed-rate block.  A lane whose budget is spent keeps stepping
+// over zero bits: a zero group bit ends each section at once, so its plane
+// words stay zero.  Bits past the end of the block read as zero.  That gives
+// the exact result everywhere except when the bit budget runs out inside a
+// run: there the zero bits walk on to coefficient 15, where the code instead
+// sets the coefficient the run had reached when the budget ended.  The number
+// of zeros read past the end says which one that was.  Only planes in which
+// some lane of the wave is past its budget pay for that correction, and the
+// first kSafePlanes do not look for one.
 //
 // Returns the wave's mask of lanes past their budget.
 template <int NW, int STRIDE, int P>
-__device__ __forceinline__ uint64_t decode_plane(const uint32_t* lw, const uint32_t* tab, uint32_t& pos,
-                                                 uint32_t& ns, uint32_t (&A)[16])
+__device__ __forceinline__ uint64_t decode_plane(const uint32_t* lw, const SectionReader& sec, uint32_t& S,
+                                                 uint32_t (&G)[8])
 {
     constexpr uint32_t kMaxBits = 32u * NW;
-    // word of pos (positions stay below 1024: kMaxBits + 32 + one plane)
-    uint32_t q = word_of(pos);
-    // 32 bits from pos: the verbatim bits (nsig <= 16) and the first 8
-    // section bits always fit
-    const uint32_t lo = funnel(lw[(q + 1) * STRIDE], lw[q * STRIDE], pos & 31u);
-    // (i) verbatim bits of the significant coefficients (v_bfe takes the
-    // width mod 32: nsig)
-    const uint32_t xv = __builtin_amdgcn_ubfe(lo, 0u, ns);
-    // (ii) group tests, 8 bits per table lookup.  acc's low half collects
-    // the plane's new ones; its high half is the latest entry's fields, so
-    // the loop carries no separate copy of the entry
-    uint32_t acc = sec_lookup(tab, ns, __builtin_amdgcn_ubfe(lo, ns, 8u));
-    uint32_t at = add_nsig(pos, ns) + ent_used(acc); // next unread bit
-    ns += ent_adv(acc) * (uint32_t)kSecRow;
-    if (__any(ent_open(acc))) {
-        do {
-            q = word_of(at);
-            const uint32_t bits = funnel(lw[(q + 1) * STRIDE], lw[q * STRIDE], at & 31u);
-            // ended: the index is past kSecDone and clamps onto it
-            acc = (acc & 0xFFFFu) | sec_lookup_clamped(tab, add_byte0(ns, bits), ent_next(acc));
-            at += ent_used(acc);
-            ns += ent_adv(acc) * (uint32_t)kSecRow;
-        } while (__any(ent_open(acc)));
+    uint32_t xv;
+    uint32_t ones = plane_bits(RowBits<STRIDE>{lw}, sec, S, xv);
+    uint64_t past = 0;
+    if constexpr (31 - P >= kSafePlanes<NW>) {
+        past = __ballot(S >= state_at(kMaxBits));
+        if (__builtin_expect(past != 0, 0)) { // a branch, not selects on every plane
+            // the implied 1 of coefficient 15 moves back to where the run
+            // stood when the budget ended (ex = zeros read past the end; ex
+            // <= 15 wherever that 1 is set)
+            const uint32_t ex = __builtin_elementwise_sub_sat(S >> kPosShift, kMaxBits - 2u);
+            const uint32_t m = ones & 0x8000u;
+            ones ^= m ^ (m >> (ex & 31u));
+            // a lane past the end reads only zero bits: its plane word is
+            // zero; keep its position inside the padding (its nsig no longer
+            // matters)
+            S = __builtin_elementwise_min(S, state_at(kMaxBits + 32u));
+        }
     }
-    const uint64_t past = __ballot(at >= kMaxBits);
-    if (__builtin_expect(past != 0, 0)) { // a branch, not selects on every plane
-        // the implied 1 of coefficient 15 moves back to where the run stood
-        // when the budget ended (ex = zeros read past the end; ex <= 15
-        // wherever that 1 is set)
-        const uint32_t ex = __builtin_elementwise_sub_sat(at, kMaxBits);
-        const uint32_t m = acc & 0x8000u;
-        acc ^= m ^ (m >> (ex & 31u));
-        // a lane past the end reads only zero bits: its plane word is zero
-        // and its state stays put; keep its position inside the padding
-        at = __builtin_elementwise_min(at, kMaxBits + 32u);
-    }
-    pos = at;
-    store_plane<P>(A, acc, xv);
+    store_plane<P>(G, ones, xv);
     return past;
 }
 
@@ -426,85 +468,99 @@ __device__ __forceinline__ uint64_t decode_plane(const uint32_t* lw, const uint3
 // coefficient by less than 2^(lo+1), the 2-D inverse lift multiplies that by
 // at most 3.75^2, and the block's integers stay below 2^30 + 2^29.3 < 2^31.
 constexpr int kSafeCutPlane = 26;
+// whether a block of NW words can be cut above that plane at all
+template <int NW>
+constexpr bool kCanCut = 32 - kSafeCutPlane > kSafePlanes<NW>;
 
-// `cut` ends true when the budget ended before plane kSafeCutPlane was read
-// in full (the block's top planes only), else false.  `past`: the wave's
-// lanes already past their budget.
-template <int NW, int STRIDE, int P>
-__device__ __forceinline__ void decode_planes_from(const uint32_t* lw, const uint32_t* tab, uint32_t& pos,
-                                                   uint32_t& ns, uint32_t (&A)[16], bool& cut, uint64_t past)
+// Planes P..LAST of a half.  `cut` ends true when the budget ended before
+// plane kSafeCutPlane was read in full (the block's top planes only), else
+// false.  `past`: the wave's lanes already past their budget; when that is
+// every lane, the planes left are zero.
+template <int NW, int STRIDE, int P, int LAST>
+__device__ __forceinline__ void decode_planes_from(const uint32_t* lw, const SectionReader& sec, uint32_t& S,
+                                                   uint32_t (&G)[8], bool& cut, uint64_t& past)
 {
-    if constexpr (P >= 0) {
-        if (past == __builtin_amdgcn_read_exec()) {
-            // planes P..0 stay zero: words 0..P-16 were never written
-            if constexpr (P >= 16) {
-#pragma unroll
-                for (int q = 0; q <= P - 16; ++q)
-                    A[q] = 0u;
+    if constexpr (P >= LAST) {
+        if constexpr (31 - P >= kSafePlanes<NW>) {
+            if (past == __builtin_amdgcn_read_exec()) {
+                clear_planes<P>(G);
+                return;
             }
-            return;
         }
-        past = decode_plane<NW, STRIDE, P>(lw, tab, pos, ns, A);
-        if constexpr (P == kSafeCutPlane)
-            cut = pos > 32u * NW;
-        decode_planes_from<NW, STRIDE, P - 1>(lw, tab, pos, ns, A, cut, past);
+        past = decode_plane<NW, STRIDE, P>(lw, sec, S, G);
+        if constexpr (P == kSafeCutPlane && kCanCut<NW>)
+            cut = cut && S > state_at(32u * NW + 1u) - 1u;
+        decode_planes_from<NW, STRIDE, P - 1, LAST>(lw, sec, S, G, cut, past);
     }
 }
 
 // Words a lane's staged block occupies in LDS: NW words of the block, then
-// zeros, which the decoder reads past the end of the bit budget.  Each read
-// takes words q and q + 1 of a position; a position stays below 32 bits past
-// the end plus one plane (a plane never spans more than 31 bits: nsig
-// verbatim bits and at most 1 + 2 (15 - nsig) section bits, or 16 verbatim
-// bits), so word NW + 2 is the last one read.
+// zeros, which the decoder reads past the end of the bit budget.  A window
+// takes two words from a position that stays below 32 bits past the end
+// (clamped there after each plane; a plane never spans more than 31 bits:
+// nsig verbatim bits and at most 1 + 2 (15 - nsig) section bits, or 16
+// verbatim bits), so word NW + 1 is the last one read.
 template <int NW>
-constexpr int kStagedWords = NW + 3;
+constexpr int kStagedWords = NW + 2;
 
 // Decode the coefficients of the block staged at lw[q * STRIDE], q =
-// 0..NW-1 (lw[q * STRIDE] == 0 for q = NW..NW+2); w0 == lw[0]; tab = the
-// section table (in LDS).  Outputs the 16 transform coefficients (two's
+// 0..NW-1 (lw[q * STRIDE] == 0 for q = NW, NW+1); w0 == lw[0].  Outputs the 16 transform coefficients (two's
 // complement, at their block positions 4r + c, before the inverse
 // transform) and emax.  Returns false for an all-zero block (then cf[] is
 // all 0).  Every bit pattern decodes (the function is total).
 // `cut`: the budget ended above plane kSafeCutPlane (then only the exact
 // integer lift reproduces the decoded block; see lin_inv_lift).
 template <int NW, int STRIDE>
-__device__ __forceinline__ bool decode_block_coeffs(const uint32_t* lw, const uint32_t* tab, uint32_t w0, int& emax,
+__device__ __forceinline__ bool decode_block_coeffs(const uint32_t* lw, const SectionReader& sec, uint32_t w0, int& emax,
                                                     uint32_t (&cf)[16], bool& cut)
 {
     const bool nz = (w0 & 1u) != 0;
     emax = (int)((w0 >> 1) & 0xFFu) - 127;
-    uint32_t pos = nz ? 9u : 32u * NW; // next bit to read; decoding stops at 32*NW
-    uint32_t ns = 0u;                   // nsig * kSecRow: coefficients 0..nsig-1 significant
-    uint32_t A[16]; // every word is written by a plane or by the early exit
-    cut = nz;       // a zero block is exact; others until plane kSafeCutPlane is read
-    decode_planes_from<NW, STRIDE, 31>(lw, tab, pos, ns, A, cut, __ballot(!nz));
-    transpose_planes(A);
-    // negabinary -> two's complement (one v_xad each), undo the sequency
-    // order
+    uint32_t S = nz ? state_at(9u) : state_at(32u * NW);
+    cut = kCanCut<NW> && nz; // a zero block is exact; others until plane kSafeCutPlane is read
+    uint64_t past = kSafePlanes<NW> > 0 ? 0 : __ballot(!nz);
+    uint32_t H[8], L[8]; // every word is written by a plane or by the early exit
+    decode_planes_from<NW, STRIDE, 31, 16>(lw, sec, S, H, cut, past);
+    complement_odd_planes(H);
+    transpose_half(H);
+    if (past == __builtin_amdgcn_read_exec()) { // no lane has a plane below 16
+        const uint32_t none = vgpr_const(kNega);
 #pragma unroll
-    for (int s = 0; s < 16; ++s)
-        cf[order_of(s)] = nega_to_int(A[s]);
+        for (int q = 0; q < 8; ++q)
+            L[q] = none;
+    } else {
+        decode_planes_from<NW, STRIDE, 15, 0>(lw, sec, S, L, cut, past);
+        complement_odd_planes(L);
+        transpose_half(L);
+    }
+    assemble_coeffs(H, L, cf);
     return nz;
 }
 
 // The decoded block: its coefficients through the inverse transform, as
 // integers (value = iv * 2^(emax - 30)).
 template <int NW, int STRIDE>
-__device__ __forceinline__ bool decode_block_coeffs(const uint32_t* lw, const uint32_t* tab, uint32_t w0, int& emax,
+__device__ __forceinline__ bool decode_block_coeffs(const uint32_t* lw, const SectionReader& sec, uint32_t w0, int& emax,
                                                     uint32_t (&cf)[16])
 {
     bool cut;
-    return decode_block_coeffs<NW, STRIDE>(lw, tab, w0, emax, cf, cut);
+    return decode_block_coeffs<NW, STRIDE>(lw, sec, w0, emax, cf, cut);
+}
+
+template <int NW, int STRIDE>
+__device__ __forceinline__ bool decode_block_ints(const uint32_t* lw, const SectionReader& sec, uint32_t w0, int& emax,
+                                                  uint32_t (&iv)[16])
+{
+    const bool nz = decode_block_coeffs<NW, STRIDE>(lw, sec, w0, emax, iv);
+    inv_xform(iv);
+    return nz;
 }
 
 template <int NW, int STRIDE>
 __device__ __forceinline__ bool decode_block_ints(const uint32_t* lw, const uint32_t* tab, uint32_t w0, int& emax,
                                                   uint32_t (&iv)[16])
 {
-    const bool nz = decode_block_coeffs<NW, STRIDE>(lw, tab, w0, emax, iv);
-    inv_xform(iv);
-    return nz;
+    return decode_block_ints<NW, STRIDE>(lw, section_reader(tab), w0, emax, iv);
 }
 
 // The inverse lift without its two floor halvings is a linear map B (the

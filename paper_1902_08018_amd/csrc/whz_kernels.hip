@@ -84,13 +84,14 @@ __global__ void __launch_bounds__(kThreads) decode_blocks_kernel(const uint32_t*
     uint32_t* row = lds + threadIdx.x;
     clear_pad<NW, kThreads>(row);
     load_section_table<kThreads>(tab);
+    const SectionReader sec = section_reader(tab);
     const uint64_t stride = (uint64_t)gridDim.x * kThreads;
     for (uint64_t i = (uint64_t)blockIdx.x * kThreads + threadIdx.x; i < nblocks; i += stride) {
         uint32_t w[NW];
         stage_block<NW, kThreads>(row, stream + (b0 + i) * NW, w);
         int emax;
         uint32_t iv[16];
-        decode_block_ints<NW, kThreads>(row, tab, w[0], emax, iv);
+        decode_block_ints<NW, kThreads>(row, sec, w[0], emax, iv);
         float4* o = reinterpret_cast<float4*>(out + 16 * i);
 #pragma unroll
         for (int r = 0; r < 4; ++r)
@@ -122,6 +123,7 @@ __global__ void __launch_bounds__(kDecThreads<NW>) decode_matrix_kernel(const ui
     uint32_t* row = lds + threadIdx.x;
     clear_pad<NW, T>(row);
     load_section_table<T>(tab);
+    const SectionReader sec = section_reader(tab);
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64u);
     const uint32_t lane = threadIdx.x % 64u;
     const uint64_t stride = (uint64_t)gridDim.x * kWaves;
@@ -133,7 +135,7 @@ __global__ void __launch_bounds__(kDecThreads<NW>) decode_matrix_kernel(const ui
         stage_block<NW, T>(row, stream + (bi * nbc + bj) * NW, w);
         int emax;
         uint32_t iv[16];
-        decode_block_ints<NW, T>(row, tab, w[0], emax, iv);
+        decode_block_ints<NW, T>(row, sec, w[0], emax, iv);
         if ((cols & 3u) == 0 && 4 * bi + 3 < rows) { // a whole block on 16-byte aligned rows
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
@@ -338,6 +340,7 @@ __global__ void __launch_bounds__(kGemvThreads<NW>, kGemvMinWaves<NW>) gemv_kern
     uint32_t* row = lds + threadIdx.x;
     clear_pad<NW, THREADS>(row);
     load_section_table<THREADS>(tab);
+    const SectionReader sec = section_reader(tab);
 
     const uint32_t G = 1u << lg, groups = (uint32_t)THREADS >> lg;
     const uint32_t grp = threadIdx.x >> lg, gl = threadIdx.x & (G - 1);
@@ -384,7 +387,7 @@ __global__ void __launch_bounds__(kGemvThreads<NW>, kGemvMinWaves<NW>) gemv_kern
             if constexpr (Acc::kPerProduct) {
                 // Fig. 7: each FP32 product of the decoded value and u is
                 // added to the FP64 sum on its own
-                decode_block_ints<NW, THREADS>(row, tab, w[0], emax, iv);
+                decode_block_ints<NW, THREADS>(row, sec, w[0], emax, iv);
                 const int k = emax - 30;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
@@ -397,7 +400,7 @@ __global__ void __launch_bounds__(kGemvThreads<NW>, kGemvMinWaves<NW>) gemv_kern
                 // coefficients against B^T u (FP32); B is applied once to the
                 // row group's sums below
                 bool cut;
-                decode_block_coeffs<NW, THREADS>(row, tab, w[0], emax, iv, cut);
+                decode_block_coeffs<NW, THREADS>(row, sec, w[0], emax, iv, cut);
                 float ut[4];
                 lin_bt_u<float>(uu.x, uu.y, uu.z, uu.w, ut);
                 const int k = emax - 30;
@@ -409,8 +412,9 @@ __global__ void __launch_bounds__(kGemvThreads<NW>, kGemvMinWaves<NW>) gemv_kern
                     v[r] = __builtin_fmaf((float)(int32_t)iv[4 * r + 2], ut[2], v[r]);
                     v[r] = __builtin_fmaf((float)(int32_t)iv[4 * r + 3], ut[3], v[r]);
                 }
-                if (__any(cut) && cut) // rare: the exact lift, back to coefficient space
-                    exact_block_sums(iv, uu, v);
+                if constexpr (kCanCut<NW>)
+                    if (__any(cut) && cut) // rare: the exact lift, back to coefficient space
+                        exact_block_sums(iv, uu, v);
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
                     acc[r].add(__builtin_ldexpf(v[r], k));
@@ -739,6 +743,7 @@ __global__ void __launch_bounds__(64 * mrhs_waves(NT, (MrhsMath)MATH), mrhs_wave
     uint32_t* row = lds + threadIdx.x;
     clear_pad<NW, T>(row);
     load_section_table<T>(tab); // the last workgroup barrier
+    const SectionReader sec = section_reader(tab);
 
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const uint32_t tile = blockIdx.x / nslab, slab = blockIdx.x % nslab;
@@ -833,13 +838,14 @@ __global__ void __launch_bounds__(64 * mrhs_waves(NT, (MrhsMath)MATH), mrhs_wave
         int emax;
         uint32_t cf[16];
         bool cut;
-        decode_block_coeffs<NW, T>(row, tab, w0, emax, cf, cut);
+        decode_block_coeffs<NW, T>(row, sec, w0, emax, cf, cut);
         float sc[16];
 #pragma unroll
         for (int v = 0; v < 16; ++v)
             sc[v] = __builtin_ldexpf((float)(int32_t)cf[v], emax - 30);
-        if (__any(cut) && cut) // rare: the exact lift (see exact_block_coeffs)
-            exact_block_coeffs(cf, emax, sc);
+        if constexpr (kCanCut<NW>)
+            if (__any(cut) && cut) // rare: the exact lift (see exact_block_coeffs)
+                exact_block_coeffs(cf, emax, sc);
 #pragma unroll
         for (int n = 0; n < NA; ++n)
             acc[n] = mf32x4{0.f, 0.f, 0.f, 0.f};

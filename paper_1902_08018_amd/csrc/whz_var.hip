@@ -87,7 +87,11 @@ constexpr uint32_t kVarRing = 24, kVarRow = kVarRing + 1;
 struct GlobalBits {
     const uint32_t* g;
     uint32_t lim;
-    __device__ __forceinline__ uint32_t window(uint32_t pos) const { return vwindow(g, lim, pos); }
+    __device__ __forceinline__ uint32_t bits_at(uint32_t pos) const { return vwindow(g, lim, pos); }
+    __device__ __forceinline__ uint32_t window(const SectionReader&, uint32_t S) const
+    {
+        return bits_at(S >> kPosShift);
+    }
 };
 
 // Reading a block from a lane's ring at lw[k * T]: positions count from bit 0
@@ -99,11 +103,15 @@ template <int T>
 struct StagedBits {
     const uint32_t* lw;
     uint32_t sb;
-    __device__ __forceinline__ uint32_t window(uint32_t pos) const
+    __device__ __forceinline__ uint32_t bits_at(uint32_t pos) const
     {
         uint32_t q = __builtin_elementwise_min(pos >> 5, kVarRing - 1u) + sb;
         q = __builtin_elementwise_min(q, q - kVarRing); // the ring's slot
         return funnel(lw[(q + 1) * T], lw[q * T], pos & 31u);
+    }
+    __device__ __forceinline__ uint32_t window(const SectionReader&, uint32_t S) const
+    {
+        return bits_at(S >> kPosShift);
     }
 };
 
@@ -117,55 +125,27 @@ __host__ __device__ __forceinline__ int var_planes(int mode, int param, int emax
     return p < 0 ? 0 : (p > 32 ? 32 : p);
 }
 
-// Plane P of a block, all lanes in lockstep.  A lane whose lowest plane lo
-// is above P reads zero bits: its plane word is zero, and its position and
-// significance count stay put.  With no bit budget, the implied 1 at the end
-// of a run is always coefficient 15's.
-template <int P, typename Bits>
-__device__ __forceinline__ void var_plane(const Bits& rd, const uint32_t* tab, uint32_t lo, uint32_t& pos,
-                                          uint32_t& ns, uint32_t (&A)[16])
+// Planes P..LAST of a half, the lanes whose lowest plane lo is not above the
+// plane in lockstep; the plane words of the others are zero.  With no bit
+// budget, the implied 1 at the end of a run is always coefficient 15's.
+// Returns true when no lane has a plane below the last one read.
+template <int P, int LAST, typename Bits>
+__device__ __forceinline__ bool var_planes_from(const Bits& rd, const SectionReader& sec, uint32_t lo, uint32_t& S,
+                                                uint32_t (&G)[8])
 {
-    const bool live = (uint32_t)P >= lo;
-    const uint32_t w = live ? rd.window(pos) : 0u;
-    const uint32_t xv = __builtin_amdgcn_ubfe(w, 0u, ns); // ns = nsig * kSecRow; v_bfe reads nsig
-    uint32_t e = sec_lookup(tab, ns, __builtin_amdgcn_ubfe(w, ns, 8u));
-    uint32_t acc = e;
-    uint32_t at = add_nsig(pos, ns) + ent_used(e);
-    ns += ent_adv(e) * (uint32_t)kSecRow;
-    if (__any(ent_open(e))) {
-        do {
-            const uint32_t bits = live ? rd.window(at) : 0u;
-            const uint32_t idx = ns + ent_next(e) + (bits & 0xFFu);
-            e = tab[__builtin_elementwise_min(idx, (uint32_t)kSecDone)];
-            acc |= e;
-            at += ent_used(e);
-            ns += ent_adv(e) * (uint32_t)kSecRow;
-        } while (__any(ent_open(e)));
-    }
-    const uint32_t x = (acc & 0xFFFFu) | xv; // coefficient 15's implied 1 is in the table's ones
-    if (live)
-        pos = at;
-    if constexpr (P >= 16)
-        A[P - 16] = (x << 16) ^ kOddPlanes(P - 16);
-    else
-        A[P] ^= x;
-}
-
-template <int P, typename Bits>
-__device__ __forceinline__ void var_planes_from(const Bits& rd, const uint32_t* tab, uint32_t lo, uint32_t& pos,
-                                                uint32_t& ns, uint32_t (&A)[16])
-{
-    if constexpr (P >= 0) {
-        if (!__any((uint32_t)P >= lo)) { // every lane is done: planes P..0 stay zero
-            if constexpr (P >= 16) {
-#pragma unroll
-                for (int q = 0; q <= P - 16; ++q)
-                    A[q] = kOddPlanes(q);
-            }
-            return;
+    if constexpr (P >= LAST) {
+        const bool live = (uint32_t)P >= lo;
+        if (!__any(live)) { // every lane is done: the half's planes left are zero
+            clear_planes<P>(G);
+            return true;
         }
-        var_plane<P>(rd, tab, lo, pos, ns, A);
-        var_planes_from<P - 1>(rd, tab, lo, pos, ns, A);
+        uint32_t ones = 0u, xv = 0u;
+        if (live)
+            ones = plane_bits(rd, sec, S, xv);
+        store_plane<P>(G, ones, xv);
+        return var_planes_from<P - 1, LAST>(rd, sec, lo, S, G);
+    } else {
+        return !__any((uint32_t)LAST > lo);
     }
 }
 
@@ -174,22 +154,31 @@ __device__ __forceinline__ void var_planes_from(const Bits& rd, const uint32_t* 
 // live == false decodes a zero block and does not move.  Returns whether the
 // block is nonzero.
 template <typename Bits>
-__device__ __forceinline__ bool var_block_coeffs(const Bits& rd, const uint32_t* tab, int mode, int param, bool live,
+__device__ __forceinline__ bool var_block_coeffs(const Bits& rd, const SectionReader& sec, int mode, int param, bool live,
                                                  uint32_t& pos, int& emax, uint32_t (&cf)[16])
 {
-    const uint32_t h = live ? rd.window(pos) : 0u;
+    const uint32_t h = live ? rd.bits_at(pos) : 0u;
     const bool nz = (h & 1u) != 0;
     emax = (int)((h >> 1) & 0xFFu) - 127;
-    if (live)
-        pos += nz ? 9u : 1u;
     const uint32_t lo = nz ? (uint32_t)(32 - var_planes(mode, param, emax)) : 32u;
-    uint32_t ns = 0u; // nsig * kSecRow
-    uint32_t A[16];
-    var_planes_from<31>(rd, tab, lo, pos, ns, A);
-    transpose_planes(A);
+    uint32_t S = state_at(pos + 9u); // of a nonzero block
+    uint32_t H[8], L[8];
+    const bool none_below = var_planes_from<31, 16>(rd, sec, lo, S, H);
+    complement_odd_planes(H);
+    transpose_half(H);
+    if (none_below) {
+        const uint32_t none = vgpr_const(kNega);
 #pragma unroll
-    for (int s = 0; s < 16; ++s)
-        cf[order_of(s)] = A[s] - kNega;
+        for (int q = 0; q < 8; ++q)
+            L[q] = none;
+    } else {
+        var_planes_from<15, 0>(rd, sec, lo, S, L);
+        complement_odd_planes(L);
+        transpose_half(L);
+    }
+    assemble_coeffs(H, L, cf);
+    if (live)
+        pos = nz ? (S >> kPosShift) + 2u : pos + 1u;
     return nz;
 }
 
@@ -220,7 +209,7 @@ struct VarRing {
 // most 32 planes, and the check keeps a code that breaks the bound (a
 // corrupt stream) from decoding out of stale ring words.
 template <int T>
-__device__ __forceinline__ bool var_next_block(const uint32_t* g, uint32_t lim, uint32_t* row, const uint32_t* tab,
+__device__ __forceinline__ bool var_next_block(const uint32_t* g, uint32_t lim, uint32_t* row, const SectionReader& sec,
                                                int mode, int param, bool live, uint32_t& pos, int& emax,
                                                uint32_t (&cf)[16], VarRing& ring)
 {
@@ -269,12 +258,12 @@ __device__ __forceinline__ bool var_next_block(const uint32_t* g, uint32_t lim, 
     }
     // the block's piece b sits where the ring's head is now (24 words on)
     uint32_t lpos = pos + 32u * a - 32u * b;
-    bool nz = var_block_coeffs(StagedBits<T>{row, 4u * ring.hs}, tab, mode, param, live, lpos, emax, cf);
+    bool nz = var_block_coeffs(StagedBits<T>{row, 4u * ring.hs}, sec, mode, param, live, lpos, emax, cf);
     const bool over = live && lpos >= 32u * (kVarRing - 1u);
     if (__any(over)) {
         if (over) {
             uint32_t p = pos;
-            nz = var_block_coeffs(GlobalBits{g, lim}, tab, mode, param, true, p, emax, cf);
+            nz = var_block_coeffs(GlobalBits{g, lim}, sec, mode, param, true, p, emax, cf);
             lpos = p + 32u * a - 32u * b;
         }
     }
@@ -302,6 +291,7 @@ __global__ void __launch_bounds__(kVarThreadsSmall) var_decode_kernel(
     __shared__ uint32_t stage[T * kVarRow];
     uint32_t* row = stage + threadIdx.x;
     load_table<T>(tab);
+    const SectionReader sec = section_reader(tab);
     const uint64_t lane_id = (uint64_t)blockIdx.x * T + threadIdx.x;
     const bool in = lane_id < nlanes;
     const uint32_t bi = in ? (uint32_t)(lane_id / ngroups) : 0u, a = in ? (uint32_t)(lane_id % ngroups) : 0u;
@@ -318,7 +308,7 @@ __global__ void __launch_bounds__(kVarThreadsSmall) var_decode_kernel(
             const uint32_t bj = a * 32u + j0 + s;
             int emax;
             uint32_t iv[16];
-            var_next_block<T>(g, lim, row, tab, mode, param, in && bj < nbc, pos, emax, iv, ring);
+            var_next_block<T>(g, lim, row, sec, mode, param, in && bj < nbc, pos, emax, iv, ring);
             inv_xform(iv);
 #pragma unroll
             for (int i = 0; i < 16; ++i)
@@ -405,6 +395,7 @@ __global__ void __launch_bounds__(T) var_gemv_kernel(
     uint32_t* row = reinterpret_cast<uint32_t*>(stage_d) + threadIdx.x;
     double* red = stage_d;
     load_table<T>(tab);
+    const SectionReader sec = section_reader(tab);
     const uint32_t G = 1u << lg, groups = (uint32_t)T >> lg;
     const uint32_t grp = threadIdx.x >> lg, gl = threadIdx.x & (G - 1);
     const uint32_t tile = blockIdx.x / nslab, slab = blockIdx.x % nslab;
@@ -430,7 +421,7 @@ __global__ void __launch_bounds__(T) var_gemv_kernel(
         }
         int emax;
         uint32_t iv[16];
-        const bool nz = var_next_block<T>(g, lim, row, tab, mode, param, live, pos, emax, iv, ring);
+        const bool nz = var_next_block<T>(g, lim, row, sec, mode, param, live, pos, emax, iv, ring);
         if (live && nz) {
             // the exact integer inverse transform (not B (C (B^T u))): a
             // coefficient cut to its top planes can reach -2^31, where the
