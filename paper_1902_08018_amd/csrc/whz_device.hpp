@@ -11,8 +11,9 @@
 // block row then every block column; sequency order; negabinary.
 //
 // One lane decodes one block.  The bits of the lane's block sit in a
-// lane-private LDS row (words 0..NW-1 plus three zero words), so a 64-bit
-// window can be read at any bit position with two funnel shifts.
+// lane-private LDS row (words 0..NW-1 plus three zero words).  A lane carries
+// 32 bits from its position on and reads the 32 that follow from that row
+// beside the table lookup of each plane.
 //
 // Included by the .hip translation units after <hip/hip_runtime.h>.
 #pragma once
@@ -207,12 +208,12 @@ __device__ __forceinline__ void assemble_coeffs(const uint32_t (&H)[8], const ui
 // and once all are significant the plane ends.
 //
 // Table entry for (nsig, 9 bits), at index (nsig << 9) + bits:
-//   bits  0..15  coefficients that became significant, at their absolute
+//   bits 16..31  coefficients that became significant, at their absolute
 //                positions, including coefficient 15's implied 1
-//   bits 16..31  what the decoder's state (below) advances by: the
-//                coefficients passed in bits 16..20, the bits passed in bits
-//                23..27
-//   bit  31      the section is open: it goes on past the 9 bits.  The entry
+//   bits  0..15  what the decoder's state (below) advances by: the
+//                coefficients passed in bits 0..4, the bits passed in bits
+//                7..11
+//   bit  12      the section is open: it goes on past the 9 bits.  The entry
 //                then stops inside a run, in front of the last bit that
 //                belongs to the run's part already read: the next lookup
 //                takes that bit as the 1 that opens a run, so every lookup
@@ -232,11 +233,49 @@ constexpr int kSecEntries = kSecN * kSecRow;
 // read the low five bits of a register, so S serves as nsig there as it is;
 // pos - 2 because a window read from two bits early holds the section's bits
 // at the byte offset of their table entry; << 7 because bits 12 and up then
-// are the byte offset of the window's word in a staged row of 1024 lanes.
+// are the byte offset of the window's word in a staged row of 1024 lanes.  Blocks
+// of up to 14 words keep it in 16 bits (pos stays below 32 NW + 48): whole
+// entries are then added to it, and its high half gathers what the entries
+// hold above their low half, which nothing reads.  WIDE: the others, whose
+// state takes the entries' low halves only.
 constexpr uint32_t kPosShift = 7;
-constexpr uint32_t kEntOpen = 1u << 31;
+constexpr uint32_t kEntOpen = 1u << 12;
+template <int NW>
+constexpr bool kWideState = NW > 14;
+template <bool WIDE>
+__device__ __forceinline__ uint32_t advance(uint32_t S, uint32_t e)
+{
+    return WIDE ? S + (e & 0xFFFFu) : S + e;
+}
+template <bool WIDE>
+__device__ __forceinline__ uint32_t state_value(uint32_t S)
+{
+    return WIDE ? S : S & 0xFFFFu;
+}
 __host__ __device__ __forceinline__ constexpr uint32_t state_at(uint32_t pos) { return (pos - 2u) << kPosShift; }
-__host__ __device__ __forceinline__ constexpr bool ent_open(uint32_t e) { return (int32_t)e < 0; }
+
+// The lanes whose v has a low half of at least `least`, as a wave mask (one
+// 16-bit compare; written plainly the compiler masks the half out first).
+__device__ __forceinline__ uint64_t lanes_from_u16(uint32_t v, uint32_t least)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    uint64_t m;
+    asm("v_cmp_le_u16_e64 %0, %1, %2" : "=s"(m) : "s"(least), "v"(v));
+    return m;
+#else
+    return __ballot((v & 0xFFFFu) >= least);
+#endif
+}
+
+// Whether this lane's section goes on after entry e.
+__device__ __forceinline__ bool ent_open(uint32_t e)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    return __builtin_amdgcn_inverse_ballot_w64(lanes_from_u16(e, kEntOpen));
+#else
+    return (e & 0xFFFFu) >= kEntOpen;
+#endif
+}
 
 __host__ __device__ constexpr uint32_t section_entry(int nsig, int bits)
 {
@@ -282,7 +321,7 @@ __host__ __device__ constexpr uint32_t section_entry(int nsig, int bits)
         }
     }
     const uint32_t passed = (uint32_t)(open ? used - adv : nsig + used);
-    return ones | ((uint32_t)adv | passed << kPosShift) << 16 | (open ? kEntOpen : 0u);
+    return ones << 16 | (uint32_t)adv | passed << kPosShift | (open ? kEntOpen : 0u);
 }
 
 struct SectionTable {
@@ -303,9 +342,10 @@ struct SectionReader {
     uint32_t word_mask; // the byte offset of a window's word in S
 };
 
+template <bool WIDE>
 __device__ __forceinline__ SectionReader section_reader(const uint32_t* tab)
 {
-    return SectionReader{tab, vgpr_const(4u * (kSecRow - 1)), vgpr_const(0x3F000u)};
+    return SectionReader{tab, vgpr_const(4u * (kSecRow - 1)), vgpr_const(WIDE ? 0x1F000u : 0xF000u)};
 }
 
 // Byte offset of the table's row for state S: nsig << 11 (a 16-bit left
@@ -333,10 +373,11 @@ __device__ __forceinline__ uint32_t sec_lookup(const SectionReader& sec, uint32_
     return *(const uint32_t*)((const char*)sec.tab + (off + sec_row(S)));
 }
 
-// 32 bits of the block staged at lw[word * STRIDE], from two bits in front of
-// state S's position.
+// Bits 32..63 of the block staged at lw[word * STRIDE], counted from two bits
+// in front of state S's position: two words, from the one after the
+// position's on.
 template <int STRIDE>
-__device__ __forceinline__ uint32_t state_window(const uint32_t* lw, const SectionReader& sec, uint32_t S)
+__device__ __forceinline__ uint32_t bits_ahead(const uint32_t* lw, const SectionReader& sec, uint32_t S)
 {
     const uint32_t* p;
     if constexpr (STRIDE == 1024 || STRIDE == 512 || STRIDE == 256) {
@@ -344,29 +385,29 @@ __device__ __forceinline__ uint32_t state_window(const uint32_t* lw, const Secti
         const uint32_t off = (S & sec.word_mask) / (1024 / STRIDE);
         p = (const uint32_t*)((const char*)lw + off);
     } else {
-        p = lw + (S >> 12) * STRIDE;
+        p = lw + ((S & sec.word_mask) >> 12) * STRIDE;
     }
-    return funnel(p[STRIDE], p[0], S >> kPosShift);
+    return funnel(p[2 * STRIDE], p[STRIDE], S >> kPosShift);
 }
 
-// Plane P's word, the low halves of ones | xv, into its half: the planes p0 +
-// 8.. come first and go to the high halves (low halves zero), p0.. to the low
-// ones.  One instruction each: an SDWA or writing one half of its destination
-// (the other half zeroed, or kept).
+// Plane P's word, ones' high half | xv's low half, into its half: the planes
+// p0 + 8.. come first and go to the high halves (low halves zero), p0.. to the
+// low ones.  One instruction each: an SDWA or writing one half of its
+// destination (the other half zeroed, or kept).
 template <int P>
 __device__ __forceinline__ void store_plane(uint32_t (&G)[8], uint32_t ones, uint32_t xv)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
     if constexpr (P & 8)
-        asm("v_or_b32_sdwa %0, %1, %2 dst_sel:WORD_1 dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:DWORD"
+        asm volatile("v_or_b32_sdwa %0, %1, %2 dst_sel:WORD_1 dst_unused:UNUSED_PAD src0_sel:WORD_1 src1_sel:DWORD"
             : "=v"(G[P & 7])
             : "v"(ones), "v"(xv));
     else
-        asm("v_or_b32_sdwa %0, %1, %2 dst_sel:WORD_0 dst_unused:UNUSED_PRESERVE src0_sel:DWORD src1_sel:DWORD"
+        asm volatile("v_or_b32_sdwa %0, %1, %2 dst_sel:WORD_0 dst_unused:UNUSED_PRESERVE src0_sel:WORD_1 src1_sel:DWORD"
             : "+v"(G[P & 7])
             : "v"(ones), "v"(xv));
 #else
-    const uint32_t x = (ones | xv) & 0xFFFFu;
+    const uint32_t x = ones >> 16 | (xv & 0xFFFFu);
     if constexpr (P & 8)
         G[P & 7] = x << 16;
     else
@@ -386,37 +427,42 @@ __device__ __forceinline__ void clear_planes(uint32_t (&G)[8])
     }
 }
 
-// One bit plane of the embedded code (decoded in lockstep by all lanes of
-// the wave) in `rd`, whose window(sec, S) reads 32 bits from two bits in front
-// of S's position.  Returns the plane word in its low half as two parts: the
-// significant coefficients' verbatim bits in xv, and the new ones.
-template <typename Bits>
-__device__ __forceinline__ uint32_t plane_bits(const Bits& rd, const SectionReader& sec, uint32_t& S, uint32_t& xv)
+// A block between two planes: the state, and 32 bits from two bits in front of
+// its position.
+struct PlaneCursor {
+    uint32_t S, w;
+};
+
+// One bit plane of the embedded code (decoded in lockstep by all lanes of the
+// wave).  `ahead` are the 32 bits that follow c.w.  Returns the plane word in
+// two parts: the significant coefficients' verbatim bits in xv (low half), and
+// the new ones (high half).
+// A plane spans at most 31 bits, so the next one's window lies within these
+// 64: the only read a plane waits for is the section table's, and the stream
+// words are read beside it (a variable-rate GEMV of 8192^2, two waves a SIMD
+// and so bound by this chain, went from 186 to 169 us; before, a plane waited
+// for its window and then for its entry).
+template <bool WIDE>
+__device__ __forceinline__ uint32_t plane_bits(const SectionReader& sec, PlaneCursor& c, uint32_t ahead, uint32_t& xv)
 {
     // the window holds the verbatim bits (nsig <= 16) and the first 9 section
     // bits (v_bfe takes the width modulo 32: nsig)
-    const uint32_t w = rd.window(sec, S);
-    xv = __builtin_amdgcn_ubfe(w, 2u, S);
-    uint32_t e = sec_lookup<true>(sec, S, w);
-    uint32_t ones = e;
-    S += e >> 16;
-    while (ent_open(e)) { // the lanes whose section goes on
-        S -= kEntOpen >> 16;
-        e = sec_lookup<false>(sec, S, rd.window(sec, S));
-        S += e >> 16;
-        ones |= e;
+    uint32_t e = sec_lookup<true>(sec, c.S, c.w);
+    xv = __builtin_amdgcn_ubfe(c.w, 2u, c.S);
+    uint32_t ones = e, moved = e; // bits 7..11 of moved: the bits passed
+    c.S = advance<WIDE>(c.S, e);
+    if (ent_open(e)) {
+        do { // the lanes whose section goes on
+            c.S -= kEntOpen;
+            e = sec_lookup<false>(sec, c.S, funnel(ahead, c.w, moved >> kPosShift));
+            c.S = advance<WIDE>(c.S, e);
+            moved += e;
+            ones |= e;
+        } while (ent_open(e));
     }
+    c.w = funnel(ahead, c.w, moved >> kPosShift);
     return ones;
 }
-
-template <int STRIDE>
-struct RowBits {
-    const uint32_t* lw;
-    __device__ __forceinline__ uint32_t window(const SectionReader& sec, uint32_t S) const
-    {
-        return state_window<STRIDE>(lw, sec, S);
-    }
-};
 
 // Planes that no block of NW words can run past its end in: P planes take at
 // most 25 + 17 P bits with the header (16 verbatim bits a plane after the
@@ -424,44 +470,6 @@ struct RowBits {
 // bits and 16 run bits).
 template <int NW>
 constexpr int kSafePlanes = 32 * NW < 25 ? 0 : (32 * NW - 25) / 17;
-
-// Plane P of a fixed-rate block.  A lane whose budget is spent keeps stepping
-// over zero bits: a zero group bit ends each section at once, so its plane
-// words stay zero.  Bits past the end of the block read as zero.  That gives
-// the exact result everywhere except when the bit budget runs out inside a
-// run: there the zero bits walk on to coefficient 15, where the code instead
-// sets the coefficient the run had reached when the budget ended.  The number
-// of zeros read past the end says which one that was.  Only planes in which
-// some lane of the wave is past its budget pay for that correction, and the
-// first kSafePlanes do not look for one.
-//
-// Returns the wave's mask of lanes past their budget.
-template <int NW, int STRIDE, int P>
-__device__ __forceinline__ uint64_t decode_plane(const uint32_t* lw, const SectionReader& sec, uint32_t& S,
-                                                 uint32_t (&G)[8])
-{
-    constexpr uint32_t kMaxBits = 32u * NW;
-    uint32_t xv;
-    uint32_t ones = plane_bits(RowBits<STRIDE>{lw}, sec, S, xv);
-    uint64_t past = 0;
-    if constexpr (31 - P >= kSafePlanes<NW>) {
-        past = __ballot(S >= state_at(kMaxBits));
-        if (__builtin_expect(past != 0, 0)) { // a branch, not selects on every plane
-            // the implied 1 of coefficient 15 moves back to where the run
-            // stood when the budget ended (ex = zeros read past the end; ex
-            // <= 15 wherever that 1 is set)
-            const uint32_t ex = __builtin_elementwise_sub_sat(S >> kPosShift, kMaxBits - 2u);
-            const uint32_t m = ones & 0x8000u;
-            ones ^= m ^ (m >> (ex & 31u));
-            // a lane past the end reads only zero bits: its plane word is
-            // zero; keep its position inside the padding (its nsig no longer
-            // matters)
-            S = __builtin_elementwise_min(S, state_at(kMaxBits + 32u));
-        }
-    }
-    store_plane<P>(G, ones, xv);
-    return past;
-}
 
 // Planes below this one may be cut by the bit budget without the exact
 // inverse lift leaving the int32 range: a cut at plane lo moves a
@@ -472,86 +480,166 @@ constexpr int kSafeCutPlane = 26;
 template <int NW>
 constexpr bool kCanCut = 32 - kSafeCutPlane > kSafePlanes<NW>;
 
-// Planes P..LAST of a half.  `cut` ends true when the budget ended before
-// plane kSafeCutPlane was read in full (the block's top planes only), else
-// false.  `past`: the wave's lanes already past their budget; when that is
-// every lane, the planes left are zero.
+// What a fixed-rate block's planes share.
+template <int NW, int STRIDE>
+struct BlockReader {
+    const uint32_t* lw;
+    SectionReader sec;
+    uint64_t past; // the wave's lanes past their budget
+    bool cut;      // see decode_block_coeffs
+};
+
+// Plane P of a fixed-rate block into its half G; `ahead`: the 32 bits that
+// follow c.w.  A lane whose budget is spent keeps stepping over zero bits: a
+// zero group bit ends each section at once, so its plane words stay zero.
+// Bits past the end of the block read as zero.  That gives the exact result
+// everywhere except when the bit budget runs out inside a run: there the zero
+// bits walk on to coefficient 15, where the code instead sets the coefficient
+// the run had reached when the budget ended.  The number of zeros read past
+// the end says which one that was.  Only planes in which some lane of the wave
+// is past its budget pay for that correction, and the first kSafePlanes do not
+// look for one.
+template <int NW, int STRIDE, int P>
+__device__ __forceinline__ void decode_plane(BlockReader<NW, STRIDE>& rd, PlaneCursor& c, uint32_t ahead,
+                                             uint32_t (&G)[8])
+{
+    constexpr uint32_t kMaxBits = 32u * NW;
+    constexpr bool kWide = kWideState<NW>;
+    uint32_t xv;
+    uint32_t ones = plane_bits<kWide>(rd.sec, c, ahead, xv);
+    if constexpr (31 - P >= kSafePlanes<NW>) {
+        const uint32_t at = state_value<kWide>(c.S);
+        if constexpr (P == kSafeCutPlane && kCanCut<NW>)
+            rd.cut = rd.cut && at >= state_at(kMaxBits + 1u);
+        rd.past = kWide ? __ballot(at >= state_at(kMaxBits)) : lanes_from_u16(c.S, state_at(kMaxBits));
+        if (__builtin_expect(rd.past != 0, 0)) { // a branch, not selects on every plane
+            // the implied 1 of coefficient 15 moves back to where the run
+            // stood when the budget ended (ex = zeros read past the end; ex
+            // <= 15 wherever that 1 is set)
+            const uint32_t ex = __builtin_elementwise_sub_sat(at >> kPosShift, kMaxBits - 2u);
+            const uint32_t m = ones & 0x80000000u;
+            ones ^= m ^ (m >> (ex & 31u));
+            // a lane past the end reads only zero bits: its plane word is
+            // zero; it goes on from the end, with nothing significant (which
+            // no longer matters), where the words it may have read are zero
+            c.S = __builtin_elementwise_min(at, state_at(kMaxBits));
+        }
+    }
+    store_plane<P>(G, ones, xv);
+}
+
+// Planes P..LAST of a half.  When every lane of the wave is past its budget
+// the planes left are zero.
 template <int NW, int STRIDE, int P, int LAST>
-__device__ __forceinline__ void decode_planes_from(const uint32_t* lw, const SectionReader& sec, uint32_t& S,
-                                                   uint32_t (&G)[8], bool& cut, uint64_t& past)
+__device__ __forceinline__ void decode_planes_from(BlockReader<NW, STRIDE>& rd, PlaneCursor& c, uint32_t (&G)[8])
 {
     if constexpr (P >= LAST) {
-        if constexpr (31 - P >= kSafePlanes<NW>) {
-            if (past == __builtin_amdgcn_read_exec()) {
+        if constexpr (31 - P > kSafePlanes<NW> || kSafePlanes<NW> == 0) {
+            if (rd.past == __builtin_amdgcn_read_exec()) {
                 clear_planes<P>(G);
                 return;
             }
         }
-        past = decode_plane<NW, STRIDE, P>(lw, sec, S, G);
-        if constexpr (P == kSafeCutPlane && kCanCut<NW>)
-            cut = cut && S > state_at(32u * NW + 1u) - 1u;
-        decode_planes_from<NW, STRIDE, P - 1, LAST>(lw, sec, S, G, cut, past);
+        decode_plane<NW, STRIDE, P>(rd, c, bits_ahead<STRIDE>(rd.lw, rd.sec, c.S), G);
+        decode_planes_from<NW, STRIDE, P - 1, LAST>(rd, c, G);
     }
 }
 
 // Words a lane's staged block occupies in LDS: NW words of the block, then
-// zeros, which the decoder reads past the end of the bit budget.  A window
-// takes two words from a position that stays below 32 bits past the end
-// (clamped there after each plane; a plane never spans more than 31 bits:
-// nsig verbatim bits and at most 1 + 2 (15 - nsig) section bits, or 16
-// verbatim bits), so word NW + 1 is the last one read.
+// zeros, which the decoder reads past the end of the bit budget.  bits_ahead
+// takes the two words after a position that stays below 32 bits past the end
+// (a lane past it goes back to it after each plane, or stands in a zero block
+// and moves one bit a plane; a plane never spans more than 31 bits: nsig
+// verbatim bits and at most 1 + 2 (15 - nsig) section bits, or 16 verbatim
+// bits), so word NW + 2 is the last one read.
 template <int NW>
-constexpr int kStagedWords = NW + 2;
+constexpr int kStagedWords = NW + 3;
+
+// Planes 31 and 30, the first from the block's first words (w0, w1, w2): every
+// lane is at bit 9 with nothing significant.  Plane 31 is empty in all blocks
+// but those with a coefficient below -(2^31 - 1) / 3, so when no lane of the
+// wave opens a run in it, it is one bit to pass.
+template <int NW, int STRIDE>
+__device__ __forceinline__ void decode_top_planes(BlockReader<NW, STRIDE>& rd, uint32_t w0, uint32_t w1, uint32_t w2,
+                                                  bool nz, PlaneCursor& c, uint32_t (&H)[8])
+{
+    static_assert(kSafePlanes<NW> >= 2, "no block ends within its first two planes");
+    c.w = nz ? funnel(w1, w0, 7u) : 0u;
+    uint32_t ahead = nz ? funnel(w2, w1, 7u) : 0u;
+    if (__any((c.w & 4u) != 0u)) {
+        decode_plane<NW, STRIDE, 31>(rd, c, ahead, H);
+        ahead = bits_ahead<STRIDE>(rd.lw, rd.sec, c.S);
+    } else {
+        H[7] = 0u;
+        c.S += 1u << kPosShift;
+        c.w = funnel(ahead, c.w, 1u);
+        ahead >>= 1; // plane 30 has nothing verbatim: 31 bits are enough
+    }
+    decode_plane<NW, STRIDE, 30>(rd, c, ahead, H);
+}
 
 // Decode the coefficients of the block staged at lw[q * STRIDE], q =
-// 0..NW-1 (lw[q * STRIDE] == 0 for q = NW, NW+1); w0 == lw[0].  Outputs the 16 transform coefficients (two's
+// 0..NW-1 (lw[q * STRIDE] == 0 for q = NW..NW+2); w: its words again, in
+// registers (the first three are used).  Outputs the 16 transform coefficients (two's
 // complement, at their block positions 4r + c, before the inverse
-// transform) and emax.  Returns false for an all-zero block (then cf[] is
-// all 0).  Every bit pattern decodes (the function is total).
+// transform).  Returns false for an all-zero block (then cf[] is all 0).
+// Every bit pattern decodes (the function is total).
 // `cut`: the budget ended above plane kSafeCutPlane (then only the exact
 // integer lift reproduces the decoded block; see lin_inv_lift).
-template <int NW, int STRIDE>
-__device__ __forceinline__ bool decode_block_coeffs(const uint32_t* lw, const SectionReader& sec, uint32_t w0, int& emax,
-                                                    uint32_t (&cf)[16], bool& cut)
+// `planes_read` is called once the code's bits have all been read: a caller
+// loads the next block's words there, with the transposes and its own work
+// on the coefficients still to come.
+template <int NW, int STRIDE, typename F>
+__device__ __forceinline__ bool decode_block_coeffs(const uint32_t* lw, const SectionReader& sec,
+                                                    const uint32_t (&w)[NW], uint32_t (&cf)[16], bool& cut,
+                                                    F planes_read)
 {
-    const bool nz = (w0 & 1u) != 0;
-    emax = (int)((w0 >> 1) & 0xFFu) - 127;
-    uint32_t S = nz ? state_at(9u) : state_at(32u * NW);
-    cut = kCanCut<NW> && nz; // a zero block is exact; others until plane kSafeCutPlane is read
-    uint64_t past = kSafePlanes<NW> > 0 ? 0 : __ballot(!nz);
+    const bool nz = (w[0] & 1u) != 0;
+    // a zero block is exact; others are cut until plane kSafeCutPlane is read
+    BlockReader<NW, STRIDE> rd{lw, sec, 0, kCanCut<NW> && nz};
+    PlaneCursor c;
+    c.S = nz ? state_at(9u) : state_at(32u * NW);
     uint32_t H[8], L[8]; // every word is written by a plane or by the early exit
-    decode_planes_from<NW, STRIDE, 31, 16>(lw, sec, S, H, cut, past);
+    const uint32_t w1 = NW > 1 ? w[NW > 1 ? 1 : 0] : 0u, w2 = NW > 2 ? w[NW > 2 ? 2 : 0] : 0u;
+    if constexpr (kSafePlanes<NW> >= 2) {
+        decode_top_planes<NW, STRIDE>(rd, w[0], w1, w2, nz, c, H);
+        decode_planes_from<NW, STRIDE, 29, 16>(rd, c, H);
+    } else {
+        rd.past = __ballot(!nz);
+        c.w = nz ? funnel(w1, w[0], 7u) : 0u;
+        decode_planes_from<NW, STRIDE, 31, 16>(rd, c, H);
+    }
+    const bool low = rd.past != __builtin_amdgcn_read_exec(); // some lane has planes below 16
+    if (low)
+        decode_planes_from<NW, STRIDE, 15, 0>(rd, c, L);
+    cut = rd.cut;
+    planes_read();
     complement_odd_planes(H);
     transpose_half(H);
-    if (past == __builtin_amdgcn_read_exec()) { // no lane has a plane below 16
+    if (low) {
+        complement_odd_planes(L);
+        transpose_half(L);
+    } else {
         const uint32_t none = vgpr_const(kNega);
 #pragma unroll
         for (int q = 0; q < 8; ++q)
             L[q] = none;
-    } else {
-        decode_planes_from<NW, STRIDE, 15, 0>(lw, sec, S, L, cut, past);
-        complement_odd_planes(L);
-        transpose_half(L);
     }
     assemble_coeffs(H, L, cf);
     return nz;
 }
 
+// The binade exponent of the block whose first word is w0.
+__device__ __forceinline__ int block_emax(uint32_t w0) { return (int)((w0 >> 1) & 0xFFu) - 127; }
+
 // The decoded block: its coefficients through the inverse transform, as
 // integers (value = iv * 2^(emax - 30)).
-template <int NW, int STRIDE>
-__device__ __forceinline__ bool decode_block_coeffs(const uint32_t* lw, const SectionReader& sec, uint32_t w0, int& emax,
-                                                    uint32_t (&cf)[16])
+template <int NW, int STRIDE, typename F>
+__device__ __forceinline__ bool decode_block_ints(const uint32_t* lw, const SectionReader& sec,
+                                                  const uint32_t (&w)[NW], uint32_t (&iv)[16], F planes_read)
 {
     bool cut;
-    return decode_block_coeffs<NW, STRIDE>(lw, sec, w0, emax, cf, cut);
-}
-
-template <int NW, int STRIDE>
-__device__ __forceinline__ bool decode_block_ints(const uint32_t* lw, const SectionReader& sec, uint32_t w0, int& emax,
-                                                  uint32_t (&iv)[16])
-{
-    const bool nz = decode_block_coeffs<NW, STRIDE>(lw, sec, w0, emax, iv);
+    const bool nz = decode_block_coeffs<NW, STRIDE>(lw, sec, w, iv, cut, planes_read);
     inv_xform(iv);
     return nz;
 }
@@ -560,7 +648,12 @@ template <int NW, int STRIDE>
 __device__ __forceinline__ bool decode_block_ints(const uint32_t* lw, const uint32_t* tab, uint32_t w0, int& emax,
                                                   uint32_t (&iv)[16])
 {
-    return decode_block_ints<NW, STRIDE>(lw, section_reader(tab), w0, emax, iv);
+    uint32_t w[NW];
+#pragma unroll
+    for (int k = 0; k < NW; ++k)
+        w[k] = lw[k * STRIDE];
+    emax = block_emax(w0);
+    return decode_block_ints<NW, STRIDE>(lw, section_reader<kWideState<NW>>(tab), w, iv, [] {});
 }
 
 // The inverse lift without its two floor halvings is a linear map B (the

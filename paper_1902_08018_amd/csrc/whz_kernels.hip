@@ -4,11 +4,16 @@
 //
 // Fused GEMV (the deformation product y = C.S of Eq. 2 over a zfp-compressed
 // matrix, Sec. 4.3-4.4):
-//   grid     one 512-lane workgroup per (row tile, column slab)
+//   grid     one workgroup (1024 lanes, or 768 above 16 bits/value) per (row
+//            tile, column slab)
 //   lanes    groups of 2^lg lanes (8 by default); a group sweeps one block
 //            row's slab, each lane decoding one 4x4 block per step (its
 //            words staged in LDS), so a wave works on an 8 x 8 patch of
-//            blocks; a tile holds (512 / 2^lg) x rpg block rows
+//            blocks; a tile holds (lanes / 2^lg) x rpg block rows
+//   bound    the decoder's vector instructions: 65536^2 at rate 8 takes 3.00
+//            ms (3.67 before the one-register state, the 64-bit window and
+//            the half transposes), 1.43 TB/s of stream; the wave's VALU
+//            cycles fill about 85 % of the time and LDS 60 %
 //   product  each block's coefficients against B^T u (FP32), its power-of-two
 //            scale applied to the sum; B once per block row at the end; blocks
 //            cut by the bit budget above plane 26 take the exact inverse lift
@@ -28,23 +33,40 @@ namespace {
 
 constexpr int kThreads = 256;
 
-// The section table, built at compile time; copied to LDS by every workgroup.
-__device__ const SectionTable g_section_table{};
+// The section table, built at compile time; copied to LDS by every workgroup,
+// 16 bytes a lane and all loads before the first store: a lane copying word
+// by word waits for memory nine times before its workgroup's first block.
+__device__ const __align__(16) SectionTable g_section_table{};
+static_assert(kSecEntries % 4 == 0, "the table is whole 16-byte pieces");
 
-template <int THREADS>
-__device__ __forceinline__ void load_section_table(uint32_t* tab)
+// `beside` is called with the loads under way: a kernel's other first loads
+// go there, so that its start waits for memory once.
+template <int THREADS, typename F>
+__device__ __forceinline__ void load_section_table(uint32_t* tab, F beside)
 {
-    for (int i = threadIdx.x; i < kSecEntries; i += THREADS)
-        tab[i] = g_section_table.e[i];
+    constexpr uint32_t kPieces = kSecEntries / 4;
+    constexpr int kRounds = (int)((kPieces + THREADS - 1) / THREADS);
+    const u32x4* g = reinterpret_cast<const u32x4*>(g_section_table.e);
+    u32x4 v[kRounds];
+#pragma unroll
+    for (int k = 0; k < kRounds; ++k) {
+        const uint32_t i = threadIdx.x + k * THREADS;
+        if (i < kPieces)
+            v[k] = g[i];
+    }
+    beside();
+#pragma unroll
+    for (int k = 0; k < kRounds; ++k) {
+        const uint32_t i = threadIdx.x + k * THREADS;
+        if (i < kPieces)
+            reinterpret_cast<u32x4*>(tab)[i] = v[k];
+    }
     __syncthreads();
 }
 
-// Staged blocks live word-major in LDS: word q of the block of lane l is at
-// lds[q * STRIDE + l] (STRIDE = the workgroup's lanes), so every lane-varying
-// read of a wave touches 64 distinct banks.
-// Stage one block (NW words at g) at lw = lds + lane.
-template <int NW, int STRIDE>
-__device__ __forceinline__ void stage_block(uint32_t* lw, const uint32_t* __restrict__ g, uint32_t (&w)[NW])
+// Loads of a lane's block words (no LDS yet): NW words at g.
+template <int NW>
+__device__ __forceinline__ void load_block_words(const uint32_t* __restrict__ g, uint32_t (&w)[NW])
 {
     if constexpr (NW % 4 == 0) {
         const u32x4* g4 = reinterpret_cast<const u32x4*>(g);
@@ -61,6 +83,16 @@ __device__ __forceinline__ void stage_block(uint32_t* lw, const uint32_t* __rest
         for (int k = 0; k < NW; ++k)
             w[k] = g[k];
     }
+}
+
+// Staged blocks live word-major in LDS: word q of the block of lane l is at
+// lds[q * STRIDE + l] (STRIDE = the workgroup's lanes), so every lane-varying
+// read of a wave touches 64 distinct banks.
+// Stage one block (NW words at g) at lw = lds + lane.
+template <int NW, int STRIDE>
+__device__ __forceinline__ void stage_block(uint32_t* lw, const uint32_t* __restrict__ g, uint32_t (&w)[NW])
+{
+    load_block_words<NW>(g, w);
 #pragma unroll
     for (int k = 0; k < NW; ++k)
         lw[k * STRIDE] = w[k];
@@ -80,18 +112,18 @@ __global__ void __launch_bounds__(kThreads) decode_blocks_kernel(const uint32_t*
                                                                  uint64_t nblocks, float* __restrict__ out)
 {
     __shared__ uint32_t lds[kThreads * kStagedWords<NW>];
-    __shared__ uint32_t tab[kSecEntries];
+    __shared__ __align__(16) uint32_t tab[kSecEntries];
     uint32_t* row = lds + threadIdx.x;
     clear_pad<NW, kThreads>(row);
-    load_section_table<kThreads>(tab);
-    const SectionReader sec = section_reader(tab);
+    load_section_table<kThreads>(tab, [] {});
+    const SectionReader sec = section_reader<kWideState<NW>>(tab);
     const uint64_t stride = (uint64_t)gridDim.x * kThreads;
     for (uint64_t i = (uint64_t)blockIdx.x * kThreads + threadIdx.x; i < nblocks; i += stride) {
         uint32_t w[NW];
         stage_block<NW, kThreads>(row, stream + (b0 + i) * NW, w);
-        int emax;
+        const int emax = block_emax(w[0]);
         uint32_t iv[16];
-        decode_block_ints<NW, kThreads>(row, sec, w[0], emax, iv);
+        decode_block_ints<NW, kThreads>(row, sec, w, iv, [] {});
         float4* o = reinterpret_cast<float4*>(out + 16 * i);
 #pragma unroll
         for (int r = 0; r < 4; ++r)
@@ -119,11 +151,11 @@ __global__ void __launch_bounds__(kDecThreads<NW>) decode_matrix_kernel(const ui
     constexpr int T = kDecThreads<NW>;
     constexpr uint32_t kWaves = T / 64;
     __shared__ uint32_t lds[T * kStagedWords<NW>];
-    __shared__ uint32_t tab[kSecEntries];
+    __shared__ __align__(16) uint32_t tab[kSecEntries];
     uint32_t* row = lds + threadIdx.x;
     clear_pad<NW, T>(row);
-    load_section_table<T>(tab);
-    const SectionReader sec = section_reader(tab);
+    load_section_table<T>(tab, [] {});
+    const SectionReader sec = section_reader<kWideState<NW>>(tab);
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64u);
     const uint32_t lane = threadIdx.x % 64u;
     const uint64_t stride = (uint64_t)gridDim.x * kWaves;
@@ -133,9 +165,9 @@ __global__ void __launch_bounds__(kDecThreads<NW>) decode_matrix_kernel(const ui
             continue;
         uint32_t w[NW];
         stage_block<NW, T>(row, stream + (bi * nbc + bj) * NW, w);
-        int emax;
+        const int emax = block_emax(w[0]);
         uint32_t iv[16];
-        decode_block_ints<NW, T>(row, sec, w[0], emax, iv);
+        decode_block_ints<NW, T>(row, sec, w, iv, [] {});
         if ((cols & 3u) == 0 && 4 * bi + 3 < rows) { // a whole block on 16-byte aligned rows
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
@@ -198,11 +230,21 @@ __global__ void __launch_bounds__(kThreads) encode_kernel(const float* __restric
 }
 
 // ------------------------------------------------------------ fused GEMV
+// An accumulator takes a block's FP32 sums v, scaled by the block's 2^(emax -
+// 30): add(v, scale(w0)), w0 the block's first word, emax + 127 in its bits
+// 1..8.
 struct Fp64Acc {
     static constexpr bool kPerProduct = false;
     double s;
     __device__ __forceinline__ void zero() { s = 0.0; }
     __device__ __forceinline__ void add(float p) { s += (double)p; }
+    // the scale as a double: it is exact there for every exponent, and one
+    // FMA (exact product, one rounding) scales and adds
+    __device__ __forceinline__ static double scale(uint32_t w0)
+    {
+        return __hiloint2double((int)(((w0 & 0x1FEu) << 19) + ((1023u - 157u) << 20)), 0);
+    }
+    __device__ __forceinline__ void add(float v, double scale) { s = __builtin_fma((double)v, scale, s); }
     __device__ __forceinline__ double value() const { return s; }
     __device__ __forceinline__ void merge_from_lane(int mask)
     {
@@ -229,6 +271,8 @@ struct TwoSumAcc {
         hi = s;
         lo += e;
     }
+    __device__ __forceinline__ static int scale(uint32_t w0) { return block_emax(w0) - 30; }
+    __device__ __forceinline__ void add(float v, int scale) { add(__builtin_ldexpf(v, scale)); }
     __device__ __forceinline__ double value() const { return (double)hi + (double)lo; }
     __device__ __forceinline__ void merge_from_lane(int mask)
     {
@@ -300,6 +344,22 @@ __device__ __forceinline__ void exact_block_coeffs(const uint32_t (&cf)[16], int
         sc[i] = __builtin_ldexpf(f[i], emax - 30);
 }
 
+// u of block column bj; zero past the matrix's last column.
+__device__ __forceinline__ float4 block_u(const float* __restrict__ u, uint32_t bj, uint32_t cols)
+{
+    const uint32_t j = 4 * bj;
+    if (j + 3 < cols)
+        return reinterpret_cast<const float4*>(u)[bj];
+    return make_float4(u[j], j + 1 < cols ? u[j + 1] : 0.0f, j + 2 < cols ? u[j + 2] : 0.0f, 0.0f);
+}
+
+__device__ __forceinline__ float4 block_ut(float4 uu)
+{
+    float ut[4];
+    lin_bt_u<float>(uu.x, uu.y, uu.z, uu.w, ut);
+    return make_float4(ut[0], ut[1], ut[2], ut[3]);
+}
+
 // The workgroup's lanes (1024, or 768 from 17 bits/value) form groups of
 // 2^lg lanes (4 to 512).  A group sweeps a block row's slab of block columns,
 // its lanes striding them; the workgroup's tile is (lanes >> lg) groups x rpg
@@ -311,13 +371,22 @@ __device__ __forceinline__ void exact_block_coeffs(const uint32_t (&cf)[16], int
 // two workgroups per CU: 1024-lane ones in 64 VGPRs (32 waves)
 template <int NW>
 constexpr int kGemvMinWaves = kGemvThreads<NW> == 1024 ? 8 : 6;
-// From 14 bits/value a 1024-lane workgroup's staging rows and section table
-// leave no room for its own row-sum doubles within two workgroups' LDS; the
-// sums then go over the staging rows once every wave has decoded its blocks,
-// which needs one tile row per group (the planner's choice there).
+// Block columns whose B^T u a workgroup holds in LDS: its slab's, made once
+// and read by all its block rows.  The planner's slabs of narrow groups have
+// at most 384; a wider slab (wide groups, so few block rows) makes B^T u at
+// each block.
+template <int NW>
+constexpr uint32_t kSlabVectors = NW >= 10 ? 64 : (NW == 6 || NW == 8 ? 128 : 384);
+// what LDS holds beside a workgroup's staging rows
+template <int NW>
+constexpr int kGemvTables = kSecEntries * 4 + (int)kSlabVectors<NW> * 16 * (kCanCut<NW> ? 2 : 1);
+// From 14 bits/value a 1024-lane workgroup's staging rows and tables leave no
+// room for its own row-sum doubles within two workgroups' LDS; the sums then
+// go over the staging rows once every wave has decoded its blocks, which
+// needs one tile row per group (the planner's choice there).
 template <int NW>
 constexpr bool kGemvSumsInStaging =
-    kGemvThreads<NW> * (kStagedWords<NW> * 4 + 8) + kSecEntries * 4 > kLdsPerWorkgroupOfTwo;
+    kGemvThreads<NW> * (kStagedWords<NW> * 4 + 8) + kGemvTables<NW> > kLdsPerWorkgroupOfTwo;
 
 template <int NW, typename Acc>
 __global__ void __launch_bounds__(kGemvThreads<NW>, kGemvMinWaves<NW>) gemv_kernel(const uint32_t* __restrict__ stream,
@@ -330,7 +399,11 @@ __global__ void __launch_bounds__(kGemvThreads<NW>, kGemvMinWaves<NW>) gemv_kern
     constexpr int THREADS = kGemvThreads<NW>;
     constexpr bool kShared = kGemvSumsInStaging<NW>;
     __shared__ __align__(16) uint32_t lds[THREADS * kStagedWords<NW>];
-    __shared__ uint32_t tab[kSecEntries];
+    __shared__ __align__(16) uint32_t tab[kSecEntries];
+    // the slab's B^T u (and u, for blocks that need the exact lift), or u for
+    // the Fig. 7 sums
+    constexpr bool kKeepU = Acc::kPerProduct || kCanCut<NW>;
+    __shared__ float4 slab_ut[Acc::kPerProduct ? 1 : kSlabVectors<NW>], slab_u[kKeepU ? kSlabVectors<NW> : 1];
     // a group's four row sums per tile row: one slot per wave when a group
     // spans whole waves, else one per group (over the staging rows when they
     // must share its LDS)
@@ -338,23 +411,37 @@ __global__ void __launch_bounds__(kGemvThreads<NW>, kGemvMinWaves<NW>) gemv_kern
     static_assert(!kShared || kStagedWords<NW> >= 2, "the row sums fit the staging rows");
     double* red = kShared ? reinterpret_cast<double*>(lds) : red_own;
     uint32_t* row = lds + threadIdx.x;
-    clear_pad<NW, THREADS>(row);
-    load_section_table<THREADS>(tab);
-    const SectionReader sec = section_reader(tab);
-
-    const uint32_t G = 1u << lg, groups = (uint32_t)THREADS >> lg;
-    const uint32_t grp = threadIdx.x >> lg, gl = threadIdx.x & (G - 1);
     const uint32_t tile = blockIdx.x / nslab, slab = blockIdx.x % nslab;
-    const uint32_t bi0 = bi_begin + tile * groups * rpg;
     const uint32_t bc0 = slab * slab_bc;
     const uint32_t bc1 = bc0 + slab_bc < nbc ? bc0 + slab_bc : nbc;
+    const bool slab_fits = slab_bc <= kSlabVectors<NW>;
+    const uint32_t G = 1u << lg, groups = (uint32_t)THREADS >> lg;
+    const uint32_t grp = threadIdx.x >> lg, gl = threadIdx.x & (G - 1);
+    const uint32_t bi0 = bi_begin + tile * groups * rpg;
+    // the first block's words: loaded before anything is waited for
+    const uint32_t* src = stream + ((uint64_t)(bi0 + grp) * nbc + bc0 + gl) * NW;
+    uint32_t w[NW];
+    if (bi0 + grp < bi_end && bc0 + gl < bc1)
+        load_block_words<NW>(src, w);
+    clear_pad<NW, THREADS>(row);
+    load_section_table<THREADS>(tab, [&] {
+        if (slab_fits) {
+            for (uint32_t j = threadIdx.x; j < bc1 - bc0; j += THREADS) {
+                const float4 uu = block_u(u, bc0 + j, cols);
+                if constexpr (kKeepU)
+                    slab_u[j] = uu;
+                if constexpr (!Acc::kPerProduct)
+                    slab_ut[j] = block_ut(uu);
+            }
+        }
+    });
+    const SectionReader sec = section_reader<kWideState<NW>>(tab);
 
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const bool wide = lg >= 6; // a group spans whole waves
     const uint32_t slot = wide ? (uint32_t)wave : grp, slot_len = 4 * rpg;
     const bool leader = wide ? lane == 0 : gl == 0;
     const int first_mask = wide ? 32 : (int)(G >> 1);
-    const float4* u4 = reinterpret_cast<const float4*>(u);
     // one tile row at a time (rolled loop: one copy of the decoder), so only
     // that row's four accumulators are live while blocks decode
 #pragma unroll 1
@@ -368,27 +455,36 @@ __global__ void __launch_bounds__(kGemvThreads<NW>, kGemvMinWaves<NW>) gemv_kern
 #pragma unroll
         for (int r = 0; r < 4; ++r)
             acc[r].zero();
-        const uint32_t* srow = stream + (uint64_t)bi * nbc * NW;
-        for (uint32_t bj = bc0 + gl; bi < bi_end && bj < bc1; bj += G) {
-            float4 uu;
-            if (4 * bj + 3 < cols) {
-                uu = u4[bj];
-            } else { // the partial last block column: u is zero past the last column
-                const uint32_t j = 4 * bj;
-                uu.x = u[j];
-                uu.y = j + 1 < cols ? u[j + 1] : 0.0f;
-                uu.z = j + 2 < cols ? u[j + 2] : 0.0f;
-                uu.w = 0.0f;
-            }
-            uint32_t w[NW];
-            stage_block<NW, THREADS>(row, srow + (uint64_t)bj * NW, w);
-            int emax;
+        uint32_t bj = bc0 + gl;
+        bool more = bi < bi_end && bj < bc1;
+        if (t > 0) {
+            src = stream + ((uint64_t)bi * nbc + bj) * NW;
+            if (more)
+                load_block_words<NW>(src, w);
+        }
+        while (more) {
+#pragma unroll
+            for (int k = 0; k < NW; ++k)
+                row[k * THREADS] = w[k];
+            const uint32_t w0 = w[0], at = bj;
+            uint32_t cur[NW];
+#pragma unroll
+            for (int k = 0; k < NW; ++k)
+                cur[k] = w[k];
+            bj += G;
+            src += (uint64_t)G * NW;
+            more = bj < bc1;
+            const auto next = [&] {
+                if (more)
+                    load_block_words<NW>(src, w);
+            };
             uint32_t iv[16];
             if constexpr (Acc::kPerProduct) {
                 // Fig. 7: each FP32 product of the decoded value and u is
                 // added to the FP64 sum on its own
-                decode_block_ints<NW, THREADS>(row, sec, w[0], emax, iv);
-                const int k = emax - 30;
+                decode_block_ints<NW, THREADS>(row, sec, cur, iv, next);
+                const float4 uu = slab_fits ? slab_u[at - bc0] : block_u(u, at, cols);
+                const int k = block_emax(w0) - 30;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     acc[r].add(__builtin_ldexpf((float)(int32_t)iv[4 * r], k) * uu.x);
@@ -400,24 +496,23 @@ __global__ void __launch_bounds__(kGemvThreads<NW>, kGemvMinWaves<NW>) gemv_kern
                 // coefficients against B^T u (FP32); B is applied once to the
                 // row group's sums below
                 bool cut;
-                decode_block_coeffs<NW, THREADS>(row, sec, w[0], emax, iv, cut);
-                float ut[4];
-                lin_bt_u<float>(uu.x, uu.y, uu.z, uu.w, ut);
-                const int k = emax - 30;
+                decode_block_coeffs<NW, THREADS>(row, sec, cur, iv, cut, next);
+                const float4 ut = slab_fits ? slab_ut[at - bc0] : block_ut(block_u(u, at, cols));
                 float v[4];
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    v[r] = (float)(int32_t)iv[4 * r] * ut[0];
-                    v[r] = __builtin_fmaf((float)(int32_t)iv[4 * r + 1], ut[1], v[r]);
-                    v[r] = __builtin_fmaf((float)(int32_t)iv[4 * r + 2], ut[2], v[r]);
-                    v[r] = __builtin_fmaf((float)(int32_t)iv[4 * r + 3], ut[3], v[r]);
+                    v[r] = (float)(int32_t)iv[4 * r] * ut.x;
+                    v[r] = __builtin_fmaf((float)(int32_t)iv[4 * r + 1], ut.y, v[r]);
+                    v[r] = __builtin_fmaf((float)(int32_t)iv[4 * r + 2], ut.z, v[r]);
+                    v[r] = __builtin_fmaf((float)(int32_t)iv[4 * r + 3], ut.w, v[r]);
                 }
                 if constexpr (kCanCut<NW>)
                     if (__any(cut) && cut) // rare: the exact lift, back to coefficient space
-                        exact_block_sums(iv, uu, v);
+                        exact_block_sums(iv, slab_fits ? slab_u[at - bc0] : block_u(u, at, cols), v);
+                const auto scale = Acc::scale(w0);
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
-                    acc[r].add(__builtin_ldexpf(v[r], k));
+                    acc[r].add(v[r], scale);
             }
         }
         // reduce the row's sums across the group's lanes within the wave
@@ -646,27 +741,6 @@ __global__ void __launch_bounds__(kThreads) mrhs_btu_kernel(const void* __restri
     }
 }
 
-// Loads of a lane's block words (no LDS yet): NW words at g.
-template <int NW>
-__device__ __forceinline__ void load_block_words(const uint32_t* __restrict__ g, uint32_t (&w)[NW])
-{
-    if constexpr (NW % 4 == 0) {
-        const u32x4* g4 = reinterpret_cast<const u32x4*>(g);
-#pragma unroll
-        for (int k = 0; k < NW / 4; ++k) {
-            const u32x4 v = __builtin_nontemporal_load(g4 + k);
-            w[4 * k] = v.x;
-            w[4 * k + 1] = v.y;
-            w[4 * k + 2] = v.z;
-            w[4 * k + 3] = v.w;
-        }
-    } else {
-#pragma unroll
-        for (int k = 0; k < NW; ++k)
-            w[k] = g[k];
-    }
-}
-
 // FP32 U: the B operands of one quarter (4 block columns from bc) for this
 // lane (j = lane % 16, block column bc + lane / 16): B^T U's four values
 // m = 0..3 of right-hand side 16 n + j, one MFMA each.
@@ -735,15 +809,15 @@ __global__ void __launch_bounds__(64 * mrhs_waves(NT, (MrhsMath)MATH), mrhs_wave
     // one for the 4x4x1 path (its groups of 4 lie in different lanes)
     constexpr int NA = NARROW ? 1 : NT;
     __shared__ uint32_t lds[T * kStagedWords<NW>];
-    __shared__ uint32_t tab[kSecEntries];
+    __shared__ __align__(16) uint32_t tab[kSecEntries];
     // the wave's A tile: FP32 quarters (16 x 16, swizzled), BF16 halves
     // (16 x 32, swizzled), or three BF16 halves (one per part) for X6
     __shared__ __align__(16) float atile[W][X6 ? 3 * 16 * kATileStride
                                               : (BF16U ? 16 * kATileBf16Stride / 2 : 16 * kATile32Stride)];
     uint32_t* row = lds + threadIdx.x;
     clear_pad<NW, T>(row);
-    load_section_table<T>(tab); // the last workgroup barrier
-    const SectionReader sec = section_reader(tab);
+    load_section_table<T>(tab, [] {}); // the last workgroup barrier
+    const SectionReader sec = section_reader<kWideState<NW>>(tab);
 
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const uint32_t tile = blockIdx.x / nslab, slab = blockIdx.x % nslab;
@@ -794,7 +868,10 @@ __global__ void __launch_bounds__(64 * mrhs_waves(NT, (MrhsMath)MATH), mrhs_wave
 #pragma unroll
         for (int q = 0; q < NW; ++q)
             row[q * T] = w[q];
-        const uint32_t w0 = w[0];
+        uint32_t cur[NW];
+#pragma unroll
+        for (int q = 0; q < NW; ++q)
+            cur[q] = w[q];
         if constexpr (kAhead) {
             const bool valid = bi < bi_end && cb + 16 + c < bc1;
             if (valid)
@@ -835,10 +912,10 @@ __global__ void __launch_bounds__(64 * mrhs_waves(NT, (MrhsMath)MATH), mrhs_wave
                 mrhs_load_bq<NT>(btf, cb + 4 * q, lane, bq[q]);
         }
         // ---- decode one block per lane: scaled coefficients (registers)
-        int emax;
+        const int emax = block_emax(cur[0]);
         uint32_t cf[16];
         bool cut;
-        decode_block_coeffs<NW, T>(row, sec, w0, emax, cf, cut);
+        decode_block_coeffs<NW, T>(row, sec, cur, cf, cut, [] {});
         float sc[16];
 #pragma unroll
         for (int v = 0; v < 16; ++v)

@@ -39,79 +39,109 @@ namespace wh {
 
 namespace {
 
-// Workgroup sizes: 256 lanes, or for the fused GEMV 1024 from 2^18 lanes of
-// work up (16 waves per CU share one section table, where LDS holds only two
-// 256-lane workgroups, 8 waves).
-constexpr int kVarThreadsSmall = 256, kVarThreadsLarge = 1024;
+// Workgroup sizes: 256 lanes (two workgroups a CU in LDS), or for the fused
+// GEMV 768 from 2^18 lanes of work up (12 waves per CU share one section
+// table, where two 256-lane workgroups make 8).
+constexpr int kVarThreadsSmall = 256, kVarThreadsLarge = 768;
 constexpr uint64_t kVarLargeFrom = 1ull << 18;
 
-__device__ const SectionTable g_var_section_table{};
+__device__ const __align__(16) SectionTable g_var_section_table{};
 
 template <int T>
 __device__ __forceinline__ void load_table(uint32_t* tab)
 {
-    for (int i = threadIdx.x; i < kSecEntries; i += T)
-        tab[i] = g_var_section_table.e[i];
+    constexpr uint32_t kPieces = kSecEntries / 4;
+    constexpr int kRounds = (int)((kPieces + T - 1) / T);
+    const u32x4* g = reinterpret_cast<const u32x4*>(g_var_section_table.e);
+    u32x4 v[kRounds];
+#pragma unroll
+    for (int k = 0; k < kRounds; ++k) {
+        const uint32_t i = threadIdx.x + k * T;
+        if (i < kPieces)
+            v[k] = g[i];
+    }
+#pragma unroll
+    for (int k = 0; k < kRounds; ++k) {
+        const uint32_t i = threadIdx.x + k * T;
+        if (i < kPieces)
+            reinterpret_cast<u32x4*>(tab)[i] = v[k];
+    }
     __syncthreads();
 }
 
-// Word i of a lane's code view (g = the word holding its group's first bit,
-// lim = the words from there to the end of the code); zero past the end.
-__device__ __forceinline__ uint32_t vword(const uint32_t* __restrict__ g, uint32_t lim, uint32_t i)
-{
-    return i < lim ? g[i] : 0u;
-}
+// A lane's code in LDS: a ring of 32 words, filled 16 bytes at a time, so that
+// each piece of the code is loaded from global memory once.  A block of P
+// planes takes at most 25 + 17 P bits, whatever they are: the 9-bit header,
+// at most 16 verbatim bits a plane after the first, one ending group bit a
+// plane, and across all planes at most 16 run-opening bits and 16 run bits (a
+// run passes each coefficient once).  With P <= 32, the start offset (< 32)
+// and the last 32-bit window, every read stays below bit 632 of the block's
+// first word, and the 32 bits read ahead below bit 664: 21 words hold any
+// block, 24 from the 16-byte boundary at or before it.  The ring holds 32: the other two pieces load while the block
+// decodes and go to LDS after it, so a lane waits for memory only behind a
+// block of more than 8 words.  Two words after the ring mirror its first two,
+// so that a read's words are always adjacent.
+constexpr uint32_t kVarRing = 32, kVarRow = kVarRing + 2, kVarNeed = 24;
 
-// 32 code bits from bit position pos of the view.
-__device__ __forceinline__ uint32_t vwindow(const uint32_t* __restrict__ g, uint32_t lim, uint32_t pos)
-{
-    const uint32_t q = pos >> 5;
-    return funnel(vword(g, lim, q + 1), vword(g, lim, q), pos & 31u);
-}
-
-// A lane's code in LDS: a ring of kVarRing words, refilled 16 bytes at a
-// time, so that each piece of the code is loaded from global memory once.
-// A block of P planes takes at most 25 + 17 P bits: the 9-bit header, at
-// most 16 verbatim bits a plane after the first, one ending group bit a
-// plane, and across all planes at most 16 run-starting group bits and 16 run
-// bits (a run passes each coefficient once).  With P <= 32, the start
-// offset (< 32) and the last 32-bit window, every read stays below bit 632
-// of the block's first word: 20 words hold any block.  Before a block the
-// ring is filled through 24 words from the 16-byte boundary at or before
-// that word (up to 3 words earlier): 6 pieces, of which the blocks before
-// have already loaded all but the new ones.  One word after the ring
-// mirrors its first, so that a window's two words are always adjacent.
-constexpr uint32_t kVarRing = 24, kVarRow = kVarRing + 1;
-
-// Reading a lane's code straight from global memory: two loads a window.
-struct GlobalBits {
-    const uint32_t* g;
-    uint32_t lim;
-    __device__ __forceinline__ uint32_t bits_at(uint32_t pos) const { return vwindow(g, lim, pos); }
-    __device__ __forceinline__ uint32_t window(const SectionReader&, uint32_t S) const
-    {
-        return bits_at(S >> kPosShift);
-    }
-};
-
-// Reading a block from a lane's ring at lw[k * T]: positions count from bit 0
-// of the block's first 16-byte piece, which sits at word sb of the ring.  A
-// window at or past word kVarRing - 1 reads the last word's slot (the word
-// index is clamped), so a block that runs past 32 * (kVarRing - 1) bits
-// must be decoded again from global memory.
 template <int T>
-struct StagedBits {
-    const uint32_t* lw;
-    uint32_t sb;
-    __device__ __forceinline__ uint32_t bits_at(uint32_t pos) const
+struct VarBits {
+    const uint32_t* base; // the 16-byte boundary at or before the group's first word
+    uint32_t first, end;  // words of the view, counted from base; others read as zero
+    uint32_t* row;        // the lane's column in LDS
+    uint32_t head;        // words from base loaded so far (a multiple of 4)
+
+    // the group's view of the code from bit `start`; returns the position of
+    // that bit from base
+    __device__ __forceinline__ uint32_t open(const uint32_t* code, uint64_t nwords, uint64_t start, uint32_t* lds_row)
     {
-        uint32_t q = __builtin_elementwise_min(pos >> 5, kVarRing - 1u) + sb;
-        q = __builtin_elementwise_min(q, q - kVarRing); // the ring's slot
-        return funnel(lw[(q + 1) * T], lw[q * T], pos & 31u);
+        const uint64_t q = start >> 5;
+        const uint64_t left = q < nwords ? nwords - q : 0;
+        const uint32_t* g = code + (q < nwords ? q : 0);
+        first = (uint32_t)(reinterpret_cast<uintptr_t>(g) >> 2) & 3u;
+        base = g - first;
+        end = first + (uint32_t)(left < 0xFFFFFFF0ull ? left : 0xFFFFFFF0ull);
+        row = lds_row;
+        head = 0u;
+        return 32u * first + (uint32_t)(start & 31u);
     }
-    __device__ __forceinline__ uint32_t window(const SectionReader&, uint32_t S) const
+    __device__ __forceinline__ u32x4 load(uint32_t h) const
     {
-        return bits_at(S >> kPosShift);
+        if (h >= first && h + 4u <= end)
+            return *reinterpret_cast<const u32x4*>(base + h);
+        u32x4 v;
+#pragma unroll
+        for (uint32_t i = 0; i < 4; ++i)
+            v[i] = (h + i >= first && h + i < end) ? base[h + i] : 0u;
+        return v;
+    }
+    __device__ __forceinline__ void put(uint32_t h, u32x4 v)
+    {
+        const uint32_t slot = h & (kVarRing - 1u);
+#pragma unroll
+        for (uint32_t i = 0; i < 4; ++i)
+            row[(slot + i) * T] = v[i];
+        if (slot == 0u) { // the mirror words
+            row[kVarRing * T] = v[0];
+            row[(kVarRing + 1u) * T] = v[1];
+        }
+    }
+    // the whole ring, from base
+    __device__ __forceinline__ void fill()
+    {
+        u32x4 v[kVarRing / 4];
+#pragma unroll
+        for (uint32_t k = 0; k < kVarRing / 4; ++k)
+            v[k] = load(4u * k);
+#pragma unroll
+        for (uint32_t k = 0; k < kVarRing / 4; ++k)
+            put(4u * k, v[k]);
+        head = kVarRing;
+    }
+    // 32 bits from bit `pos`
+    __device__ __forceinline__ uint32_t bits(const SectionReader& sec, uint32_t pos) const
+    {
+        const uint32_t* p = row + ((pos >> 5) & (kVarRing - 1u)) * T;
+        return funnel(p[T], p[0], pos & 31u);
     }
 };
 
@@ -126,148 +156,79 @@ __host__ __device__ __forceinline__ int var_planes(int mode, int param, int emax
 }
 
 // Planes P..LAST of a half, the lanes whose lowest plane lo is not above the
-// plane in lockstep; the plane words of the others are zero.  With no bit
+// plane in lockstep; the plane words of the others stay zero.  With no bit
 // budget, the implied 1 at the end of a run is always coefficient 15's.
-// Returns true when no lane has a plane below the last one read.
-template <int P, int LAST, typename Bits>
-__device__ __forceinline__ bool var_planes_from(const Bits& rd, const SectionReader& sec, uint32_t lo, uint32_t& S,
-                                                uint32_t (&G)[8])
+template <int P, int LAST, int T>
+__device__ __forceinline__ void var_planes_from(const uint32_t* row, const SectionReader& sec, uint32_t lo,
+                                                PlaneCursor& c, uint32_t (&G)[8])
 {
     if constexpr (P >= LAST) {
-        const bool live = (uint32_t)P >= lo;
-        if (!__any(live)) { // every lane is done: the half's planes left are zero
-            clear_planes<P>(G);
-            return true;
+        if ((uint32_t)P >= lo) {
+            uint32_t xv;
+            const uint32_t ones = plane_bits<true>(sec, c, bits_ahead<T>(row, sec, c.S), xv);
+            store_plane<P>(G, ones, xv);
+            var_planes_from<P - 1, LAST, T>(row, sec, lo, c, G);
         }
-        uint32_t ones = 0u, xv = 0u;
-        if (live)
-            ones = plane_bits(rd, sec, S, xv);
-        store_plane<P>(G, ones, xv);
-        return var_planes_from<P - 1, LAST>(rd, sec, lo, S, G);
-    } else {
-        return !__any((uint32_t)LAST > lo);
     }
 }
 
-// Decode the block at pos (advanced past it) into its 16 transform
-// coefficients (two's complement, local order 4r + c) and emax.  A lane with
-// live == false decodes a zero block and does not move.  Returns whether the
-// block is nonzero.
-template <typename Bits>
-__device__ __forceinline__ bool var_block_coeffs(const Bits& rd, const SectionReader& sec, int mode, int param, bool live,
-                                                 uint32_t& pos, int& emax, uint32_t (&cf)[16])
+// The next block of a lane's view at bit pos (from the view's base; advanced
+// past it), decoded into its 16 transform coefficients (two's complement,
+// local order 4r + c) and emax.  A lane with live == false decodes a zero
+// block and does not move.  Returns whether the block is nonzero.
+template <int T>
+__device__ __forceinline__ bool var_next_block(VarBits<T>& rd, const SectionReader& sec, int mode, int param,
+                                               bool live, uint32_t& pos, int& emax, uint32_t (&cf)[16])
 {
-    const uint32_t h = live ? rd.bits_at(pos) : 0u;
+    // pieces the ring has room for; the block reads none of the last two
+    uint32_t n = live ? (((pos >> 5) & ~3u) + kVarRing - rd.head) >> 2 : 0u;
+    while (__any(n > (kVarRing - kVarNeed) / 4u)) {
+        if (n > (kVarRing - kVarNeed) / 4u) {
+            rd.put(rd.head, rd.load(rd.head));
+            rd.head += 4u;
+            --n;
+        }
+    }
+    u32x4 v0, v1;
+    if (n > 0u)
+        v0 = rd.load(rd.head);
+    if (n > 1u)
+        v1 = rd.load(rd.head + 4u);
+
+    const uint32_t h = live ? rd.bits(sec, pos) : 0u;
     const bool nz = (h & 1u) != 0;
-    emax = (int)((h >> 1) & 0xFFu) - 127;
+    emax = block_emax(h);
     const uint32_t lo = nz ? (uint32_t)(32 - var_planes(mode, param, emax)) : 32u;
-    uint32_t S = state_at(pos + 9u); // of a nonzero block
+    PlaneCursor c{state_at(pos + 9u), rd.bits(sec, pos + 7u)}; // of a nonzero block
     uint32_t H[8], L[8];
-    const bool none_below = var_planes_from<31, 16>(rd, sec, lo, S, H);
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+        H[q] = L[q] = 0u;
+    var_planes_from<31, 16, T>(rd.row, sec, lo, c, H);
+    const bool low = __any(lo < 16u);
+    if (low)
+        var_planes_from<15, 0, T>(rd.row, sec, lo, c, L);
+    if (live)
+        pos = nz ? (c.S >> kPosShift) + 2u : pos + 1u;
+
+    if (n > 0u)
+        rd.put(rd.head, v0);
+    if (n > 1u)
+        rd.put(rd.head + 4u, v1);
+    rd.head += 4u * n;
+
     complement_odd_planes(H);
     transpose_half(H);
-    if (none_below) {
+    if (low) {
+        complement_odd_planes(L);
+        transpose_half(L);
+    } else {
         const uint32_t none = vgpr_const(kNega);
 #pragma unroll
         for (int q = 0; q < 8; ++q)
             L[q] = none;
-    } else {
-        var_planes_from<15, 0>(rd, sec, lo, S, L);
-        complement_odd_planes(L);
-        transpose_half(L);
     }
     assemble_coeffs(H, L, cf);
-    if (live)
-        pos = nz ? (S >> kPosShift) + 2u : pos + 1u;
-    return nz;
-}
-
-// A lane's view of the code from the group starting at bit `start`.
-__device__ __forceinline__ void lane_view(const uint32_t* code, uint64_t nwords, uint64_t start, const uint32_t*& g,
-                                          uint32_t& lim, uint32_t& pos)
-{
-    const uint64_t q = start >> 5;
-    const uint64_t left = q < nwords ? nwords - q : 0;
-    g = code + (q < nwords ? q : 0);
-    lim = (uint32_t)(left < 0xFFFFFFFFull ? left : 0xFFFFFFFFull);
-    pos = (uint32_t)(start & 31u);
-}
-
-// A lane's ring: `head` is the view word (counted from the 16-byte boundary
-// at or before the view's first word) up to which it is filled, a multiple
-// of 4; `hs` the ring piece (0..5) that word goes to.  Both start at 0.
-struct VarRing {
-    uint32_t head = 0u, hs = 0u;
-};
-
-// The next block of a lane's view at bit pos (advanced past it): the ring is
-// refilled through 24 words from the block's 16-byte piece and the block
-// decoded there.  A piece inside the view is one 16-byte load, a piece
-// reaching before the view's first word or past its end is read word by word
-// (zero outside).  A block that read past the ring would be decoded again
-// from global memory; by the bound above that never happens for codes of at
-// most 32 planes, and the check keeps a code that breaks the bound (a
-// corrupt stream) from decoding out of stale ring words.
-template <int T>
-__device__ __forceinline__ bool var_next_block(const uint32_t* g, uint32_t lim, uint32_t* row, const SectionReader& sec,
-                                               int mode, int param, bool live, uint32_t& pos, int& emax,
-                                               uint32_t (&cf)[16], VarRing& ring)
-{
-    constexpr uint32_t kPieces = kVarRing / 4;
-    const uint32_t a = (uint32_t)(reinterpret_cast<uintptr_t>(g) >> 2) & 3u; // g's word within its 16 bytes
-    const uint32_t b = ((pos >> 5) + a) & ~3u; // the block's first piece, in words from g - a
-    const uint32_t h0 = __builtin_elementwise_max(ring.head, b);
-    const uint32_t n = live ? (b + kVarRing - h0) >> 2 : 0u; // pieces to load
-    u32x4 v[kPieces];
-#pragma unroll
-    for (uint32_t k = 0; k < kPieces; ++k) {
-        v[k] = u32x4{0u, 0u, 0u, 0u};
-        if (__any(k < n)) {
-            if (k < n) {
-                const int64_t s0 = (int64_t)(h0 + 4 * k) - (int64_t)a; // view word of the piece's first word
-                if (s0 >= 0 && s0 + 4 <= (int64_t)lim) {
-                    v[k] = *reinterpret_cast<const u32x4*>(g + s0);
-                } else {
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        v[k][i] = (s0 + i >= 0 && s0 + i < (int64_t)lim) ? g[s0 + i] : 0u;
-                }
-            }
-        }
-    }
-    // the pieces into their ring slots, piece h0 / 4 + k at slot c0 + k
-    // (mod 6): on from the head's slot, or from slot 0 when the block starts
-    // past the ring's end (all 6 pieces are new then)
-    const uint32_t c0 = h0 > ring.head ? 0u : ring.hs;
-#pragma unroll
-    for (uint32_t k = 0; k < kPieces; ++k) {
-        if (k < n) {
-            uint32_t c = c0 + k;
-            c = __builtin_elementwise_min(c, c - kPieces);
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                row[(4 * c + i) * T] = v[k][i];
-            if (c == 0)
-                row[kVarRing * T] = v[k][0]; // the mirror word
-        }
-    }
-    if (live) {
-        const uint32_t hs = c0 + n;
-        ring.hs = __builtin_elementwise_min(hs, hs - kPieces);
-        ring.head = b + kVarRing;
-    }
-    // the block's piece b sits where the ring's head is now (24 words on)
-    uint32_t lpos = pos + 32u * a - 32u * b;
-    bool nz = var_block_coeffs(StagedBits<T>{row, 4u * ring.hs}, sec, mode, param, live, lpos, emax, cf);
-    const bool over = live && lpos >= 32u * (kVarRing - 1u);
-    if (__any(over)) {
-        if (over) {
-            uint32_t p = pos;
-            nz = var_block_coeffs(GlobalBits{g, lim}, sec, mode, param, true, p, emax, cf);
-            lpos = p + 32u * a - 32u * b;
-        }
-    }
-    pos = lpos + 32u * b - 32u * a;
     return nz;
 }
 
@@ -287,18 +248,18 @@ __global__ void __launch_bounds__(kVarThreadsSmall) var_decode_kernel(
 {
     constexpr int T = kVarThreadsSmall;
     static_assert(32 % kVarSpan == 0, "spans tile a group");
-    __shared__ uint32_t tab[kSecEntries];
+    __shared__ __align__(16) uint32_t tab[kSecEntries];
     __shared__ uint32_t stage[T * kVarRow];
     uint32_t* row = stage + threadIdx.x;
     load_table<T>(tab);
-    const SectionReader sec = section_reader(tab);
+    const SectionReader sec = section_reader<true>(tab);
     const uint64_t lane_id = (uint64_t)blockIdx.x * T + threadIdx.x;
     const bool in = lane_id < nlanes;
     const uint32_t bi = in ? (uint32_t)(lane_id / ngroups) : 0u, a = in ? (uint32_t)(lane_id % ngroups) : 0u;
-    const uint32_t* g;
-    uint32_t lim, pos;
-    lane_view(code, nwords, in ? index[lane_id] : 0ull, g, lim, pos);
-    VarRing ring;
+    VarBits<T> rd;
+    uint32_t pos = rd.open(code, nwords, in ? index[lane_id] : 0ull, row);
+    if (in)
+        rd.fill();
     // rows of whole blocks: every span of whole blocks starts 16-byte aligned
     const bool whole = (cols & 3u) == 0u;
     for (uint32_t j0 = 0; j0 < 32u; j0 += kVarSpan) {
@@ -308,7 +269,7 @@ __global__ void __launch_bounds__(kVarThreadsSmall) var_decode_kernel(
             const uint32_t bj = a * 32u + j0 + s;
             int emax;
             uint32_t iv[16];
-            var_next_block<T>(g, lim, row, sec, mode, param, in && bj < nbc, pos, emax, iv, ring);
+            var_next_block<T>(rd, sec, mode, param, in && bj < nbc, pos, emax, iv);
             inv_xform(iv);
 #pragma unroll
             for (int i = 0; i < 16; ++i)
@@ -382,12 +343,12 @@ struct VarTwoSumAcc {
 // takes group slab * G + gl (32 blocks).  Output row i of the range is
 // matrix row 4 * bi_begin + skip + i.
 template <int T, typename Acc>
-__global__ void __launch_bounds__(T) var_gemv_kernel(
+__global__ void __launch_bounds__(T, T == kVarThreadsSmall ? 2 : 3) var_gemv_kernel(
     const uint64_t* __restrict__ index, const uint32_t* __restrict__ code, uint64_t nwords, int mode, int param,
     const float* __restrict__ u, float* __restrict__ y, double* __restrict__ part, uint32_t nbc, uint32_t ngroups,
     uint32_t bi_begin, uint32_t bi_end, uint32_t nslab, uint32_t cols, uint32_t nrows, uint32_t skip, uint32_t lg)
 {
-    __shared__ uint32_t tab[kSecEntries];
+    __shared__ __align__(16) uint32_t tab[kSecEntries];
     // the lanes' staging rows; after the blocks, the row sums per group
     // (<= 512) and row of the block
     __shared__ double stage_d[T * kVarRow / 2];
@@ -395,17 +356,17 @@ __global__ void __launch_bounds__(T) var_gemv_kernel(
     uint32_t* row = reinterpret_cast<uint32_t*>(stage_d) + threadIdx.x;
     double* red = stage_d;
     load_table<T>(tab);
-    const SectionReader sec = section_reader(tab);
+    const SectionReader sec = section_reader<true>(tab);
     const uint32_t G = 1u << lg, groups = (uint32_t)T >> lg;
     const uint32_t grp = threadIdx.x >> lg, gl = threadIdx.x & (G - 1);
     const uint32_t tile = blockIdx.x / nslab, slab = blockIdx.x % nslab;
     const uint32_t bi = bi_begin + tile * groups + grp;
     const uint32_t a = slab * G + gl;
     const bool in = bi < bi_end && a < ngroups;
-    const uint32_t* g;
-    uint32_t lim, pos;
-    lane_view(code, nwords, in ? index[(uint64_t)bi * ngroups + a] : 0ull, g, lim, pos);
-    VarRing ring;
+    VarBits<T> rd;
+    uint32_t pos = rd.open(code, nwords, in ? index[(uint64_t)bi * ngroups + a] : 0ull, row);
+    if (in)
+        rd.fill();
     Acc acc[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r)
@@ -421,7 +382,7 @@ __global__ void __launch_bounds__(T) var_gemv_kernel(
         }
         int emax;
         uint32_t iv[16];
-        const bool nz = var_next_block<T>(g, lim, row, sec, mode, param, live, pos, emax, iv, ring);
+        const bool nz = var_next_block<T>(rd, sec, mode, param, live, pos, emax, iv);
         if (live && nz) {
             // the exact integer inverse transform (not B (C (B^T u))): a
             // coefficient cut to its top planes can reach -2^31, where the
