@@ -700,96 +700,142 @@ __device__ __forceinline__ void lin_bt_u(T u0, T u1, T u2, T u3, T (&ut)[4])
 }
 
 // --------------------------------------------------------------- encoding
-// Bit writer over a lane-private word array of NW words (zeroed first).
-template <int NW>
-struct BitSink {
-    uint32_t w[NW];
-    uint32_t pos;
+// The coefficients' planes, from the decoder's transpose run the other way: a
+// half's registers are put together from the coefficients' bytes, and the same
+// three exchange stages give the planes.
+__device__ __forceinline__ void coeff_planes(const uint32_t (&n)[16], bool high, uint32_t (&G)[8])
+{
+#pragma unroll
+    for (int t = 0; t < 8; ++t) // bytes 2 and 3 (high) or 0 and 1 of coefficients t and t + 8, alternating
+        G[t] = __builtin_amdgcn_perm(n[t + 8], n[t], high ? 0x07030602u : 0x05010400u);
+    transpose_half(G);
+}
 
-    __device__ __forceinline__ void put(uint32_t bits, uint32_t k) // k <= 16
+// A section's code comes 8 coefficients at a time from a table: the tokens of
+// the bits c (each one of c: a 1 that opens its run, the run's zeros, the 1),
+// in bits 0..15, how many bits they are in bits 16..20, and the coefficients
+// they pass in bits 24..27.
+struct EncodeTable {
+    uint32_t e[256];
+    constexpr EncodeTable() : e()
     {
-        if (k == 0u)
-            return;
-        const uint32_t q = pos >> 5, o = pos & 31u;
-        w[q] |= bits << o;
-        if (o + k > 32u)
-            w[q + 1] |= bits >> (32u - o);
-        pos += k;
+        for (int c = 0; c < 256; ++c) {
+            uint32_t code = 0, len = 0, adv = 0;
+            for (uint32_t i = 0; i < 8; ++i) {
+                if ((c >> i & 1) == 0)
+                    continue;
+                code |= 1u << len | 1u << (len + 1u + (i - adv));
+                len += 2u + (i - adv);
+                adv = i + 1u;
+            }
+            e[c] = code | len << 16 | adv << 24;
+        }
     }
 };
 
-// Biased exponent field F of a value.  For a normal value the binade
-// exponent is e = F - 126 (|f| in [2^(e-1), 2^e)); a subnormal has F = 0 and
-// e <= -126, which the clamp at -126 turns into F - 126 as well.  So
-// emax = max over nonzero values of F, minus 126.
-__device__ __forceinline__ uint32_t exp_field(float f) { return (__float_as_uint(f) >> 23) & 0xFFu; }
+// A block's code as it is written: the next free bit, and how many
+// coefficients are significant.
+struct EncodeState {
+    uint32_t pos, nsig;
+};
 
-// Encode 16 values (local index 4r + c) into out (NW words).  Returns false
-// if a value is NaN or Inf (the block is then written as a zero block).
-template <int NW>
-__device__ __forceinline__ bool encode_block(const float (&f)[16], uint32_t (&out)[NW])
+// Code of one plane word x (at most 31 bits: the nsig verbatim bits, then the
+// section's tokens and the 0 that ends it unless every coefficient is
+// significant) into `sink`.
+template <int NW, typename Sink>
+__device__ __forceinline__ void encode_plane(uint32_t x, const uint32_t* tab, EncodeState& st, Sink& sink)
 {
-    constexpr uint32_t kMaxBits = 32u * NW;
-    BitSink<NW> sink;
-#pragma unroll
-    for (int k = 0; k < NW; ++k)
-        sink.w[k] = 0u;
-    sink.pos = 0u;
-    bool finite = true, nonzero = false;
-    uint32_t emax_field = 0u;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-        const uint32_t e = exp_field(f[v]);
-        finite = finite && e != 0xFFu;
-        if (f[v] != 0.0f) {
-            nonzero = true;
-            emax_field = e > emax_field ? e : emax_field;
+    const uint32_t r = x >> st.nsig;
+    uint32_t e = tab[r & 0xFFu];
+    uint32_t code = e & 0xFFFFu, len = __builtin_amdgcn_ubfe(e, 16u, 5u), adv = e >> 24;
+    if (__any(r > 0xFFu)) {
+        if (r > 0xFFu) {
+            // the next token's run starts with the zeros left of the first 8
+            e = tab[r >> 8];
+            const uint32_t z = 8u - adv;
+            code |= (1u | ((e & 0xFFFFu) >> 1) << (1u + z)) << len;
+            len += __builtin_amdgcn_ubfe(e, 16u, 5u) + z;
+            adv = 8u + (e >> 24);
         }
     }
-    if (finite && nonzero) {
-        const int emax = (int)emax_field - 126;
-        sink.put(1u, 1u);
-        sink.put((uint32_t)(emax + 127), 8u);
+    const uint32_t sig = st.nsig + adv;
+    // coefficient 15's 1 is implied; anything less ends with a 0
+    len = sig == 16u ? __builtin_elementwise_sub_sat(len, 1u) : len + 1u;
+    const uint32_t bits = __builtin_amdgcn_ubfe(x, 0u, st.nsig) | __builtin_amdgcn_ubfe(code, 0u, len) << (st.nsig & 31u);
+    sink.put(st.pos, bits);
+    // past the budget everything goes to the two words after the block
+    st.pos = __builtin_elementwise_min(st.pos + st.nsig + len, 32u * NW);
+    st.nsig = sig;
+}
+
+// Planes of a half from P = p0 + 15 down; stops when the wave's blocks are full.
+template <int NW, int P, int LAST, typename Sink>
+__device__ __forceinline__ bool encode_planes(const uint32_t (&G)[8], const uint32_t* tab, EncodeState& st, Sink& sink)
+{
+    if constexpr (P >= LAST) {
+        if (!__any(st.pos < 32u * NW))
+            return false;
+        encode_plane<NW>(P & 8 ? G[P & 7] >> 16 : G[P & 7] & 0xFFFFu, tab, st, sink);
+        return encode_planes<NW, P - 1, LAST>(G, tab, st, sink);
+    } else {
+        return true;
+    }
+}
+
+// Encode 16 values (local index 4r + c) into `sink`, whose words are zero:
+// put(pos, bits) ORs bits in at bit pos, pos <= 32 * NW, up to 31 bits on.
+// Returns false if a value is NaN or Inf (the block is then a zero block).
+template <int NW, typename Sink>
+__device__ __forceinline__ bool encode_block(const float (&f)[16], const uint32_t* tab, Sink& sink)
+{
+    // the largest magnitude's bit pattern: its exponent field F gives emax =
+    // F - 126 (|f| in [2^(emax-1), 2^emax); a subnormal has F = 0, emax = -126)
+    uint32_t m = 0u;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        const uint32_t a = __float_as_uint(f[v]) & 0x7FFFFFFFu;
+        m = a > m ? a : m;
+    }
+    const bool finite = m < 0x7F800000u, live = finite && m != 0u;
+    const int emax = (int)(m >> 23) - 126;
+    uint32_t n[16];
+    {
         uint32_t iv[16];
 #pragma unroll
         for (int v = 0; v < 16; ++v)
-            iv[v] = (uint32_t)(int32_t)__builtin_truncf(__builtin_ldexpf(f[v], 30 - emax));
+            iv[v] = finite ? (uint32_t)(int32_t)__builtin_ldexpf(f[v], 30 - emax) : 0u; // truncates
         fwd_xform(iv);
-        uint32_t nb[16];
 #pragma unroll
         for (int s = 0; s < 16; ++s)
-            nb[s] = (iv[order_of(s)] + kNega) ^ kNega;
-        uint32_t left = kMaxBits - 9u, nsig = 0u;
-        for (int p = 31; p >= 0 && left != 0u; --p) {
-            uint32_t x = 0u;
-#pragma unroll
-            for (int s = 0; s < 16; ++s)
-                x |= ((nb[s] >> p) & 1u) << s;
-            const uint32_t m = nsig < left ? nsig : left;
-            sink.put(x & ((1u << m) - 1u), m);
-            x >>= m;
-            left -= m;
-            while (nsig < 16u && left != 0u) {
-                const uint32_t g = x != 0u;
-                sink.put(g, 1u);
-                left -= 1u;
-                if (!g)
-                    break;
-                while (nsig < 15u && left != 0u) {
-                    const uint32_t bit = x & 1u;
-                    sink.put(bit, 1u);
-                    left -= 1u;
-                    if (bit)
-                        break;
-                    x >>= 1;
-                    nsig += 1u;
-                }
-                x >>= 1;
-                nsig += 1u;
-            }
-        }
+            n[s] = (iv[order_of(s)] + kNega) ^ kNega;
     }
-#pragma unroll
+    EncodeState st{live ? 9u : 32u * NW, 0u};
+    if (live)
+        sink.put(0u, 1u | (uint32_t)(emax + 127) << 1);
+    uint32_t G[8];
+    coeff_planes(n, true, G);
+    if (encode_planes<NW, 31, 16>(G, tab, st, sink) && __any(st.pos < 32u * NW)) {
+        coeff_planes(n, false, G);
+        (void)encode_planes<NW, 15, 0>(G, tab, st, sink);
+    }
+    return finite;
+}
+
+// The same into an array of NW words.
+template <int NW>
+__device__ __forceinline__ bool encode_block(const float (&f)[16], uint32_t (&out)[NW])
+{
+    static constexpr EncodeTable tab{};
+    struct Words {
+        uint32_t w[NW + 2] = {};
+        __device__ void put(uint32_t pos, uint32_t bits)
+        {
+            const uint64_t v = (uint64_t)bits << (pos & 31u);
+            w[pos >> 5] |= (uint32_t)v;
+            w[(pos >> 5) + 1] |= (uint32_t)(v >> 32);
+        }
+    } sink;
+    const bool finite = encode_block<NW>(f, tab.e, sink);
     for (int k = 0; k < NW; ++k)
         out[k] = sink.w[k];
     return finite;

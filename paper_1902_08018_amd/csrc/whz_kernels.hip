@@ -190,19 +190,55 @@ __global__ void __launch_bounds__(kDecThreads<NW>) decode_matrix_kernel(const ui
 }
 
 // ---------------------------------------------------------------- encoder
+__device__ const EncodeTable g_encode_table{};
+// 16 bytes stored at any word's address: the stream a caller passes need not
+// start on 16 bytes
+typedef uint32_t u32x4_word_aligned __attribute__((ext_vector_type(4), aligned(4)));
+
+// A block's words as they are written: the lane's column of LDS.
+template <int STRIDE>
+struct RowSink {
+    uint32_t* row;
+    __device__ __forceinline__ void put(uint32_t pos, uint32_t bits)
+    {
+        const uint64_t v = (uint64_t)bits << (pos & 31u);
+        uint32_t* p = row + (pos >> 5) * STRIDE;
+        __hip_atomic_fetch_or(p, (uint32_t)v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+        __hip_atomic_fetch_or(p + STRIDE, (uint32_t)(v >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+    }
+};
+
+// One lane per block, lanes along the block row (each of a block's four rows
+// is then one contiguous read of a wave).  A lane's code gathers in its column
+// of LDS, where a word is reached by position; held in registers it took a
+// dynamic register index, which is scratch memory.  Bound by HBM and vector
+// instructions about alike: 16384^2 at rate 8 takes 0.32 ms, 4.2 TB/s read
+// and written (2.46 ms before, bit by bit).  step_bi, step_bj: the
+// grid's stride in block rows and columns, so that no block's place needs a
+// division.
 template <int NW>
 __global__ void __launch_bounds__(kThreads) encode_kernel(const float* __restrict__ M, uint32_t nbc, uint32_t rows,
-                                                          uint32_t cols, uint64_t nblocks, uint32_t* __restrict__ stream,
+                                                          uint32_t cols, uint64_t nblocks, uint32_t step_bi,
+                                                          uint32_t step_bj, uint32_t* __restrict__ stream,
                                                           uint32_t* __restrict__ bad)
 {
+    __shared__ uint32_t lds[kThreads * (NW + 2)];
+    __shared__ uint32_t tab[256];
+    static_assert(kThreads == 256, "one table entry a lane");
+    tab[threadIdx.x] = g_encode_table.e[threadIdx.x];
+    __syncthreads();
+    uint32_t* row = lds + threadIdx.x;
     const uint64_t stride = (uint64_t)gridDim.x * kThreads;
-    for (uint64_t b = (uint64_t)blockIdx.x * kThreads + threadIdx.x; b < nblocks; b += stride) {
-        const uint64_t bi = b / nbc, bj = b % nbc;
+    const uint32_t first = blockIdx.x * (uint32_t)kThreads + threadIdx.x;
+    uint64_t bi = first / nbc;
+    uint32_t bj = first % nbc;
+    for (uint64_t b = first; b < nblocks; b += stride) {
         float f[16];
         if ((cols & 3u) == 0 && 4 * bi + 3 < rows) { // a whole block on 16-byte aligned rows
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const float4 v = *reinterpret_cast<const float4*>(M + (4 * bi + r) * cols + 4 * bj);
+                const f32x4 v = __builtin_nontemporal_load(
+                    reinterpret_cast<const f32x4*>(M + (4 * bi + r) * cols + 4 * (uint64_t)bj));
                 f[4 * r] = v.x;
                 f[4 * r + 1] = v.y;
                 f[4 * r + 2] = v.z;
@@ -214,18 +250,34 @@ __global__ void __launch_bounds__(kThreads) encode_kernel(const float* __restric
                 const uint64_t i = 4 * bi + r < rows ? 4 * bi + r : rows - 1;
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
-                    const uint64_t j = 4 * bj + c < cols ? 4 * bj + c : cols - 1;
+                    const uint64_t j = 4 * (uint64_t)bj + c < cols ? 4 * (uint64_t)bj + c : cols - 1;
                     f[4 * r + c] = M[i * cols + j];
                 }
             }
         }
-        uint32_t out[NW];
-        const bool finite = encode_block<NW>(f, out);
-        if (!finite && bad)
-            atomicAdd(bad, 1u);
 #pragma unroll
         for (int k = 0; k < NW; ++k)
-            stream[b * NW + k] = out[k];
+            row[k * kThreads] = 0u;
+        RowSink<kThreads> sink{row};
+        const bool finite = encode_block<NW>(f, tab, sink);
+        if (!finite && bad)
+            atomicAdd(bad, 1u);
+        if constexpr (NW % 4 == 0) {
+#pragma unroll
+            for (int k = 0; k < NW; k += 4)
+                *reinterpret_cast<u32x4_word_aligned*>(stream + b * NW + k) = u32x4_word_aligned{
+                    row[k * kThreads], row[(k + 1) * kThreads], row[(k + 2) * kThreads], row[(k + 3) * kThreads]};
+        } else {
+#pragma unroll
+            for (int k = 0; k < NW; ++k)
+                stream[b * NW + k] = row[k * kThreads];
+        }
+        bi += step_bi;
+        bj += step_bj;
+        if (bj >= nbc) {
+            bj -= nbc;
+            ++bi;
+        }
     }
 }
 
@@ -1198,10 +1250,12 @@ hipError_t launch_decode_matrix(const uint32_t* s, uint32_t rows, uint32_t cols,
 template <int NW>
 hipError_t launch_encode(const float* M, uint32_t rows, uint32_t cols, uint32_t* s, uint32_t* bad, hipStream_t st)
 {
-    const uint32_t nbc = (cols + 3) / 4;
-    const uint64_t nb = (uint64_t)((rows + 3) / 4) * nbc;
-    hipLaunchKernelGGL(encode_kernel<NW>, dim3(grid_for(nb, 65536)), dim3(kThreads), 0, st, M, nbc, rows, cols, nb, s,
-                       bad);
+    const uint32_t nbc = (uint32_t)(((uint64_t)cols + 3) / 4);
+    const uint64_t nb = ((uint64_t)rows + 3) / 4 * nbc;
+    const unsigned grid = grid_for(nb, 65536);
+    const uint32_t stride = grid * (uint32_t)kThreads;
+    hipLaunchKernelGGL(encode_kernel<NW>, dim3(grid), dim3(kThreads), 0, st, M, nbc, rows, cols, nb, stride / nbc,
+                       stride % nbc, s, bad);
     return hipGetLastError();
 }
 

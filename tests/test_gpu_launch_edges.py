@@ -4,6 +4,8 @@
                  that depends on the rate, and makes it per block above:
                  slabs on both sides of it, within 1e-6 relative L2 of the
                  FP64 oracle (the stated tolerance of every mode)
+  encode         a stream that starts on 4 bytes but not on 16; more blocks
+                 than one sweep of the grid
 """
 import numpy as np
 import pytest
@@ -37,3 +39,32 @@ def test_slab_vector_limits(monkeypatch, rate, flags):
             assert err <= 1e-6, (slabs, err)
         finally:
             wh.wh_destroy(ctx)
+
+
+@pytest.mark.parametrize("rate", [8, 16, 6])
+def test_encode_into_word_aligned_stream(gpu_ctx, rate):
+    rows, cols = 37, 150
+    M = synth.matrix(synth.MatrixSpec(rows, cols, 16, 4.0, seed=62))
+    want = oracle.encode(M, rate)
+    buf = torch.zeros(want.size + 8, dtype=torch.uint8, device="cuda")
+    wh.wh_encode(gpu_ctx, torch.from_numpy(M).cuda(), rate, buf[4:4 + want.size])
+    torch.cuda.synchronize()
+    got = buf.cpu().numpy()
+    assert np.array_equal(got[4:4 + want.size], want)
+    assert not got[:4].any() and not got[4 + want.size:].any()
+
+
+def test_encode_more_blocks_than_one_sweep(gpu_ctx):
+    # 65536 workgroups of 256 lanes are one sweep: 16,777,216 blocks.  The
+    # parts are encoded by launches below that, so a block's code must not
+    # depend on the sweep it is in
+    rows, cols, rate, cut = 4 * 1025, 4 * 16385, 2, 4 * 512
+    M = torch.rand(rows, cols, device="cuda", generator=torch.Generator("cuda").manual_seed(5))
+    whole = torch.empty(wh.stream_bytes(rows, cols, rate), dtype=torch.uint8, device="cuda")
+    wh.wh_encode(gpu_ctx, M, rate, whole)
+    at = wh.stream_bytes(cut, cols, rate)
+    parts = torch.empty_like(whole)
+    wh.wh_encode(gpu_ctx, M[:cut], rate, parts[:at])
+    wh.wh_encode(gpu_ctx, M[cut:], rate, parts[at:])
+    torch.cuda.synchronize()
+    assert torch.equal(whole, parts)
