@@ -116,16 +116,37 @@ uint32_t set_slabs(GemvPlan& pl, uint32_t nslab, uint32_t width)
 //    groups only where a tile of 512 / G block rows would be mostly empty
 //    (few rows); narrower where a row has fewer than 8 block columns.
 //  * One block row per group and tile.
-//  * Column slabs of `iters` blocks per lane and row: about 2048 workgroups
-//    (some three rounds of the 768 resident at once) with 3 to 16 blocks per
-//    lane; past 2^27 blocks, about 8192 workgroups of up to 48 blocks per
-//    lane, which keeps the FP64 partial sums small (the times differ by under
-//    1 % there).
+//  * Column slabs of 1 to 16 blocks per lane and row, by gemv_shape_cost;
+//    past 2^27 blocks, about 8192 workgroups of up to 48 blocks per lane,
+//    which keeps the FP64 partial sums small (the times differ by under 1 %
+//    there).
+namespace {
+
+// What a launch of `wgs` workgroups with `iters` blocks a lane takes, in the
+// time of one block a lane at two workgroups a CU (`resident` = 2 x the CUs).
+// A workgroup costs its blocks and 0.8 of one for its start (section table,
+// slab of u, sums).  The last workgroups run in a device that empties, about
+// 0.3 of their blocks; and a launch is never shorter than its longest
+// workgroup, whose blocks take two thirds of the time with the CU to itself.
+// Measured against full sweeps (us): 4096^2 at rate 8 with 1024 / 512 / 344 /
+// 256 workgroups (1 to 4 blocks) 29.7 / 26.4 / 32.3 / 26.7, the 378 x 256000
+// slit with 3 / 4 / 6 / 8 / 12 blocks 87.4 / 83.0 / 84.2 / 86.3 / 90.0, 10000^2
+// with 3 / 4 / 5 / 6 / 8 blocks 108.3 / 106.7 / 101.7 / 107.2 / 110.8, and
+// 256 x 1024 at rate 16 with 1 / 3 blocks 17 / 26.
+double gemv_shape_cost(uint32_t wgs, uint32_t iters, uint32_t resident)
+{
+    const double start = 0.8;
+    const double work = (double)wgs / resident * (start + iters) + 0.3 * iters;
+    const double longest = start + iters * (2 * wgs <= resident ? 2.0 / 3.0 : 1.0);
+    return std::max(work, longest);
+}
+
+} // namespace
+
 GemvPlan whz_gemv_plan(uint32_t rate, uint32_t rows, uint32_t cols, uint32_t row_begin, uint32_t row_end,
                        int num_cus, const GemvTuning* tune)
 {
     (void)rows;
-    (void)num_cus;
     GemvPlan pl = range_plan(cols, row_begin, row_end);
     const uint32_t lanes = gemv_wg_lanes(rate), max_lg = gemv_max_lg(lanes);
     pl.lanes = lanes;
@@ -153,10 +174,20 @@ GemvPlan whz_gemv_plan(uint32_t rate, uint32_t rows, uint32_t cols, uint32_t row
     pl.ntiles = ceil_div(nbr, (uint64_t)(lanes >> lg) * rpg);
     const uint32_t G = 1u << lg;
     const uint64_t blocks = (uint64_t)nbr * pl.nbc;
-    const uint64_t per_wg = (uint64_t)lanes;
-    uint64_t iters = std::min<uint64_t>(16, std::max<uint64_t>(3, (blocks + per_wg * 1024) / (per_wg * 2048)));
-    if (blocks > (1ull << 27))
-        iters = std::min<uint64_t>(48, blocks / (per_wg * 8192));
+    uint64_t iters = 1;
+    if (blocks > (1ull << 27)) {
+        iters = std::min<uint64_t>(48, blocks / ((uint64_t)lanes * 8192));
+    } else {
+        const uint32_t resident = 2u * (num_cus > 0 ? (uint32_t)num_cus : 256u);
+        double best = 0.0;
+        for (uint32_t it = 1; it <= 16; ++it) {
+            const double cost = gemv_shape_cost(pl.ntiles * ceil_div(pl.nbc, (uint64_t)G * it), it * rpg, resident);
+            if (it == 1 || cost < best) {
+                best = cost;
+                iters = it;
+            }
+        }
+    }
     uint32_t nslab = ceil_div(pl.nbc, (uint64_t)G * iters);
     if (tune && tune->slabs)
         nslab = tune->slabs;
