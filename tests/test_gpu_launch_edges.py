@@ -4,6 +4,8 @@
                  that depends on the rate, and makes it per block above:
                  slabs on both sides of it, within 1e-6 relative L2 of the
                  FP64 oracle (the stated tolerance of every mode)
+  thermal rows   rows of 0 to 11 entries (the kernel takes five at a time),
+                 columns out of range and infinities where nothing reads
   encode         a stream that starts on 4 bytes but not on 16; more blocks
                  than one sweep of the grid
 """
@@ -68,3 +70,34 @@ def test_encode_more_blocks_than_one_sweep(gpu_ctx):
     wh.wh_encode(gpu_ctx, M[cut:], rate, parts[at:])
     torch.cuda.synchronize()
     assert torch.equal(whole, parts)
+
+
+@pytest.mark.parametrize("n", [1, 511, 512, 513, 1500])
+def test_thermal_row_lengths(gpu_ctx, n):
+    rng = np.random.default_rng(n)
+    counts = np.arange(n) % 12
+    row_ptr = np.concatenate([[0], np.cumsum(counts)]).astype(np.uint32)
+    nnz = int(row_ptr[-1])
+    col = rng.integers(0, n, nnz).astype(np.uint32)
+    val = rng.uniform(-1, 1, nnz).astype(np.float32)
+    bad = rng.random(nnz) < 0.05
+    col[bad] = n + rng.integers(0, 5, int(bad.sum()))  # skipped
+    if nnz:
+        col[(col == 0)] = min(1, n - 1)
+    b = rng.uniform(0, 1, n).astype(np.float32)
+    T = rng.uniform(19, 21, n).astype(np.float32)
+    u = rng.uniform(0, 1, n).astype(np.float32)
+    if n > 1:
+        T[0] = np.inf  # no entry reads cell 0
+    want = np.empty(n, np.float32)
+    for i in range(n):
+        s = 0.0  # every product is exact in FP64, the sum rounds as the kernel's
+        for p in range(int(row_ptr[i]), int(row_ptr[i + 1])):
+            if col[p] < n:
+                s += float(val[p]) * float(T[col[p]])
+        want[i] = np.float32(s + float(b[i]) * float(u[i]))
+    sysm = wh.ThermalSystem(row_ptr, col, val, b)
+    out = torch.empty(n, device="cuda")
+    wh.wh_thermal_step(gpu_ctx, sysm, torch.from_numpy(T).cuda(), torch.from_numpy(u).cuda(), out)
+    torch.cuda.synchronize()
+    assert np.array_equal(out.cpu().numpy(), want)
