@@ -169,6 +169,8 @@ extern "C" wh_status wh_gemv_host(wh_ctx* ctx, const void* h_code, uint32_t rows
                 const wh_status s = ensure_partials(ctx, (size_t)pl.nslab * pl.part_rows(), st);
                 if (s != WH_OK)
                     return s;
+            } else if (pl.uncapturable && capturing(st)) {
+                return WH_ERR_INVALID;
             }
             const hipError_t e = whz_gemv(rate, pl, mode, dev, d_u, d_y, pl.nslab > 1 ? ctx->part : nullptr, st);
             return device_error(ctx, pl.nslab > 1 ? partials_release(ctx, st, e) : e);
@@ -183,6 +185,7 @@ extern "C" wh_status wh_gemv_host(wh_ctx* ctx, const void* h_code, uint32_t rows
         // workspace, in stream order
         // (the first and last chunks plan on their own, the others alike)
         size_t part_need = 0;
+        bool uncapturable = false;
         const uint64_t nchunks = (be - bb + cb - 1) / cb;
         for (uint64_t n : {(uint64_t)0, (uint64_t)1, nchunks - 1}) {
             if (n >= nchunks)
@@ -193,7 +196,10 @@ extern "C" wh_status wh_gemv_host(wh_ctx* ctx, const void* h_code, uint32_t rows
             const GemvPlan pl = whz_gemv_plan(rate, c.rows, cols, c.lo, c.hi, ctx->num_cus, &ctx->gemv_tune);
             if (pl.nslab > 1)
                 part_need = std::max(part_need, (size_t)pl.nslab * pl.part_rows());
+            uncapturable = uncapturable || pl.uncapturable;
         }
+        if (!part_need && uncapturable && capturing(st))
+            return WH_ERR_INVALID;
         if (part_need) {
             s = ensure_partials(ctx, part_need, st);
             if (s != WH_OK)

@@ -105,6 +105,8 @@ wh_status storage_bytes(const wh_matrix_desc& d, uint64_t& nbytes)
 
 wh_status grow_partials(wh_ctx* ctx, size_t count);
 
+constexpr size_t kPartialsAtStart = (size_t)1 << 19; // doubles: 4 MiB
+
 bool capturing(hipStream_t st)
 {
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
@@ -239,6 +241,15 @@ wh_status wh_create(int hip_device, uint64_t hbm_budget_bytes, wh_ctx** out)
         if (hipEventCreateWithFlags(&ctx->part_ev, hipEventDisableTiming) != hipSuccess) {
             delete ctx;
             return WH_ERR_DEVICE;
+        }
+        // the slab partials of calls up to about 10^8 matrix values, so that a
+        // context's first such call does not wait for an allocation (80 us);
+        // without it the first call allocates
+        if (hipMalloc(reinterpret_cast<void**>(&ctx->part), kPartialsAtStart * sizeof(double)) == hipSuccess) {
+            ctx->part_cap = kPartialsAtStart;
+        } else {
+            (void)hipGetLastError();
+            ctx->part = nullptr;
         }
         // the host pipeline's copy stream is created on its first use: a
         // stream holds a hardware queue (HIP maps streams onto a few queues
@@ -436,6 +447,8 @@ wh_status wh_gemv(wh_ctx* ctx, wh_mat m, const float* d_u, float* d_y, uint32_t 
                 if (s2 != WH_OK)
                     return s2;
                 part = ctx->part;
+            } else if (pl.uncapturable && capturing(st)) {
+                return WH_ERR_INVALID;
             }
             hipError_t e = whz_gemv(mat.desc.rate, pl, mode, mat.dptr, d_u, d_y, part, st);
             return device_error(ctx, part ? partials_release(ctx, st, e) : e);

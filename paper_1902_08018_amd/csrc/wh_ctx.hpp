@@ -48,6 +48,7 @@ wh_status device_error(wh_ctx* ctx, hipError_t e);
 // WH_ERR_INVALID while `st` is being captured into a graph: a later call may
 // regrow (free) the workspace that the graph would keep using.
 wh_status ensure_partials(wh_ctx* ctx, size_t count, hipStream_t st);
+bool capturing(hipStream_t st);
 hipError_t partials_release(wh_ctx* ctx, hipStream_t st, hipError_t e);
 Matrix* find_matrix(wh_ctx* ctx, wh_mat m);
 bool aligned(const void* p, uintptr_t a);

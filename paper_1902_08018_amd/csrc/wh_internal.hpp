@@ -51,6 +51,9 @@ struct GemvPlan {
     uint32_t skip;     // row_begin % 4: rows of the first block row before the range
     uint32_t lanes;    // workgroup lanes (gemv_wg_lanes of the rate)
     uint32_t math;     // multi-RHS plans: the contraction (MrhsMath)
+    // the call belongs to those that use the context's workspace, which are
+    // refused under graph capture (also where this plan has one slab)
+    bool uncapturable;
     // FP64 partials per slab and right-hand side: the range's block-rows
     uint32_t part_rows() const { return (bi_end - bi_begin) * 4; }
 };

@@ -116,11 +116,47 @@ uint32_t set_slabs(GemvPlan& pl, uint32_t nslab, uint32_t width)
 //    groups only where a tile of 512 / G block rows would be mostly empty
 //    (few rows); narrower where a row has fewer than 8 block columns.
 //  * One block row per group and tile.
-//  * Column slabs of 1 to 16 blocks per lane and row, by gemv_shape_cost;
-//    past 2^27 blocks, about 8192 workgroups of up to 48 blocks per lane,
-//    which keeps the FP64 partial sums small (the times differ by under 1 %
-//    there).
+//  * Column slabs of 1 to 16 blocks per lane and row, by gemv_shape_cost; or
+//    no slabs, with groups wide enough to take a whole block row at a block a
+//    lane, where that costs less (up to 1024 columns: no partial sums, no
+//    second kernel, no ordering of the workspace's users; 256 x 1024 at rate
+//    16 16.3 -> 10.9 us).  Past
+//    2^27 blocks, about 8192 workgroups of up to 48 blocks per lane, which
+//    keeps the FP64 partial sums small (the times differ by under 1 % there).
 namespace {
+
+// Column slabs by a fixed rule: about 2048 workgroups of 3 to 16 blocks per
+// lane, and past 2^27 blocks about 8192 of up to 48.
+uint32_t split_slabs(uint64_t blocks, uint32_t nbc, uint32_t lanes, uint32_t G)
+{
+    uint64_t iters = std::min<uint64_t>(16, std::max<uint64_t>(3, (blocks + (uint64_t)lanes * 1024) / ((uint64_t)lanes * 2048)));
+    if (blocks > (1ull << 27))
+        iters = std::min<uint64_t>(48, blocks / ((uint64_t)lanes * 8192));
+    return ceil_div(nbc, (uint64_t)G * iters);
+}
+
+// Whether that rule splits the columns of groups of 2^lg lanes.  Calls for
+// such a matrix use the context's workspace and are not captured into graphs,
+// whatever the plan's own slabs are; the others always get one slab.
+bool columns_split(uint32_t nbr, uint32_t nbc, uint32_t lanes, uint32_t lg)
+{
+    GemvPlan pl{};
+    pl.nbc = nbc;
+    return set_slabs(pl, split_slabs((uint64_t)nbr * nbc, nbc, lanes, 1u << lg), 1u << lg) > 1;
+}
+
+// The slab partials' price in the unit of gemv_shape_cost: the reduce kernel
+// (4 us) and ordering the workspace's users (3 us).
+constexpr double kSlabReduceCost = 1.2;
+
+// What a block costs in a wave that takes 2^lg block columns of each of its
+// rows, against 8: neighbouring blocks in two dimensions need more alike
+// numbers of planes and lookups (65536^2: 16 lanes 2 %, 64 and more 14 %).
+// Wider groups are taken for a clear gain only: 6 % on top of that.
+double row_group_cost(uint32_t lg)
+{
+    return lg <= 3 ? 1.0 : (lg == 4 ? 1.02 : (lg == 5 ? 1.06 : 1.14)) * 1.06;
+}
 
 // What a launch of `wgs` workgroups with `iters` blocks a lane takes, in the
 // time of one block a lane at two workgroups a CU (`resident` = 2 x the CUs).
@@ -161,11 +197,39 @@ GemvPlan whz_gemv_plan(uint32_t rate, uint32_t rows, uint32_t cols, uint32_t row
             break;
         ++lg;
     }
-    uint32_t rpg = 1;
+    pl.uncapturable = columns_split(nbr, pl.nbc, lanes, lg);
+    const uint64_t blocks = (uint64_t)nbr * pl.nbc;
+    const uint32_t resident = 2u * (num_cus > 0 ? (uint32_t)num_cus : 256u);
+    uint32_t rpg = 1, per_lane = 0; // blocks a lane and row; 0: not chosen yet
     if (tune && tune->lanes) {
         lg = 2;
         while ((1u << lg) < tune->lanes && lg < max_lg)
             ++lg;
+    } else if (!(tune && (tune->rows || tune->slabs)) && blocks <= (1ull << 27)) {
+        double best = 1e300;
+        if (pl.uncapturable) {
+            for (uint32_t it = 1; it <= 16; ++it) {
+                const uint32_t nslab = ceil_div(pl.nbc, ((uint64_t)it) << lg);
+                const double cost = gemv_shape_cost(ceil_div(nbr, lanes >> lg) * nslab, it, resident) +
+                                    (nslab > 1 ? kSlabReduceCost : 0.0);
+                if (cost < best) {
+                    best = cost;
+                    per_lane = it;
+                }
+            }
+        }
+        const uint32_t patch_lg = lg;
+        for (uint32_t g = patch_lg; g <= max_lg; ++g) { // one slab: the group takes whole block rows
+            const uint32_t it = ceil_div(pl.nbc, 1u << g);
+            if (pl.uncapturable && (g > patch_lg ? it > 1 || g > 8 : it > 16))
+                continue; // wide groups: a block a lane, four waves
+            const double cost = gemv_shape_cost(ceil_div(nbr, lanes >> g), it, resident) * row_group_cost(g);
+            if (cost < best) {
+                best = cost;
+                per_lane = it;
+                lg = g;
+            }
+        }
     }
     if (tune && tune->rows && gemv_slots(lg, lanes) * 4 * tune->rows <= lanes && !gemv_one_tile_row(rate))
         rpg = tune->rows;
@@ -173,22 +237,8 @@ GemvPlan whz_gemv_plan(uint32_t rate, uint32_t rows, uint32_t cols, uint32_t row
     pl.rpg = rpg;
     pl.ntiles = ceil_div(nbr, (uint64_t)(lanes >> lg) * rpg);
     const uint32_t G = 1u << lg;
-    const uint64_t blocks = (uint64_t)nbr * pl.nbc;
-    uint64_t iters = 1;
-    if (blocks > (1ull << 27)) {
-        iters = std::min<uint64_t>(48, blocks / ((uint64_t)lanes * 8192));
-    } else {
-        const uint32_t resident = 2u * (num_cus > 0 ? (uint32_t)num_cus : 256u);
-        double best = 0.0;
-        for (uint32_t it = 1; it <= 16; ++it) {
-            const double cost = gemv_shape_cost(pl.ntiles * ceil_div(pl.nbc, (uint64_t)G * it), it * rpg, resident);
-            if (it == 1 || cost < best) {
-                best = cost;
-                iters = it;
-            }
-        }
-    }
-    uint32_t nslab = ceil_div(pl.nbc, (uint64_t)G * iters);
+    uint32_t nslab = per_lane ? ceil_div(pl.nbc, (uint64_t)G * per_lane)
+                              : split_slabs(blocks, pl.nbc, lanes, G);
     if (tune && tune->slabs)
         nslab = tune->slabs;
     const uint32_t max_slabs = ceil_div(pl.nbc, G);
