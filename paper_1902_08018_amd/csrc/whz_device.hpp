@@ -11,9 +11,7 @@
 // block row then every block column; sequency order; negabinary.
 //
 // One lane decodes one block.  The bits of the lane's block sit in a
-// lane-private LDS row (words 0..NW-1 plus three zero words).  A lane carries
-// 32 bits from its position on and reads the 32 that follow from that row
-// beside the table lookup of each plane.
+// lane-private LDS row (words 0..NW-1 plus three zero words).
 //
 // Included by the .hip translation units after <hip/hip_runtime.h>.
 #pragma once
@@ -373,20 +371,25 @@ __device__ __forceinline__ uint32_t sec_lookup(const SectionReader& sec, uint32_
     return *(const uint32_t*)((const char*)sec.tab + (off + sec_row(S)));
 }
 
-// Bits 32..63 of the block staged at lw[word * STRIDE], counted from two bits
-// in front of state S's position: two words, from the one after the
-// position's on.
+// The word of a block staged at lw[word * STRIDE] that holds the bit two bits in
+// front of state S's position.
 template <int STRIDE>
-__device__ __forceinline__ uint32_t bits_ahead(const uint32_t* lw, const SectionReader& sec, uint32_t S)
+__device__ __forceinline__ const uint32_t* state_word(const uint32_t* lw, const SectionReader& sec, uint32_t S)
 {
-    const uint32_t* p;
     if constexpr (STRIDE == 1024 || STRIDE == 512 || STRIDE == 256) {
         // the word's byte offset, from its place in S
         const uint32_t off = (S & sec.word_mask) / (1024 / STRIDE);
-        p = (const uint32_t*)((const char*)lw + off);
+        return (const uint32_t*)((const char*)lw + off);
     } else {
-        p = lw + ((S & sec.word_mask) >> 12) * STRIDE;
+        return lw + ((S & sec.word_mask) >> 12) * STRIDE;
     }
+}
+
+// Bits 32..63 from there.
+template <int STRIDE>
+__device__ __forceinline__ uint32_t bits_ahead(const uint32_t* lw, const SectionReader& sec, uint32_t S)
+{
+    const uint32_t* p = state_word<STRIDE>(lw, sec, S);
     return funnel(p[2 * STRIDE], p[STRIDE], S >> kPosShift);
 }
 
@@ -434,33 +437,33 @@ struct PlaneCursor {
 };
 
 // One bit plane of the embedded code (decoded in lockstep by all lanes of the
-// wave).  `ahead` are the 32 bits that follow c.w.  Returns the plane word in
-// two parts: the significant coefficients' verbatim bits in xv (low half), and
-// the new ones (high half).
-// A plane spans at most 31 bits, so the next one's window lies within these
-// 64: the only read a plane waits for is the section table's, and the stream
-// words are read beside it (a variable-rate GEMV of 8192^2, two waves a SIMD
-// and so bound by this chain, went from 186 to 169 us; before, a plane waited
-// for its window and then for its entry).
-template <bool WIDE>
-__device__ __forceinline__ uint32_t plane_bits(const SectionReader& sec, PlaneCursor& c, uint32_t ahead, uint32_t& xv)
+// wave) at cursor c.  Returns the plane word in two parts: the significant
+// coefficients' verbatim bits in xv (low half), and the new ones (high half).
+// ahead() gives the 32 bits that follow c.w.  A plane spans at most 31 bits, so
+// the windows of its later lookups and, if NEXT_W, the next plane's lie within
+// these 64.
+template <bool WIDE, bool NEXT_W, typename F>
+__device__ __forceinline__ uint32_t plane_bits(const SectionReader& sec, PlaneCursor& c, F ahead, uint32_t& xv)
 {
     // the window holds the verbatim bits (nsig <= 16) and the first 9 section
     // bits (v_bfe takes the width modulo 32: nsig)
     uint32_t e = sec_lookup<true>(sec, c.S, c.w);
     xv = __builtin_amdgcn_ubfe(c.w, 2u, c.S);
     uint32_t ones = e, moved = e; // bits 7..11 of moved: the bits passed
+    const uint32_t at = c.S;
     c.S = advance<WIDE>(c.S, e);
     if (ent_open(e)) {
+        const uint32_t more = ahead(at);
         do { // the lanes whose section goes on
             c.S -= kEntOpen;
-            e = sec_lookup<false>(sec, c.S, funnel(ahead, c.w, moved >> kPosShift));
+            e = sec_lookup<false>(sec, c.S, funnel(more, c.w, moved >> kPosShift));
             c.S = advance<WIDE>(c.S, e);
             moved += e;
             ones |= e;
         } while (ent_open(e));
     }
-    c.w = funnel(ahead, c.w, moved >> kPosShift);
+    if constexpr (NEXT_W)
+        c.w = funnel(ahead(at), c.w, moved >> kPosShift);
     return ones;
 }
 
@@ -489,8 +492,8 @@ struct BlockReader {
     bool cut;      // see decode_block_coeffs
 };
 
-// Plane P of a fixed-rate block into its half G; `ahead`: the 32 bits that
-// follow c.w.  A lane whose budget is spent keeps stepping over zero bits: a
+// Plane P of a fixed-rate block into its half G (NEXT_W, ahead: as
+// plane_bits).  A lane whose budget is spent keeps stepping over zero bits: a
 // zero group bit ends each section at once, so its plane words stay zero.
 // Bits past the end of the block read as zero.  That gives the exact result
 // everywhere except when the bit budget runs out inside a run: there the zero
@@ -499,14 +502,13 @@ struct BlockReader {
 // the end says which one that was.  Only planes in which some lane of the wave
 // is past its budget pay for that correction, and the first kSafePlanes do not
 // look for one.
-template <int NW, int STRIDE, int P>
-__device__ __forceinline__ void decode_plane(BlockReader<NW, STRIDE>& rd, PlaneCursor& c, uint32_t ahead,
-                                             uint32_t (&G)[8])
+template <int NW, int STRIDE, int P, bool NEXT_W, typename F>
+__device__ __forceinline__ void decode_plane(BlockReader<NW, STRIDE>& rd, PlaneCursor& c, F ahead, uint32_t (&G)[8])
 {
     constexpr uint32_t kMaxBits = 32u * NW;
     constexpr bool kWide = kWideState<NW>;
     uint32_t xv;
-    uint32_t ones = plane_bits<kWide>(rd.sec, c, ahead, xv);
+    uint32_t ones = plane_bits<kWide, NEXT_W>(rd.sec, c, ahead, xv);
     if constexpr (31 - P >= kSafePlanes<NW>) {
         const uint32_t at = state_value<kWide>(c.S);
         if constexpr (P == kSafeCutPlane && kCanCut<NW>)
@@ -530,6 +532,11 @@ __device__ __forceinline__ void decode_plane(BlockReader<NW, STRIDE>& rd, PlaneC
 
 // Planes P..LAST of a half.  When every lane of the wave is past its budget
 // the planes left are zero.
+// An odd plane reads 64 bits from its position and leaves the even plane below
+// it its window, so that a pair waits for the stream once; the even plane reads
+// on only where its section takes more than one lookup.  (65536^2 at rate 8:
+// 2.85 ms; 3.00 with the 32 bits ahead read in every plane, which takes 6
+// cycles more a plane; 3.06 with every plane's window read in turn.)
 template <int NW, int STRIDE, int P, int LAST>
 __device__ __forceinline__ void decode_planes_from(BlockReader<NW, STRIDE>& rd, PlaneCursor& c, uint32_t (&G)[8])
 {
@@ -540,7 +547,16 @@ __device__ __forceinline__ void decode_planes_from(BlockReader<NW, STRIDE>& rd, 
                 return;
             }
         }
-        decode_plane<NW, STRIDE, P>(rd, c, bits_ahead<STRIDE>(rd.lw, rd.sec, c.S), G);
+        if constexpr (P & 1) {
+            const uint32_t* p = state_word<STRIDE>(rd.lw, rd.sec, c.S);
+            const uint32_t lo = p[0], hi = p[STRIDE], more = p[2 * STRIDE];
+            c.w = funnel(hi, lo, c.S >> kPosShift);
+            const uint32_t ahead = funnel(more, hi, c.S >> kPosShift);
+            decode_plane<NW, STRIDE, P, true>(rd, c, [ahead](uint32_t) { return ahead; }, G);
+        } else {
+            decode_plane<NW, STRIDE, P, false>(
+                rd, c, [&rd](uint32_t S) { return bits_ahead<STRIDE>(rd.lw, rd.sec, S); }, G);
+        }
         decode_planes_from<NW, STRIDE, P - 1, LAST>(rd, c, G);
     }
 }
@@ -567,15 +583,15 @@ __device__ __forceinline__ void decode_top_planes(BlockReader<NW, STRIDE>& rd, u
     c.w = nz ? funnel(w1, w0, 7u) : 0u;
     uint32_t ahead = nz ? funnel(w2, w1, 7u) : 0u;
     if (__any((c.w & 4u) != 0u)) {
-        decode_plane<NW, STRIDE, 31>(rd, c, ahead, H);
-        ahead = bits_ahead<STRIDE>(rd.lw, rd.sec, c.S);
+        decode_plane<NW, STRIDE, 31, true>(rd, c, [ahead](uint32_t) { return ahead; }, H);
+        decode_planes_from<NW, STRIDE, 30, 30>(rd, c, H);
     } else {
         H[7] = 0u;
         c.S += 1u << kPosShift;
         c.w = funnel(ahead, c.w, 1u);
         ahead >>= 1; // plane 30 has nothing verbatim: 31 bits are enough
+        decode_plane<NW, STRIDE, 30, false>(rd, c, [ahead](uint32_t) { return ahead; }, H);
     }
-    decode_plane<NW, STRIDE, 30>(rd, c, ahead, H);
 }
 
 // Decode the coefficients of the block staged at lw[q * STRIDE], q =
@@ -606,7 +622,6 @@ __device__ __forceinline__ bool decode_block_coeffs(const uint32_t* lw, const Se
         decode_planes_from<NW, STRIDE, 29, 16>(rd, c, H);
     } else {
         rd.past = __ballot(!nz);
-        c.w = nz ? funnel(w1, w[0], 7u) : 0u;
         decode_planes_from<NW, STRIDE, 31, 16>(rd, c, H);
     }
     const bool low = rd.past != __builtin_amdgcn_read_exec(); // some lane has planes below 16

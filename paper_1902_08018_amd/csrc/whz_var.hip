@@ -165,7 +165,11 @@ __device__ __forceinline__ void var_planes_from(const uint32_t* row, const Secti
     if constexpr (P >= LAST) {
         if ((uint32_t)P >= lo) {
             uint32_t xv;
-            const uint32_t ones = plane_bits<true>(sec, c, bits_ahead<T>(row, sec, c.S), xv);
+            // the 32 bits ahead of every plane's window, beside its lookup: with
+            // few waves a SIMD the chain is what counts (186 -> 169 us at
+            // 8192^2 against one window read a plane)
+            const uint32_t ahead = bits_ahead<T>(row, sec, c.S);
+            const uint32_t ones = plane_bits<true, true>(sec, c, [ahead](uint32_t) { return ahead; }, xv);
             store_plane<P>(G, ones, xv);
             var_planes_from<P - 1, LAST, T>(row, sec, lo, c, G);
         }
