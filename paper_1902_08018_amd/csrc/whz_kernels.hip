@@ -695,6 +695,14 @@ __device__ __forceinline__ uint16_t to_bf16_rne(float f)
     return (uint16_t)((b + 0x7FFFu + ((b >> 16) & 1u)) >> 16);
 }
 
+// Two values rounded to BF16 (to nearest even) in one word, the first in the
+// low half: gfx950's own conversion, one instruction.
+__device__ __forceinline__ uint32_t pack_bf16_rne(float lo, float hi)
+{
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, bf16x2{(__bf16)lo, (__bf16)hi});
+}
+
 __device__ __forceinline__ float bf16_to_float(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
 // x = x1 + x2 + x3 exactly, each part a BF16 value (8 significant bits, cut
@@ -711,7 +719,24 @@ __device__ __forceinline__ void split3_bf16(float x, uint32_t& x1, uint32_t& x2,
 // the first in the low half.
 __device__ __forceinline__ uint32_t pack_hi16(uint32_t lo_src, uint32_t hi_src)
 {
-    return (lo_src >> 16) | (hi_src & 0xFFFF0000u);
+    return __builtin_amdgcn_perm(hi_src, lo_src, 0x07060302u);
+}
+
+// A block's coefficients times its 2^(emax - 30), w0 its first word.  The
+// scale is a normal FP32 number, and a multiplication (2 cycles, ldexp 4) the
+// same as ldexp, unless the block lies below 2^-96.
+__device__ __forceinline__ void scale_coeffs(const uint32_t (&cf)[16], uint32_t w0, float (&sc)[16])
+{
+    const uint32_t E = (w0 >> 1) & 0xFFu; // emax + 127
+    const float scale = __uint_as_float((__builtin_elementwise_max(E, 31u) - 30u) << 23);
+#pragma unroll
+    for (int v = 0; v < 16; ++v)
+        sc[v] = (float)(int32_t)cf[v] * scale;
+    if (__any(E < 31u && (w0 & 1u) != 0u)) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+            sc[v] = __builtin_ldexpf((float)(int32_t)cf[v], (int)E - 157);
+    }
 }
 
 // Orders the LDS accesses of the lanes of one wave: writes before it are
@@ -964,17 +989,14 @@ __global__ void __launch_bounds__(64 * mrhs_waves(NT, (MrhsMath)MATH), mrhs_wave
                 mrhs_load_bq<NT>(btf, cb + 4 * q, lane, bq[q]);
         }
         // ---- decode one block per lane: scaled coefficients (registers)
-        const int emax = block_emax(cur[0]);
         uint32_t cf[16];
         bool cut;
         decode_block_coeffs<NW, T>(row, sec, cur, cf, cut, [] {});
         float sc[16];
-#pragma unroll
-        for (int v = 0; v < 16; ++v)
-            sc[v] = __builtin_ldexpf((float)(int32_t)cf[v], emax - 30);
+        scale_coeffs(cf, cur[0], sc);
         if constexpr (kCanCut<NW>)
             if (__any(cut) && cut) // rare: the exact lift (see exact_block_coeffs)
-                exact_block_coeffs(cf, emax, sc);
+                exact_block_coeffs(cf, block_emax(cur[0]), sc);
 #pragma unroll
         for (int n = 0; n < NA; ++n)
             acc[n] = mf32x4{0.f, 0.f, 0.f, 0.f};
@@ -1106,7 +1128,7 @@ __global__ void __launch_bounds__(64 * mrhs_waves(NT, (MrhsMath)MATH), mrhs_wave
             uint32_t pk[8];
 #pragma unroll
             for (int v = 0; v < 8; ++v)
-                pk[v] = (uint32_t)to_bf16_rne(sc[2 * v]) | (uint32_t)to_bf16_rne(sc[2 * v + 1]) << 16;
+                pk[v] = pack_bf16_rne(sc[2 * v], sc[2 * v + 1]);
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 if (W >= 16 && h == 1) {
