@@ -69,18 +69,27 @@ __device__ __forceinline__ uint32_t select_bits(uint32_t m, uint32_t a, uint32_t
 #endif
 }
 
-// v << D.  For D == 1 the sum v + v, which issues in half a shift's time.
-template <int D>
-__device__ __forceinline__ uint32_t shift_left(uint32_t v)
+// (a & m) | c
+__device__ __forceinline__ uint32_t and_or(uint32_t a, uint32_t m, uint32_t c)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
-    if constexpr (D == 1) {
-        uint32_t r;
-        asm("v_add_u32 %0, %1, %1" : "=v"(r) : "v"(v));
-        return r;
-    }
+    return __builtin_amdgcn_bitop3_b32(a, m, c, 0xEA);
+#else
+    return (a & m) | c;
 #endif
-    return v << D;
+}
+
+// v + v, which issues in half the time of v << 1 (what the compiler makes of
+// it).
+__device__ __forceinline__ uint32_t twice(uint32_t v)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    uint32_t r;
+    asm("v_add_u32 %0, %1, %1" : "=v"(r) : "v"(v));
+    return r;
+#else
+    return v + v;
+#endif
 }
 
 __device__ __forceinline__ uint32_t asr1(uint32_t v) { return (uint32_t)((int32_t)v >> 1); }
@@ -152,26 +161,39 @@ __device__ __forceinline__ void fwd_xform(uint32_t (&v)[16])
 // bits by 8 or 16, and 16 planes take half the work of 32: blocks whose code
 // ends above plane 16 transpose one half only.
 // One stage: registers i and i + D (i & D == 0) exchange their D-wide column
-// blocks; m selects the low D columns of every 2D-wide group.  Templates keep
-// every index a compile-time constant (no register indexing, no loop).
-template <int D, int I>
-__device__ __forceinline__ void transpose_pairs(uint32_t (&G)[8], uint32_t m)
+// blocks; m selects the low D columns of every 2D-wide group.  Two registers
+// at a time: one 64-bit shift, which takes no longer than one of 32 bits,
+// serves both (the bits that cross are not selected).  65536 x 65536 at rate 8:
+// 2.94 ms with single shifts, 2.88 ms.  Templates keep every index a
+// compile-time constant (no register indexing, no loop).
+template <int D, int I, int J>
+__device__ __forceinline__ void transpose_two_pairs(uint32_t (&G)[8], uint32_t m)
 {
-    if constexpr (I < 8) {
-        if constexpr ((I & D) == 0) {
-            const uint32_t a = G[I], b = G[I + D];
-            G[I] = select_bits(m, a, shift_left<D>(b));
-            G[I + D] = select_bits(m, a >> D, b);
-        }
-        transpose_pairs<D, I + 1>(G, m);
+    uint32_t up0, up1;
+    if constexpr (D == 1) {
+        up0 = twice(G[I + D]);
+        up1 = twice(G[J + D]);
+    } else {
+        const uint64_t v = ((uint64_t)G[J + D] << 32 | G[I + D]) << D;
+        up0 = (uint32_t)v;
+        up1 = (uint32_t)(v >> 32);
     }
+    const uint32_t a0 = G[I], b0 = G[I + D], a1 = G[J], b1 = G[J + D];
+    G[I] = select_bits(m, a0, up0);
+    G[I + D] = select_bits(m, a0 >> D, b0);
+    G[J] = select_bits(m, a1, up1);
+    G[J + D] = select_bits(m, a1 >> D, b1);
 }
 
 __device__ __forceinline__ void transpose_half(uint32_t (&G)[8])
 {
-    transpose_pairs<4, 0>(G, vgpr_const(0x0F0F0F0Fu));
-    transpose_pairs<2, 0>(G, vgpr_const(0x33333333u));
-    transpose_pairs<1, 0>(G, vgpr_const(0x55555555u));
+    const uint32_t m4 = vgpr_const(0x0F0F0F0Fu), m2 = vgpr_const(0x33333333u), m1 = vgpr_const(0x55555555u);
+    transpose_two_pairs<4, 0, 1>(G, m4);
+    transpose_two_pairs<4, 2, 3>(G, m4);
+    transpose_two_pairs<2, 0, 1>(G, m2);
+    transpose_two_pairs<2, 4, 5>(G, m2);
+    transpose_two_pairs<1, 0, 2>(G, m1);
+    transpose_two_pairs<1, 4, 6>(G, m1);
 }
 
 // Complements the odd planes of a half (p0 is even): together with the
@@ -365,10 +387,10 @@ __device__ __forceinline__ uint32_t sec_row(uint32_t S)
 template <bool FIRST>
 __device__ __forceinline__ uint32_t sec_lookup(const SectionReader& sec, uint32_t S, uint32_t w)
 {
-    uint32_t off = (w >> (S & 31u)) & sec.bits_mask;
+    uint32_t off = and_or(w >> (S & 31u), sec.bits_mask, sec_row(S));
     if constexpr (!FIRST)
         off |= 4u;
-    return *(const uint32_t*)((const char*)sec.tab + (off + sec_row(S)));
+    return *(const uint32_t*)((const char*)sec.tab + off);
 }
 
 // The word of a block staged at lw[word * STRIDE] that holds the bit two bits in
