@@ -80,8 +80,9 @@ struct wh_ctx {
     std::mutex mu; // guards mats / next_id
     std::unordered_map<wh_mat, wh::Matrix> mats;
     wh_mat next_id = 1;
-    double* part = nullptr; // FP64 slab partials
+    double* part = nullptr; // FP64 slab partials: part_start, or a larger block
     size_t part_cap = 0;
+    double* part_start = nullptr; // allocated by wh_create
     hipEvent_t part_ev = nullptr; // recorded after each user of `part`
     std::atomic<bool> failed{false};
     wh::Server* server = nullptr; // owned; freed by serve_shutdown
