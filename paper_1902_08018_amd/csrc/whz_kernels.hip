@@ -678,16 +678,20 @@ static_assert(4 * mrhs_waves(1, MrhsMath::F32) <= (int)kMrhsMaxTileBlockRows &&
               "block rows per multi-RHS workgroup");
 constexpr int kMathF32 = (int)MrhsMath::F32, kMathBf16 = (int)MrhsMath::Bf16, kMathX6 = (int)MrhsMath::X6,
               kMathF32N = (int)MrhsMath::F32N;
-constexpr int kATileStride = 16 + 4; // floats per LDS row of a wave's X6 part tile (40 BF16)
-constexpr int kATile32Stride = 16;    // floats per LDS row of a wave's FP32 quarter tile (swizzled)
 typedef float mf32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 mbf16x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-// an X6 part tile of a wave: 16 rows of 32 BF16 coefficients (8 block
-// columns) plus 8 of padding
-constexpr int kATile16Stride = 40;
-static_assert(16 * kATile16Stride * 2 <= 16 * kATileStride * 4, "an X6 part tile fits its LDS");
-constexpr int kATileBf16Stride = 32; // BF16 per LDS row of a wave's BF16 half tile (swizzled)
+// A wave's A tiles, in pieces of 4 rows of 16 words (FP32: 16 coefficients of
+// a quarter; BF16: 32 of a half).  A piece is as long as one word of the wave's
+// 64 staged blocks, and those words are dead once the blocks are decoded: the
+// first NW pieces take their place, and only the others get LDS of their own.
+// At rate 16, 16 right-hand sides, that is 80 KB a workgroup instead of 96, so
+// two workgroups a CU and not one (16384 x 16384, FP32 and BF16: 494 and 405
+// us with tiles beside the rows, 360 and 295 so; 64 FP32 right-hand sides, 66
+// KB for 88: 781 and 525).
+constexpr int kTilePiece = 64; // words
+// FP32: a half's two quarters; BF16: both halves; X6: a half's three parts
+constexpr int mrhs_tile_pieces(int math) { return math == kMathX6 ? 12 : 8; }
 
 __device__ __forceinline__ uint16_t to_bf16_rne(float f)
 {
@@ -852,7 +856,6 @@ __device__ __forceinline__ void mrhs_load_bn(const float* __restrict__ btf, uint
 }
 constexpr int kMrhsNarrowAhead = 1;
 static_assert(kMrhsNarrowMax <= 4, "the 4x4x1 path holds one group of 4 right-hand sides");
-static_assert(16 * kATile32Stride >= 4 * 4 * 16, "a quarter's 16 blocks fit the FP32 tile");
 
 // X6: the B operand words (three parts, 16 bytes each) of one half and one
 // group of 16 right-hand sides for this lane.
@@ -885,12 +888,9 @@ __global__ void __launch_bounds__(64 * mrhs_waves(NT, (MrhsMath)MATH), mrhs_wave
     // accumulator tiles per lane: one per group of 16 right-hand sides, or
     // one for the 4x4x1 path (its groups of 4 lie in different lanes)
     constexpr int NA = NARROW ? 1 : NT;
-    __shared__ uint32_t lds[T * kStagedWords<NW>];
+    constexpr int kPieces = mrhs_tile_pieces(MATH), kOwnPieces = kPieces > NW ? kPieces - NW : 0;
+    __shared__ __align__(16) uint32_t lds[T * (kStagedWords<NW> + kOwnPieces)];
     __shared__ __align__(16) uint32_t tab[kSecEntries];
-    // the wave's A tile: FP32 quarters (16 x 16, swizzled), BF16 halves
-    // (16 x 32, swizzled), or three BF16 halves (one per part) for X6
-    __shared__ __align__(16) float atile[W][X6 ? 3 * 16 * kATileStride
-                                              : (BF16U ? 16 * kATileBf16Stride / 2 : 16 * kATile32Stride)];
     uint32_t* row = lds + threadIdx.x;
     clear_pad<NW, T>(row);
     load_section_table<T>(tab, [] {}); // the last workgroup barrier
@@ -903,7 +903,11 @@ __global__ void __launch_bounds__(64 * mrhs_waves(NT, (MrhsMath)MATH), mrhs_wave
     const uint32_t bc1 = bc0 + slab_bc < nbc ? bc0 + slab_bc : nbc;
     const int t = lane >> 4, c = lane & 15; // this lane's block in the wave's 4 x 16 step tile
     const uint32_t bi = bw + t;
-    float* at = atile[wave];
+    // row r of the wave's piece p (the pieces past the block's words lie past
+    // the pad)
+    const auto piece_row = [&](int p, int r) {
+        return lds + (wave * kTilePiece + (p < NW ? p : p + kStagedWords<NW> - NW) * T + r * 16);
+    };
     const float* btf = static_cast<const float*>(btu);
     const uint16_t* btb = static_cast<const uint16_t*>(btu);
 
@@ -1002,67 +1006,80 @@ __global__ void __launch_bounds__(64 * mrhs_waves(NT, (MrhsMath)MATH), mrhs_wave
             acc[n] = mf32x4{0.f, 0.f, 0.f, 0.f};
         if constexpr (NARROW) {
             // ---- four quarters of 4 block columns (the MFMA blocks and
-            // shares of mrhs_load_bn): the quarter's lanes write their blocks
-            // to the wave's tile as [t][s][r][m], then lane (t, s, r) reads
-            // row r of its share's block column and runs its 4 MFMAs (A: lane
-            // r + 4 b holds A_b[r]; B: lane j + 4 b holds B_b[j]; D_b[r][j]:
-            // lane j + 4 b, register r)
+            // shares of mrhs_load_bn), two at a time: the half's lanes write
+            // their blocks to the wave's tile, a quarter's as [t][s][r][m],
+            // then lane (t, s, r) reads row r of its share's block column and
+            // runs its 4 MFMAs (A: lane r + 4 b holds A_b[r]; B: lane j + 4 b
+            // holds B_b[j]; D_b[r][j]: lane j + 4 b, register r)
             const int tn = lane >> 4, sn = (lane >> 2) & 3, rn = lane & 3;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
+            for (int h = 0; h < 2; ++h) {
                 wave_sync_lds();
-                if ((c >> 2) == q) {
+                if ((c >> 3) == h) {
 #pragma unroll
                     for (int r = 0; r < 4; ++r)
-                        *reinterpret_cast<f32x4*>(at + ((t * 4 + (c & 3)) * 4 + r) * 4) =
+                        *reinterpret_cast<f32x4*>(piece_row((c & 4) + t, c & 3) + 4 * r) =
                             f32x4{sc[4 * r], sc[4 * r + 1], sc[4 * r + 2], sc[4 * r + 3]};
                 }
                 wave_sync_lds();
-                const int slot = q % AH;
-                const f32x4 a4 = *reinterpret_cast<const f32x4*>(at + ((tn * 4 + sn) * 4 + rn) * 4);
 #pragma unroll
-                for (int m = 0; m < 4; ++m)
-                    acc[0] = __builtin_amdgcn_mfma_f32_4x4x1f32(a4[m], bq[slot][0][m], acc[0], 0, 0, 0);
-                if (q + AH < 4) // the quarter AH on into the slot just used
-                    mrhs_load_bn(btf, cb, q + AH, lane, bq[slot][0]);
+                for (int q = 2 * h; q < 2 * h + 2; ++q) {
+                    const int slot = q % AH;
+                    const f32x4 a4 = *reinterpret_cast<const f32x4*>(piece_row(4 * (q & 1) + tn, sn) + 4 * rn);
+#pragma unroll
+                    for (int m = 0; m < 4; ++m)
+                        acc[0] = __builtin_amdgcn_mfma_f32_4x4x1f32(a4[m], bq[slot][0][m], acc[0], 0, 0, 0);
+                    if (q + AH < 4) // the quarter AH on into the slot just used
+                        mrhs_load_bn(btf, cb, q + AH, lane, bq[slot][0]);
+                }
             }
         } else if constexpr (MATH == kMathF32) {
-            // ---- four quarters of 4 block columns: the quarter's lanes write
-            // their blocks to the wave's 16 x 16 tile (row 4t + r, a 4-float
-            // group per block column, the group index XORed with t so that
-            // the column reads below spread over the banks), then every lane
-            // reads its A operands
+            // ---- four quarters of 4 block columns, two at a time (16384 x
+            // 16384, rate 8: 314 us; in four turns of one 324): the half's lanes write their blocks to
+            // their quarter's 16 x 16 tile (row 4t + r, a 4-float group per
+            // block column, the group index XORed with t so that the column
+            // reads below spread over the banks), then every lane reads its A
+            // operands
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
+            for (int h = 0; h < 2; ++h) {
                 // the tile is the wave's own: lanes read what other lanes of
                 // the wave wrote, so each hand-over is a wave-scope
                 // release/acquire (no workgroup barrier is needed)
                 wave_sync_lds();
-                if ((c >> 2) == q) {
+                if ((c >> 3) == h) {
 #pragma unroll
                     for (int r = 0; r < 4; ++r)
-                        *reinterpret_cast<f32x4*>(at + (4 * t + r) * kATile32Stride + 4 * ((c & 3) ^ t)) =
+                        *reinterpret_cast<f32x4*>(piece_row((c & 4) + t, r) + 4 * ((c & 3) ^ t)) =
                             f32x4{sc[4 * r], sc[4 * r + 1], sc[4 * r + 2], sc[4 * r + 3]};
                 }
                 wave_sync_lds();
-                const int slot = q % AH, ar = lane & 15;
-                // MFMA m contracts coefficient column m of the quarter's four
-                // block columns (K = block column): lane l holds A[l % 16][l / 16],
-                // coefficient (r, m) = ((l % 16) % 4, m) of block column l / 16
-                const f32x4 a4 =
-                    *reinterpret_cast<const f32x4*>(at + ar * kATile32Stride + 4 * ((lane >> 4) ^ (ar >> 2)));
 #pragma unroll
-                for (int m = 0; m < 4; ++m)
+                for (int q = 2 * h; q < 2 * h + 2; ++q) {
+                    const int slot = q % AH, at = (lane >> 2) & 3;
+                    // MFMA m contracts coefficient column m of the quarter's
+                    // four block columns (K = block column): lane l holds
+                    // A[l % 16][l / 16], coefficient (r, m) = ((l % 16) % 4,
+                    // m) of block column l / 16
+                    const f32x4 a4 =
+                        *reinterpret_cast<const f32x4*>(piece_row(4 * (q & 1) + at, lane & 3) + 4 * ((lane >> 4) ^ at));
 #pragma unroll
-                    for (int n = 0; n < NT; ++n)
-                        acc[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(a4[m], bq[slot][n][m], acc[n], 0, 0, 0);
-                if (q + AH < 4) // the quarter after next into the slot just used
-                    mrhs_load_bq<NT>(btf, cb + 4 * (q + AH), lane, bq[slot]);
+                    for (int m = 0; m < 4; ++m)
+#pragma unroll
+                        for (int n = 0; n < NT; ++n)
+                            acc[n] =
+                                __builtin_amdgcn_mfma_f32_16x16x4f32(a4[m], bq[slot][n][m], acc[n], 0, 0, 0);
+                    if (q + AH < 4) // the quarter after next into the slot just used
+                        mrhs_load_bq<NT>(btf, cb + 4 * (q + AH), lane, bq[slot]);
+                }
             }
         } else if constexpr (X6) {
             // ---- the coefficients' three BF16 parts, packed in pairs; both
             // halves' A operands are read before any MFMA, so that the packed
-            // words die first (the tile is then written twice)
+            // words die first (the tile is then written twice).  Rows are
+            // XORed with t too: pieces lie whole multiples of 64 words apart,
+            // so the lanes of one row would meet in 16 banks (17 right-hand
+            // sides: 389 us so, 381 with it; the 16-wave kernels above and
+            // below lose more by the addresses' registers than they gain)
             uint32_t pk[3][8];
 #pragma unroll
             for (int v = 0; v < 8; ++v) {
@@ -1073,9 +1090,8 @@ __global__ void __launch_bounds__(64 * mrhs_waves(NT, (MrhsMath)MATH), mrhs_wave
                 pk[1][v] = pack_hi16(a2, b2);
                 pk[2][v] = pack_hi16(a3, b3);
             }
-            uint16_t* at16 = reinterpret_cast<uint16_t*>(at);
-            constexpr int kPart = 16 * kATile16Stride; // BF16 elements per part's tile
             u32x4 av[2][3];
+            const int at = (lane >> 2) & 3;
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 wave_sync_lds();
@@ -1084,14 +1100,13 @@ __global__ void __launch_bounds__(64 * mrhs_waves(NT, (MrhsMath)MATH), mrhs_wave
                     for (int q = 0; q < 3; ++q)
 #pragma unroll
                         for (int r = 0; r < 4; ++r)
-                            *reinterpret_cast<u32x2*>(at16 + q * kPart + (4 * t + r) * kATile16Stride + 4 * (c & 7)) =
+                            *reinterpret_cast<u32x2*>(piece_row(4 * q + t, r ^ t) + 4 * (((c & 7) >> 1) ^ t) + 2 * (c & 1)) =
                                 u32x2{pk[q][2 * r], pk[q][2 * r + 1]};
                 }
                 wave_sync_lds();
 #pragma unroll
                 for (int q = 0; q < 3; ++q)
-                    av[h][q] = *reinterpret_cast<const u32x4*>(at16 + q * kPart + (lane & 15) * kATile16Stride +
-                                                               8 * (lane >> 4));
+                    av[h][q] = *reinterpret_cast<const u32x4*>(piece_row(4 * q + at, (lane & 3) ^ at) + 4 * ((lane >> 4) ^ at));
             }
             // ---- per half and group of 16 right-hand sides, six MFMAs; the
             // B parts of the next (half, group) load meanwhile
@@ -1118,37 +1133,31 @@ __global__ void __launch_bounds__(64 * mrhs_waves(NT, (MrhsMath)MATH), mrhs_wave
                     acc[n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, b1, acc[n], 0, 0, 0);
                 }
         } else {
-            // ---- two halves of 8 block columns (K = 32): the lanes of a half
-            // write their blocks' coefficients, rounded to BF16, to the 16 x
-            // 32 tile (row 4t + r, columns 4 (c % 8) .. + 3, each 16-byte
-            // pair of block columns XORed with t so that the reads below
-            // spread over the banks); lane l then holds A[l % 16][8 (l / 16)
-            // .. + 7] (two block columns) and B[8 (l / 16) .. + 7][l % 16]
-            uint16_t* at16 = reinterpret_cast<uint16_t*>(at);
-            uint32_t pk[8];
+            // ---- two halves of 8 block columns (K = 32), written together:
+            // each lane writes its block's coefficients, rounded to BF16, to
+            // its half's 16 x 32 tile (row 4t + r, columns 4 (c % 8) .. + 3,
+            // each 16-byte pair of block columns XORed with t so that the
+            // reads below spread over the banks); lane l then holds A[l %
+            // 16][8 (l / 16) .. + 7] (two block columns) and B[8 (l / 16) ..
+            // + 7][l % 16]
+            if constexpr (W >= 16) {
+                const uint32_t g = (uint32_t)lane >> 4, j = (uint32_t)lane & 15u;
 #pragma unroll
-            for (int v = 0; v < 8; ++v)
-                pk[v] = pack_bf16_rne(sc[2 * v], sc[2 * v + 1]);
+                for (int n = 0; n < NT; ++n)
+                    bh[1][n] = *reinterpret_cast<const u32x4*>(
+                        btb + (((uint64_t)(cb / 2 + 4 + g) * NT + n) * 16 + j) * 8);
+            }
+            wave_sync_lds();
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                *reinterpret_cast<u32x2*>(piece_row(4 * (c >> 3) + t, r) + 4 * (((c & 7) >> 1) ^ t) + 2 * (c & 1)) =
+                    u32x2{pack_bf16_rne(sc[4 * r], sc[4 * r + 1]), pack_bf16_rne(sc[4 * r + 2], sc[4 * r + 3])};
+            wave_sync_lds();
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
-                if (W >= 16 && h == 1) {
-                    const uint32_t g = (uint32_t)lane >> 4, j = (uint32_t)lane & 15u;
-#pragma unroll
-                    for (int n = 0; n < NT; ++n)
-                        bh[1][n] = *reinterpret_cast<const u32x4*>(
-                            btb + (((uint64_t)(cb / 2 + 4 + g) * NT + n) * 16 + j) * 8);
-                }
-                wave_sync_lds();
-                if ((c >> 3) == h) {
-#pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        *reinterpret_cast<u32x2*>(at16 + (4 * t + r) * kATileBf16Stride +
-                                                  8 * (((c & 7) >> 1) ^ t) + 4 * (c & 1)) = u32x2{pk[2 * r], pk[2 * r + 1]};
-                }
-                wave_sync_lds();
-                const int ar = lane & 15;
-                const u32x4 av = *reinterpret_cast<const u32x4*>(at16 + ar * kATileBf16Stride +
-                                                                 8 * ((lane >> 4) ^ (ar >> 2)));
+                const int at = (lane >> 2) & 3;
+                const u32x4 av =
+                    *reinterpret_cast<const u32x4*>(piece_row(4 * h + at, lane & 3) + 4 * ((lane >> 4) ^ at));
                 const mbf16x8 a = __builtin_bit_cast(mbf16x8, av);
 #pragma unroll
                 for (int n = 0; n < NT; ++n)
@@ -1161,6 +1170,7 @@ __global__ void __launch_bounds__(64 * mrhs_waves(NT, (MrhsMath)MATH), mrhs_wave
 #pragma unroll
             for (int j = 0; j < 4; ++j)
                 sum[n][j] += (double)acc[n][j];
+        wave_sync_lds(); // the tiles are read before the next words are staged
     }
 
     // ---- 4x4x1 sums: lane (t, s, j) holds block row t's sums over its

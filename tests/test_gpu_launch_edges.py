@@ -4,6 +4,10 @@
                  that depends on the rate, and makes it per block above:
                  slabs on both sides of it, within 1e-6 relative L2 of the
                  FP64 oracle (the stated tolerance of every mode)
+  batched tiles  the multi-RHS kernels' tiles lie in the staged blocks' place
+                 as far as a block's words reach: every count of words, more
+                 than one step of block columns, the last one partial, on
+                 every math (1e-6 FP32, 2e-3 BF16: the stated tolerances)
   thermal rows   rows of 0 to 11 entries (the kernel takes five at a time),
                  columns out of range and infinities where nothing reads
   encode         a stream that starts on 4 bytes but not on 16; more blocks
@@ -41,6 +45,24 @@ def test_slab_vector_limits(monkeypatch, rate, flags):
             assert err <= 1e-6, (slabs, err)
         finally:
             wh.wh_destroy(ctx)
+
+
+@pytest.mark.parametrize("k,dtype", [(3, "f32"), (16, "f32"), (20, "f32"), (64, "f32"), (16, "bf16"), (40, "bf16")])
+@pytest.mark.parametrize("rate", [2, 4, 6, 8, 10, 12, 14, 16, 20, 24, 32])
+def test_batched_tile_places(gpu_ctx, rate, k, dtype):
+    rows, cols = 131, 4 * 37 + 2  # 33 block rows; 38 block columns, 3 steps
+    spec = synth.MatrixSpec(rows, cols, 40, 8.0, seed=64)
+    s = oracle.encode(synth.matrix(spec), rate)
+    Mhat = oracle.decode(s, rows, cols, rate).astype(np.float64)
+    U = torch.from_numpy(synth.u_batch(spec, k)).to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    ref = U.double().numpy() @ Mhat.T
+    mat = wh.wh_load_compressed(gpu_ctx, rows, cols, wh.WH_FMT_ZFP_FIXED_RATE, rate, s)
+    Y = torch.full((k, rows), float("nan"), device="cuda")
+    wh.wh_gemv_batched(gpu_ctx, mat, U.cuda(), Y)
+    torch.cuda.synchronize()
+    err = np.linalg.norm(Y.cpu().numpy() - ref, axis=1) / np.linalg.norm(ref, axis=1)
+    assert err.max() <= (2e-3 if dtype == "bf16" else 1e-6), err.max()
+    wh.wh_unload(gpu_ctx, mat)
 
 
 @pytest.mark.parametrize("rate", [8, 16, 6])
