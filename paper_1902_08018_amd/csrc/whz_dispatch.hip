@@ -4,6 +4,7 @@
 
 #include <algorithm>
 
+#include "../../include/wh.h"
 #include "wh_internal.hpp"
 
 #define WH_FOR_EACH_NW(X) X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(10) X(12) X(16)
@@ -135,14 +136,20 @@ uint32_t split_slabs(uint64_t blocks, uint32_t nbc, uint32_t lanes, uint32_t G)
     return ceil_div(nbc, (uint64_t)G * iters);
 }
 
-// Whether that rule splits the columns of groups of 2^lg lanes.  Calls for
-// such a matrix use the context's workspace and are not captured into graphs,
-// whatever the plan's own slabs are; the others always get one slab.
-bool columns_split(uint32_t nbr, uint32_t nbc, uint32_t lanes, uint32_t lg)
+// The slabs that rule gives groups of 2^lg lanes.  Where it splits the
+// columns, calls use the context's workspace and are not captured into graphs,
+// whatever the plan's own slabs are; where it does not, the plan has one slab.
+uint32_t rule_slabs(uint32_t nbr, uint32_t nbc, uint32_t lanes, uint32_t lg)
 {
     GemvPlan pl{};
     pl.nbc = nbc;
-    return set_slabs(pl, split_slabs((uint64_t)nbr * nbc, nbc, lanes, 1u << lg), 1u << lg) > 1;
+    return set_slabs(pl, split_slabs((uint64_t)nbr * nbc, nbc, lanes, 1u << lg), 1u << lg);
+}
+
+// Whether a plan's partial sums fit wh_gemv_noalloc's scratch array.
+bool fits_scratch(uint32_t nslab, uint32_t nbr)
+{
+    return nslab <= 1 || (uint64_t)nslab * nbr * 4 * sizeof(double) <= WH_NOALLOC_SCRATCH_BYTES;
 }
 
 // The slab partials' price in the unit of gemv_shape_cost: the reduce kernel
@@ -197,7 +204,8 @@ GemvPlan whz_gemv_plan(uint32_t rate, uint32_t rows, uint32_t cols, uint32_t row
             break;
         ++lg;
     }
-    pl.uncapturable = columns_split(nbr, pl.nbc, lanes, lg);
+    const uint32_t by_rule = rule_slabs(nbr, pl.nbc, lanes, lg);
+    pl.uncapturable = by_rule > 1;
     const uint64_t blocks = (uint64_t)nbr * pl.nbc;
     const uint32_t resident = 2u * (num_cus > 0 ? (uint32_t)num_cus : 256u);
     uint32_t rpg = 1, per_lane = 0; // blocks a lane and row; 0: not chosen yet
@@ -205,11 +213,15 @@ GemvPlan whz_gemv_plan(uint32_t rate, uint32_t rows, uint32_t cols, uint32_t row
         lg = 2;
         while ((1u << lg) < tune->lanes && lg < max_lg)
             ++lg;
-    } else if (!(tune && (tune->rows || tune->slabs)) && blocks <= (1ull << 27)) {
+    } else if (!(tune && (tune->rows || tune->slabs)) && blocks <= (1ull << 27) && fits_scratch(by_rule, nbr)) {
+        // (the choice below keeps to plans that fit where the rule's does, so
+        // wh_gemv_noalloc takes and refuses the calls that it would with it)
         double best = 1e300;
         if (pl.uncapturable) {
             for (uint32_t it = 1; it <= 16; ++it) {
                 const uint32_t nslab = ceil_div(pl.nbc, ((uint64_t)it) << lg);
+                if (!fits_scratch(nslab, nbr))
+                    continue;
                 const double cost = gemv_shape_cost(ceil_div(nbr, lanes >> lg) * nslab, it, resident) +
                                     (nslab > 1 ? kSlabReduceCost : 0.0);
                 if (cost < best) {
