@@ -491,7 +491,7 @@ wh_status wh_gemv_batched(wh_ctx* ctx, wh_mat m, const void* d_U, int u_dtype, u
             return wh_gemv(ctx, m, static_cast<const float*>(d_U), d_Y, 0, mat.desc.rows, flags, stream);
         if (flags & WH_PAPER_MP)
             return WH_ERR_INVALID; // Fig. 7 per-product sums exist for one vector only
-        const MrhsPlan pl = whz_mrhs_plan(mat.desc.rows, mat.desc.cols, 0, mat.desc.rows, ctx->num_cus, k,
+        const MrhsPlan pl = whz_mrhs_plan(mat.desc.rate, mat.desc.rows, mat.desc.cols, 0, mat.desc.rows, ctx->num_cus, k,
                                           u_dtype == WH_U_BF16, &ctx->gemv_tune);
         // slab partials and B^T U share the context's workspace
         wh_status s2 = ensure_partials(ctx, mrhs_workspace(pl, k).total, st);

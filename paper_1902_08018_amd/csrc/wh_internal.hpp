@@ -12,17 +12,18 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // Accumulation of the cross-block row sums.
 enum class AccMode { Fp64, TwoSum, PaperMp };
 
-// Workgroup size of the fused GEMV: 1024 lanes up to 16 bits/value, 768
-// above.  Two workgroups share a CU: 32 waves at 1024 lanes, in 64 VGPRs
-// each (the launch bounds ask for that), or 24 at 768 lanes, where a lane
-// stages 13 or more words of LDS and two 1024-lane workgroups would not fit.
+// Workgroup size of the fused GEMV: 1024 lanes up to 16 bits/value, 768 up to
+// 24.  Two workgroups share a CU: 32 waves at 1024 lanes, in 64 VGPRs each
+// (the launch bounds ask for that), or 24 at 768 lanes, where a lane stages 13
+// or more words of LDS and two 1024-lane workgroups would not fit.  Above 24
+// bits/value (19 words) not two of 768 do either: one of 1024.
 // The most lanes a group spans (512; 256 for 768, the largest power of two
 // dividing it); the most block rows one lane group takes per tile.  The LDS
 // doubles that hold the groups' row sums (slots x 4 x rows per group: one
 // slot per wave, or per group of fewer than 64 lanes) are as many as the
 // workgroup's lanes.
 constexpr uint32_t kGemvLanes = 512;
-constexpr uint32_t gemv_wg_lanes(uint32_t rate) { return rate <= 16 ? 1024u : 768u; }
+constexpr uint32_t gemv_wg_lanes(uint32_t rate) { return rate <= 16 || rate > 24 ? 1024u : 768u; }
 // LDS of one workgroup when two share a CU
 constexpr uint32_t kLdsPerWorkgroupOfTwo = 160u * 1024u / 2u;
 // from 14 bits/value the row sums share the staging rows: one tile row
@@ -89,9 +90,14 @@ inline MrhsMath mrhs_math(uint32_t k, bool bf16, bool force_fp32)
         return MrhsMath::F32;
     return k > 16 ? MrhsMath::X6 : (k <= kMrhsNarrowMax ? MrhsMath::F32N : MrhsMath::F32);
 }
-// Waves per workgroup for NT groups of 16 right-hand sides: 16 up to 16
-// right-hand sides, 8 above (two workgroups per CU in LDS and registers).
-constexpr int mrhs_waves(int nt, MrhsMath m) { return m == MrhsMath::X6 ? 8 : (nt == 1 ? 16 : 8); }
+// Waves of the largest workgroup of which two fit a CU's LDS when a lane
+// stages a block of nw words (and three more) beside the section table; a
+// multiple of the four SIMDs: 14 waves (nw = 10) put eight of two workgroups
+// on some of them, whose registers then hold one workgroup only.
+constexpr int waves_of_two_per_cu(int nw) { return nw <= 8 ? 16 : (nw <= 12 ? 12 : 8); }
+// Waves per workgroup for NT groups of 16 right-hand sides: as many as that up
+// to 16 right-hand sides, 8 above (two workgroups per CU in LDS and registers).
+constexpr int mrhs_waves(int nt, int nw) { return nt == 1 ? waves_of_two_per_cu(nw) : 8; }
 constexpr uint32_t kMrhsMaxTileBlockRows = 64;
 constexpr uint32_t kMaxRhs = 64;
 
@@ -118,7 +124,7 @@ inline MrhsWorkspace mrhs_workspace(const MrhsPlan& pl, uint32_t k)
 bool whz_rate_supported(uint32_t rate);
 // for k right-hand sides, FP32 or BF16 U; `tune` (may be null) can fix the
 // column slab count and keep FP32 U on the FP32 MFMA
-MrhsPlan whz_mrhs_plan(uint32_t rows, uint32_t cols, uint32_t row_begin, uint32_t row_end, int num_cus, uint32_t k,
+MrhsPlan whz_mrhs_plan(uint32_t rate, uint32_t rows, uint32_t cols, uint32_t row_begin, uint32_t row_end, int num_cus, uint32_t k,
                        bool bf16, const GemvTuning* tune = nullptr);
 // `ws`: mrhs_workspace(pl, k).total doubles of device memory; U is BF16 when
 // the plan's math is MrhsMath::Bf16, else FP32

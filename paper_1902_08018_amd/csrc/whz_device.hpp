@@ -398,7 +398,7 @@ __device__ __forceinline__ uint32_t sec_lookup(const SectionReader& sec, uint32_
 template <int STRIDE>
 __device__ __forceinline__ const uint32_t* state_word(const uint32_t* lw, const SectionReader& sec, uint32_t S)
 {
-    if constexpr (STRIDE == 1024 || STRIDE == 512 || STRIDE == 256) {
+    if constexpr (STRIDE == 1024 || STRIDE == 512 || STRIDE == 256 || STRIDE == 64) {
         // the word's byte offset, from its place in S
         const uint32_t off = (S & sec.word_mask) / (1024 / STRIDE);
         return (const uint32_t*)((const char*)lw + off);

@@ -136,6 +136,22 @@ uint32_t split_slabs(uint64_t blocks, uint32_t nbc, uint32_t lanes, uint32_t G)
     return ceil_div(nbc, (uint64_t)G * iters);
 }
 
+// log2 of the narrowest groups, from 8 lanes (fewer where a row has fewer block
+// columns), whose tiles are at least 90 % full.
+uint32_t patch_group(uint32_t nbr, uint32_t nbc, uint32_t lanes)
+{
+    uint32_t lg = 3;
+    while (lg > 2 && (1u << lg) > nbc)
+        --lg;
+    for (;;) {
+        const uint64_t tile = lanes >> lg;
+        const uint64_t span = (uint64_t)ceil_div(nbr, tile) * tile;
+        if (lg >= gemv_max_lg(lanes) || 10 * (uint64_t)nbr >= 9 * span)
+            return lg;
+        ++lg;
+    }
+}
+
 // The slabs that rule gives groups of 2^lg lanes.  Where it splits the
 // columns, calls use the context's workspace and are not captured into graphs,
 // whatever the plan's own slabs are; where it does not, the plan has one slab.
@@ -194,20 +210,13 @@ GemvPlan whz_gemv_plan(uint32_t rate, uint32_t rows, uint32_t cols, uint32_t row
     const uint32_t lanes = gemv_wg_lanes(rate), max_lg = gemv_max_lg(lanes);
     pl.lanes = lanes;
     const uint32_t nbr = pl.bi_end - pl.bi_begin;
-    uint32_t lg = 3;
-    while (lg > 2 && (1u << lg) > pl.nbc) // fewer block columns than lanes
-        --lg;
-    for (;;) { // the narrowest groups whose tiles are at least 90 % full
-        const uint64_t tile = lanes >> lg;
-        const uint64_t span = (uint64_t)ceil_div(nbr, tile) * tile;
-        if (lg >= max_lg || 10 * (uint64_t)nbr >= 9 * span)
-            break;
-        ++lg;
-    }
-    const uint32_t by_rule = rule_slabs(nbr, pl.nbc, lanes, lg);
+    uint32_t lg = patch_group(nbr, pl.nbc, lanes);
+    const uint32_t rule_lanes = rate <= 16 ? 1024u : 768u; // the rule's lanes decide what is refused
+    const uint32_t by_rule = rule_slabs(nbr, pl.nbc, rule_lanes, patch_group(nbr, pl.nbc, rule_lanes));
     pl.uncapturable = by_rule > 1;
     const uint64_t blocks = (uint64_t)nbr * pl.nbc;
-    const uint32_t resident = 2u * (num_cus > 0 ? (uint32_t)num_cus : 256u);
+    const uint32_t per_cu = rate > 24 ? 1u : 2u; // workgroups (gemv_wg_lanes)
+    const uint32_t resident = per_cu * (num_cus > 0 ? (uint32_t)num_cus : 256u);
     uint32_t rpg = 1, per_lane = 0; // blocks a lane and row; 0: not chosen yet
     if (tune && tune->lanes) {
         lg = 2;
@@ -249,8 +258,9 @@ GemvPlan whz_gemv_plan(uint32_t rate, uint32_t rows, uint32_t cols, uint32_t row
     pl.rpg = rpg;
     pl.ntiles = ceil_div(nbr, (uint64_t)(lanes >> lg) * rpg);
     const uint32_t G = 1u << lg;
-    uint32_t nslab = per_lane ? ceil_div(pl.nbc, (uint64_t)G * per_lane)
-                              : split_slabs(blocks, pl.nbc, lanes, G);
+    uint32_t nslab = per_lane              ? ceil_div(pl.nbc, (uint64_t)G * per_lane)
+                     : tune && tune->lanes ? split_slabs(blocks, pl.nbc, rule_lanes, G)
+                                           : by_rule;
     if (tune && tune->slabs)
         nslab = tune->slabs;
     const uint32_t max_slabs = ceil_div(pl.nbc, G);
@@ -291,7 +301,7 @@ hipError_t whz_gemv(uint32_t rate, const GemvPlan& pl, AccMode mode, const void*
     }
 }
 
-MrhsPlan whz_mrhs_plan(uint32_t rows, uint32_t cols, uint32_t row_begin, uint32_t row_end, int num_cus, uint32_t k,
+MrhsPlan whz_mrhs_plan(uint32_t rate, uint32_t rows, uint32_t cols, uint32_t row_begin, uint32_t row_end, int num_cus, uint32_t k,
                        bool bf16, const GemvTuning* tune)
 {
     (void)rows;
@@ -305,7 +315,7 @@ MrhsPlan whz_mrhs_plan(uint32_t rows, uint32_t cols, uint32_t row_begin, uint32_
     pl.cols = cols;
     pl.nrows = row_end - row_begin;
     const uint32_t nbr = pl.bi_end - pl.bi_begin;
-    const uint32_t tile_rows = 4u * (uint32_t)mrhs_waves((int)((k + 15) / 16), math);
+    const uint32_t tile_rows = 4u * (uint32_t)mrhs_waves((int)((k + 15) / 16), (int)rate / 2);
     pl.ntiles = (nbr + tile_rows - 1) / tile_rows;
     // two workgroups are resident per CU; about two rounds of them, then the
     // slab count rounded up to a multiple of 8: on 65536^2 with up to 16

@@ -87,8 +87,21 @@ __device__ __forceinline__ void load_block_words(const uint32_t* __restrict__ g,
 }
 
 // Staged blocks live word-major in LDS: word q of the block of lane l is at
-// lds[q * STRIDE + l] (STRIDE = the workgroup's lanes), so every lane-varying
-// read of a wave touches 64 distinct banks.
+// lds[q * STRIDE + l], so every lane-varying read of a wave touches 64 distinct
+// banks.  STRIDE is the workgroup's lanes where that is a power of two (the
+// word's place in the decoder's state is then the byte offset, or a shift of
+// it); other workgroups stage each wave's blocks on their own, 64 lanes a word
+// (16384 x 16384 GEMV at rates 20 and 24: 330 and 355
+// us with a product by 768 at every read, 326 and 350 so).
+template <int T>
+constexpr int kStageStride = (T & (T - 1)) == 0 ? T : 64;
+// A thread's column where a lane stages WORDS words.
+template <int T, int WORDS>
+__device__ __forceinline__ uint32_t stage_column(uint32_t tid)
+{
+    return kStageStride<T> == T ? tid : (tid & ~63u) * WORDS + (tid & 63u);
+}
+
 // Stage one block (NW words at g) at lw = lds + lane.
 template <int NW, int STRIDE>
 __device__ __forceinline__ void stage_block(uint32_t* lw, const uint32_t* __restrict__ g, uint32_t (&w)[NW])
@@ -139,22 +152,24 @@ __global__ void __launch_bounds__(kThreads) decode_blocks_kernel(const uint32_t*
 // patch of blocks (lane l: block row 8i + l / 8, block column 8j + l % 8):
 // the lanes run the bit planes in lockstep, and neighbouring blocks need more
 // alike numbers of planes and lookups than 64 blocks along one row.  Wide
-// workgroups share one copy of the section table among more waves.
+// workgroups share one copy of the section table among more waves: at rates 20
+// and 24 12 of them, two workgroups a CU, 16384 x 16384 in 412 and 445 us (8
+// waves: 477 and 522).
 template <int NW>
-constexpr int kDecThreads = NW <= 8 ? 1024 : 512;
+constexpr int kDecThreads = 64 * waves_of_two_per_cu(NW);
 
 template <int NW>
-__global__ void __launch_bounds__(kDecThreads<NW>) decode_matrix_kernel(const uint32_t* __restrict__ stream,
+__global__ void __launch_bounds__(kDecThreads<NW>, kDecThreads<NW> / 128) decode_matrix_kernel(const uint32_t* __restrict__ stream,
                                                                         uint32_t nbr, uint32_t nbc, uint32_t npc,
                                                                         uint64_t npatch, uint32_t rows, uint32_t cols,
                                                                         float* __restrict__ out)
 {
-    constexpr int T = kDecThreads<NW>;
+    constexpr int T = kDecThreads<NW>, STRIDE = kStageStride<T>;
     constexpr uint32_t kWaves = T / 64;
     __shared__ uint32_t lds[T * kStagedWords<NW>];
     __shared__ __align__(16) uint32_t tab[kSecEntries];
-    uint32_t* row = lds + threadIdx.x;
-    clear_pad<NW, T>(row);
+    uint32_t* row = lds + stage_column<T, kStagedWords<NW>>(threadIdx.x);
+    clear_pad<NW, STRIDE>(row);
     load_section_table<T>(tab, [] {});
     const SectionReader sec = section_reader<kWideState<NW>>(tab);
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64u);
@@ -165,10 +180,10 @@ __global__ void __launch_bounds__(kDecThreads<NW>) decode_matrix_kernel(const ui
         if (bi >= nbr || bj >= nbc)
             continue;
         uint32_t w[NW];
-        stage_block<NW, T>(row, stream + (bi * nbc + bj) * NW, w);
+        stage_block<NW, STRIDE>(row, stream + (bi * nbc + bj) * NW, w);
         const int emax = block_emax(w[0]);
         uint32_t iv[16];
-        decode_block_ints<NW, T>(row, sec, w, iv, [] {});
+        decode_block_ints<NW, STRIDE>(row, sec, w, iv, [] {});
         if ((cols & 3u) == 0 && 4 * bi + 3 < rows) { // a whole block on 16-byte aligned rows
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
@@ -413,7 +428,7 @@ __device__ __forceinline__ float4 block_ut(float4 uu)
     return make_float4(ut[0], ut[1], ut[2], ut[3]);
 }
 
-// The workgroup's lanes (1024, or 768 from 17 bits/value) form groups of
+// The workgroup's lanes (1024, or 768 from 17 to 24 bits/value) form groups of
 // 2^lg lanes (4 to 512).  A group sweeps a block row's slab of block columns,
 // its lanes striding them; the workgroup's tile is (lanes >> lg) groups x rpg
 // block rows, group g taking the tile's rows g, g + groups, ...  Square and
@@ -421,9 +436,11 @@ __device__ __forceinline__ float4 block_ut(float4 uu)
 // blocks); narrow ones (few block columns) use smaller groups, so that every
 // lane has blocks to decode, and few block rows wider ones.  Output row i of
 // the range is matrix row 4 * bi_begin + skip + i.
-// two workgroups per CU: 1024-lane ones in 64 VGPRs (32 waves)
+// Two workgroups per CU: 1024-lane ones in 64 VGPRs (32 waves).  Above 24
+// bits/value a CU's LDS holds the blocks of one workgroup, and that of 1024
+// lanes (16384 x 16384 at rate 32: 445 us; with 768, three waves a SIMD, 570).
 template <int NW>
-constexpr int kGemvMinWaves = kGemvThreads<NW> == 1024 ? 8 : 6;
+constexpr int kGemvMinWaves = NW == 16 ? 4 : (kGemvThreads<NW> == 1024 ? 8 : 6);
 // Block columns whose B^T u a workgroup holds in LDS: its slab's, made once
 // and read by all its block rows.  The planner's slabs of narrow groups have
 // at most 384; a wider slab (wide groups, so few block rows) makes B^T u at
@@ -449,7 +466,7 @@ __global__ void __launch_bounds__(kGemvThreads<NW>, kGemvMinWaves<NW>) gemv_kern
                                                         uint32_t cols, uint32_t nrows, uint32_t lg, uint32_t rpg,
                                                         uint32_t skip)
 {
-    constexpr int THREADS = kGemvThreads<NW>;
+    constexpr int THREADS = kGemvThreads<NW>, STRIDE = kStageStride<THREADS>;
     constexpr bool kShared = kGemvSumsInStaging<NW>;
     __shared__ __align__(16) uint32_t lds[THREADS * kStagedWords<NW>];
     __shared__ __align__(16) uint32_t tab[kSecEntries];
@@ -463,7 +480,7 @@ __global__ void __launch_bounds__(kGemvThreads<NW>, kGemvMinWaves<NW>) gemv_kern
     __shared__ double red_own[kShared ? 1 : THREADS];
     static_assert(!kShared || kStagedWords<NW> >= 2, "the row sums fit the staging rows");
     double* red = kShared ? reinterpret_cast<double*>(lds) : red_own;
-    uint32_t* row = lds + threadIdx.x;
+    uint32_t* row = lds + stage_column<THREADS, kStagedWords<NW>>(threadIdx.x);
     const uint32_t tile = blockIdx.x / nslab, slab = blockIdx.x % nslab;
     const uint32_t bc0 = slab * slab_bc;
     const uint32_t bc1 = bc0 + slab_bc < nbc ? bc0 + slab_bc : nbc;
@@ -476,7 +493,7 @@ __global__ void __launch_bounds__(kGemvThreads<NW>, kGemvMinWaves<NW>) gemv_kern
     uint32_t w[NW];
     if (bi0 + grp < bi_end && bc0 + gl < bc1)
         load_block_words<NW>(src, w);
-    clear_pad<NW, THREADS>(row);
+    clear_pad<NW, STRIDE>(row);
     load_section_table<THREADS>(tab, [&] {
         if (slab_fits) {
             for (uint32_t j = threadIdx.x; j < bc1 - bc0; j += THREADS) {
@@ -518,7 +535,7 @@ __global__ void __launch_bounds__(kGemvThreads<NW>, kGemvMinWaves<NW>) gemv_kern
         while (more) {
 #pragma unroll
             for (int k = 0; k < NW; ++k)
-                row[k * THREADS] = w[k];
+                row[k * STRIDE] = w[k];
             const uint32_t w0 = w[0], at = bj;
             uint32_t cur[NW];
 #pragma unroll
@@ -535,7 +552,7 @@ __global__ void __launch_bounds__(kGemvThreads<NW>, kGemvMinWaves<NW>) gemv_kern
             if constexpr (Acc::kPerProduct) {
                 // Fig. 7: each FP32 product of the decoded value and u is
                 // added to the FP64 sum on its own
-                decode_block_ints<NW, THREADS>(row, sec, cur, iv, next);
+                decode_block_ints<NW, STRIDE>(row, sec, cur, iv, next);
                 const float4 uu = slab_fits ? slab_u[at - bc0] : block_u(u, at, cols);
                 const int k = block_emax(w0) - 30;
 #pragma unroll
@@ -549,7 +566,7 @@ __global__ void __launch_bounds__(kGemvThreads<NW>, kGemvMinWaves<NW>) gemv_kern
                 // coefficients against B^T u (FP32); B is applied once to the
                 // row group's sums below
                 bool cut;
-                decode_block_coeffs<NW, THREADS>(row, sec, cur, iv, cut, next);
+                decode_block_coeffs<NW, STRIDE>(row, sec, cur, iv, cut, next);
                 const float4 ut = slab_fits ? slab_ut[at - bc0] : block_ut(block_u(u, at, cols));
                 float v[4];
 #pragma unroll
@@ -634,8 +651,10 @@ __global__ void __launch_bounds__(kGemvThreads<NW>, kGemvMinWaves<NW>) gemv_kern
 // block columns itself, so the main kernel has no workgroup barrier after its
 // start: each wave runs on its own.
 //
-// Workgroup = mrhs_waves(NT) waves, a tile of 4 block rows per wave x a slab
-// of block columns: 16 waves (1024 lanes) for up to 16 right-hand sides, so
+// Workgroup = mrhs_waves(NT, NW) waves, a tile of 4 block rows per wave x a slab
+// of block columns: 16 waves (1024 lanes) for up to 16 right-hand sides (12 and
+// 8 above 16 bits/value: 16384 x 16384, 8 vectors, at rates 20, 24 and 32 501,
+// 508 and 534 us with 16 waves and one workgroup a CU, 451, 461 and 508 so), so
 // that two workgroups fit a CU in LDS and 32 waves in 64 VGPRs each; 8 waves
 // for more, whose FP64 sums leave registers for 16 waves.  Per step of 16
 // block columns, each lane decodes one block of its wave's 4 x 16 tile (with
@@ -673,9 +692,7 @@ __global__ void __launch_bounds__(kGemvThreads<NW>, kGemvMinWaves<NW>) gemv_kern
 // so each lane's four accumulators are the four coefficient rows of one
 // block row.  The FP32 MFMA accumulators cover one step (K = 64); after
 // every step they are added into FP64 sums.
-static_assert(4 * mrhs_waves(1, MrhsMath::F32) <= (int)kMrhsMaxTileBlockRows &&
-                  4 * mrhs_waves(4, MrhsMath::F32) <= (int)kMrhsMaxTileBlockRows &&
-                  4 * mrhs_waves(2, MrhsMath::X6) <= (int)kMrhsMaxTileBlockRows,
+static_assert(4 * mrhs_waves(1, 1) <= (int)kMrhsMaxTileBlockRows && 4 * mrhs_waves(4, 1) <= (int)kMrhsMaxTileBlockRows,
               "block rows per multi-RHS workgroup");
 constexpr int kMathF32 = (int)MrhsMath::F32, kMathBf16 = (int)MrhsMath::Bf16, kMathX6 = (int)MrhsMath::X6,
               kMathF32N = (int)MrhsMath::F32N;
@@ -888,21 +905,24 @@ constexpr int kX6Ahead = 2;
 // two workgroups per CU, i.e. W / 2 waves per SIMD: the register budget the
 // compiler must meet (64 VGPRs at 16 waves, 128 at 8)
 template <int NW, int MATH, int NT>
-__global__ void __launch_bounds__(64 * mrhs_waves(NT, (MrhsMath)MATH), mrhs_waves(NT, (MrhsMath)MATH) / 2)
+__global__ void __launch_bounds__(64 * mrhs_waves(NT, NW), mrhs_waves(NT, NW) / 2)
     mrhs_kernel(const uint32_t* __restrict__ stream, const void* __restrict__ btu, uint32_t k, float* __restrict__ Y,
                 uint32_t ldy, double* __restrict__ part, uint32_t nbc, uint32_t bi_begin, uint32_t bi_end,
                 uint32_t slab_bc, uint32_t nslab, uint32_t nrows_out)
 {
     constexpr bool BF16U = MATH == kMathBf16, X6 = MATH == kMathX6, NARROW = MATH == kMathF32N;
-    constexpr int W = mrhs_waves(NT, (MrhsMath)MATH), T = 64 * W;
+    constexpr int W = mrhs_waves(NT, NW), T = 64 * W;
     // accumulator tiles per lane: one per group of 16 right-hand sides, or
     // one for the 4x4x1 path (its groups of 4 lie in different lanes)
     constexpr int NA = NARROW ? 1 : NT;
     constexpr int kPieces = mrhs_tile_pieces(MATH), kOwnPieces = kPieces > NW ? kPieces - NW : 0;
-    __shared__ __align__(16) uint32_t lds[T * (kStagedWords<NW> + kOwnPieces)];
+    constexpr int kWords = kStagedWords<NW> + kOwnPieces, STRIDE = kStageStride<T>;
+    __shared__ __align__(16) uint32_t lds[T * kWords];
     __shared__ __align__(16) uint32_t tab[kSecEntries];
-    uint32_t* row = lds + threadIdx.x;
-    clear_pad<NW, T>(row);
+    static_assert(W < waves_of_two_per_cu(NW) || sizeof(lds) + sizeof(tab) <= kLdsPerWorkgroupOfTwo,
+                  "two workgroups fit a CU");
+    uint32_t* row = lds + stage_column<T, kWords>(threadIdx.x);
+    clear_pad<NW, STRIDE>(row);
     load_section_table<T>(tab, [] {}); // the last workgroup barrier
     const SectionReader sec = section_reader<kWideState<NW>>(tab);
 
@@ -916,7 +936,7 @@ __global__ void __launch_bounds__(64 * mrhs_waves(NT, (MrhsMath)MATH), mrhs_wave
     // row r of the wave's piece p (the pieces past the block's words lie past
     // the pad)
     const auto piece_row = [&](int p, int r) {
-        return lds + (wave * kTilePiece + (p < NW ? p : p + kStagedWords<NW> - NW) * T + r * 16);
+        return lds + (stage_column<T, kWords>(wave * kTilePiece) + (p < NW ? p : p + kStagedWords<NW> - NW) * STRIDE + r * 16);
     };
     const float* btf = static_cast<const float*>(btu);
     const uint16_t* btb = static_cast<const uint16_t*>(btu);
@@ -924,7 +944,7 @@ __global__ void __launch_bounds__(64 * mrhs_waves(NT, (MrhsMath)MATH), mrhs_wave
     // 16-wave workgroups load each step's block words at the step (their
     // registers hold no next step's words); smaller ones keep them in flight
     // one step ahead
-    constexpr bool kAhead = W < 16;
+    constexpr bool kAhead = NT > 1;
     uint32_t w[NW];
     if constexpr (kAhead) {
         const bool valid = bi < bi_end && bc0 + c < bc1;
@@ -958,7 +978,7 @@ __global__ void __launch_bounds__(64 * mrhs_waves(NT, (MrhsMath)MATH), mrhs_wave
         }
 #pragma unroll
         for (int q = 0; q < NW; ++q)
-            row[q * T] = w[q];
+            row[q * STRIDE] = w[q];
         uint32_t cur[NW];
 #pragma unroll
         for (int q = 0; q < NW; ++q)
@@ -988,7 +1008,7 @@ __global__ void __launch_bounds__(64 * mrhs_waves(NT, (MrhsMath)MATH), mrhs_wave
             // when 16 waves share the registers
             const uint32_t g = (uint32_t)lane >> 4, j = (uint32_t)lane & 15u;
 #pragma unroll
-            for (int h = 0; h < (W >= 16 ? 1 : 2); ++h)
+            for (int h = 0; h < (NT == 1 ? 1 : 2); ++h)
 #pragma unroll
                 for (int n = 0; n < NT; ++n)
                     bh[h][n] = *reinterpret_cast<const u32x4*>(
@@ -1005,7 +1025,7 @@ __global__ void __launch_bounds__(64 * mrhs_waves(NT, (MrhsMath)MATH), mrhs_wave
         // ---- decode one block per lane: scaled coefficients (registers)
         uint32_t cf[16];
         bool cut;
-        decode_block_coeffs<NW, T>(row, sec, cur, cf, cut, [] {});
+        decode_block_coeffs<NW, STRIDE>(row, sec, cur, cf, cut, [] {});
         float sc[16];
         scale_coeffs(cf, cur[0], sc);
         if constexpr (kCanCut<NW>)
@@ -1150,7 +1170,7 @@ __global__ void __launch_bounds__(64 * mrhs_waves(NT, (MrhsMath)MATH), mrhs_wave
             // reads below spread over the banks); lane l then holds A[l %
             // 16][8 (l / 16) .. + 7] (two block columns) and B[8 (l / 16) ..
             // + 7][l % 16]
-            if constexpr (W >= 16) {
+            if constexpr (NT == 1) {
                 const uint32_t g = (uint32_t)lane >> 4, j = (uint32_t)lane & 15u;
 #pragma unroll
                 for (int n = 0; n < NT; ++n)
@@ -1357,7 +1377,7 @@ hipError_t launch_mrhs_t(const MrhsPlan& pl, const uint32_t* s, const void* btu,
                          double* part, hipStream_t st)
 {
     hipLaunchKernelGGL((mrhs_kernel<NW, MATH, NT>), dim3(pl.ntiles * pl.nslab),
-                       dim3(64 * mrhs_waves(NT, (MrhsMath)MATH)), 0, st, s, btu, k, Y, ldy, part, pl.nbc, pl.bi_begin,
+                       dim3(64 * mrhs_waves(NT, NW)), 0, st, s, btu, k, Y, ldy, part, pl.nbc, pl.bi_begin,
                        pl.bi_end, pl.slab_bc, pl.nslab, pl.nrows);
     return hipGetLastError();
 }

@@ -10,6 +10,8 @@
                  every math (1e-6 FP32, 2e-3 BF16: the stated tolerances)
   thermal rows   rows of 0 to 11 entries (the kernel takes five at a time),
                  columns out of range and infinities where nothing reads
+  decode         workgroups of 16, 12 and 8 waves (by rate), the last one's
+                 waves partly without a patch of blocks: exact
   encode         a stream that starts on 4 bytes but not on 16; more blocks
                  than one sweep of the grid
 """
@@ -24,7 +26,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("flags", [wh.WH_ACC_DEFAULT, wh.WH_ACC_TWOSUM, wh.WH_PAPER_MP])
-@pytest.mark.parametrize("rate", [2, 4, 8, 12, 16, 24, 32])
+@pytest.mark.parametrize("rate", [2, 4, 8, 12, 16, 20, 24, 32])
 def test_slab_vector_limits(monkeypatch, rate, flags):
     rows, cols = 61, 4 * 400 + 2  # 401 block columns, the last one partial
     spec = synth.MatrixSpec(rows, cols, 48, 8.0, seed=61)
@@ -62,6 +64,18 @@ def test_batched_tile_places(gpu_ctx, rate, k, dtype):
     torch.cuda.synchronize()
     err = np.linalg.norm(Y.cpu().numpy() - ref, axis=1) / np.linalg.norm(ref, axis=1)
     assert err.max() <= (2e-3 if dtype == "bf16" else 1e-6), err.max()
+    wh.wh_unload(gpu_ctx, mat)
+
+
+@pytest.mark.parametrize("rate", [16, 20, 24, 32])
+def test_decode_workgroups(gpu_ctx, rate):
+    rows, cols = 4 * 8 * 5 - 2, 4 * 8 * 5 - 4  # 5 x 5 patches of 8 x 8 blocks
+    s = oracle.encode(synth.matrix(synth.MatrixSpec(rows, cols, 16, 4.0, seed=65)), rate)
+    mat = wh.wh_load_compressed(gpu_ctx, rows, cols, wh.WH_FMT_ZFP_FIXED_RATE, rate, s)
+    out = torch.full((rows, cols), float("nan"), device="cuda")
+    wh.wh_decode(gpu_ctx, mat, out)
+    torch.cuda.synchronize()
+    assert np.array_equal(out.cpu().numpy(), oracle.decode(s, rows, cols, rate))
     wh.wh_unload(gpu_ctx, mat)
 
 
