@@ -301,8 +301,25 @@ hipError_t whz_gemv(uint32_t rate, const GemvPlan& pl, AccMode mode, const void*
     }
 }
 
-MrhsPlan whz_mrhs_plan(uint32_t rate, uint32_t rows, uint32_t cols, uint32_t row_begin, uint32_t row_end, int num_cus, uint32_t k,
-                       bool bf16, const GemvTuning* tune)
+// What a multi-RHS call of `nslab` column slabs takes, in the time of a step of
+// 16 block columns at two workgroups a CU (`resident` of them; about 7 us).
+// The workgroups of a launch are of one length, so they go in rounds: a last
+// round of at most one a CU takes 0.6 of a full one's time, a fuller last round
+// all of it.  But workgroups drift apart: six tenths of the time go as if
+// rounds had no edges.  Partials (`per_slab` doubles each) are written and read
+// at 3 TB/s.
+double mrhs_shape_cost(uint32_t nslab, uint32_t ntiles, uint32_t steps, uint64_t per_slab, uint32_t resident)
+{
+    const uint32_t it = ceil_div(steps, nslab);
+    const uint64_t wgs = (uint64_t)ntiles * nslab, rest = wgs % resident;
+    const double alone = 0.3 + 0.6 * it, full = 0.3 + it;
+    const double rounds = (double)(wgs / resident) * full + (rest == 0 ? 0.0 : 2 * rest <= resident ? alone : full);
+    const double even = std::max((double)wgs / resident * full + 0.3 * it, alone);
+    return 0.4 * rounds + 0.6 * even + (nslab > 1 ? 0.2 + (double)nslab * (double)per_slab * 8.0 / 21e6 : 0.0);
+}
+
+MrhsPlan whz_mrhs_plan(uint32_t rate, uint32_t rows, uint32_t cols, uint32_t row_begin, uint32_t row_end,
+                       int num_cus, uint32_t k, bool bf16, const GemvTuning* tune)
 {
     (void)rows;
     const uint32_t slabs = tune ? tune->mrhs_slabs : 0;
@@ -317,32 +334,38 @@ MrhsPlan whz_mrhs_plan(uint32_t rate, uint32_t rows, uint32_t cols, uint32_t row
     const uint32_t nbr = pl.bi_end - pl.bi_begin;
     const uint32_t tile_rows = 4u * (uint32_t)mrhs_waves((int)((k + 15) / 16), (int)rate / 2);
     pl.ntiles = (nbr + tile_rows - 1) / tile_rows;
-    // two workgroups are resident per CU; about two rounds of them, then the
-    // slab count rounded up to a multiple of 8: on 65536^2 with up to 16
-    // right-hand sides, 8 to 12 slabs (5 to 8 rounds) run 5.4 ms where 3
-    // slabs (two rounds and two workgroups) take 6.2 ms and 5 to 7 take
-    // 5.65 ms.  The L2 miss count is the same for 3 and 8 slabs (34.5 M and
-    // 34.1 M): the gain is the shorter last round, not where B^T U is
-    // cached.  Each column slab adds FP64 partials, slabs x k x rows
-    const uint64_t want = (uint64_t)(num_cus > 0 ? num_cus : 256) * 4;
-    const uint32_t max_slabs = (pl.nbc + 15) / 16;
-    uint32_t nslab = pl.ntiles ? (uint32_t)((want + pl.ntiles - 1) / pl.ntiles) : 1;
-    if (nslab < 1)
-        nslab = 1;
-    if (max_slabs >= 8)
-        nslab = (nslab + 7) / 8 * 8;
     // the FP64 partials (slabs x k x rows) stay within 256 MiB: 8 slabs of up
     // to 64 right-hand sides over 65536 rows (at k = 64, 8 slabs take 7.27 ms
     // where 2 took 7.60); short row ranges (few tiles, which need the slabs to
     // fill the device) keep theirs
     const uint64_t per_slab = (uint64_t)std::max<uint32_t>(k, 1) * nbr * 4;
     const uint32_t cap = (uint32_t)std::max<uint64_t>(1, (32ull << 20) / std::max<uint64_t>(per_slab, 1));
-    if (nslab > cap)
-        nslab = cap;
+    const uint32_t steps = (pl.nbc + 15) / 16, resident = 2u * (num_cus > 0 ? (uint32_t)num_cus : 256u);
+    // about two rounds of workgroups in a multiple of 8 slabs (65536^2 with up
+    // to 16 right-hand sides: 8 slabs 5.4 ms where 3 take 6.2), unless the cost
+    // above says that another count is 2 % better.  From sweeps over 22 shapes
+    // (us, this count and the chosen one): 48573 x 660 BF16 with 42 vectors 81 /
+    // 58, 4096^2 with 64 67 / 55, 30000 x 700 with 20 59 / 51, 300 x 40000 at
+    // rate 16 with 12 58 / 49, 1500 x 20000 BF16 with 64 76 / 65; none slower
+    uint32_t nslab = pl.ntiles ? ceil_div(2 * (uint64_t)resident, pl.ntiles) : 1;
+    if (steps >= 8)
+        nslab = (nslab + 7) / 8 * 8;
+    nslab = std::max(1u, std::min(std::min(nslab, cap), steps));
+    const auto cost_of = [&](uint32_t n) { return mrhs_shape_cost(n, pl.ntiles, steps, per_slab, resident); };
+    double best = 0.98 * cost_of(nslab);
+    for (uint32_t it = 1; it < steps; it += std::max(1u, it / 16)) { // steps a slab
+        const uint32_t n = ceil_div(steps, it);
+        if (n <= cap && cost_of(n) < best) {
+            best = cost_of(n);
+            nslab = n;
+        }
+    }
+    if (cost_of(1) < best)
+        nslab = 1;
     if (slabs)
         nslab = slabs;
-    if (nslab > max_slabs)
-        nslab = max_slabs ? max_slabs : 1;
+    if (nslab > steps)
+        nslab = steps ? steps : 1;
     uint32_t slab_bc = (pl.nbc + nslab - 1) / nslab;
     slab_bc = (slab_bc + 15) / 16 * 16;
     pl.slab_bc = slab_bc ? slab_bc : 16;
