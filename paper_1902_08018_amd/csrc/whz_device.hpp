@@ -557,7 +557,8 @@ __device__ __forceinline__ void decode_plane(BlockReader<NW, STRIDE>& rd, PlaneC
 // An odd plane reads 64 bits from its position and leaves the even plane below
 // it its window, so that a pair waits for the stream once; the even plane reads
 // on only where its section takes more than one lookup.  (65536^2 at rate 8:
-// 2.85 ms; 3.00 with the 32 bits ahead read in every plane, which takes 6
+// 2.94 ms (before the transposes shifted two registers at once, 2.86 now);
+// 3.00 with the 32 bits ahead read in every plane, which takes 6
 // cycles more a plane; 3.06 with every plane's window read in turn.)
 template <int NW, int STRIDE, int P, int LAST>
 __device__ __forceinline__ void decode_planes_from(BlockReader<NW, STRIDE>& rd, PlaneCursor& c, uint32_t (&G)[8])

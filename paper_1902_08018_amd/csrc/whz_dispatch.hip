@@ -191,7 +191,7 @@ double row_group_cost(uint32_t lg)
 // 256 workgroups (1 to 4 blocks) 29.7 / 26.4 / 32.3 / 26.7, the 378 x 256000
 // slit with 3 / 4 / 6 / 8 / 12 blocks 87.4 / 83.0 / 84.2 / 86.3 / 90.0, 10000^2
 // with 3 / 4 / 5 / 6 / 8 blocks 108.3 / 106.7 / 101.7 / 107.2 / 110.8, and
-// 256 x 1024 at rate 16 with 1 / 3 blocks 17 / 26.
+// 256 x 1024 at rate 16 with 1 / 3 blocks 16.3 / 26.1.
 double gemv_shape_cost(uint32_t wgs, uint32_t iters, uint32_t resident)
 {
     const double start = 0.8;

@@ -4,15 +4,15 @@
 //
 // Fused GEMV (the deformation product y = C.S of Eq. 2 over a zfp-compressed
 // matrix, Sec. 4.3-4.4):
-//   grid     one workgroup (1024 lanes, or 768 above 16 bits/value) per (row
+//   grid     one workgroup (1024 lanes, or 768 at 17 to 24 bits/value) per (row
 //            tile, column slab)
 //   lanes    groups of 2^lg lanes (8 by default); a group sweeps one block
 //            row's slab, each lane decoding one 4x4 block per step (its
 //            words staged in LDS), so a wave works on an 8 x 8 patch of
 //            blocks; a tile holds (lanes / 2^lg) x rpg block rows
-//   bound    the decoder's vector instructions: 65536^2 at rate 8 takes 3.00
+//   bound    the decoder's vector instructions: 65536^2 at rate 8 takes 2.80
 //            ms (3.67 before the one-register state, the 64-bit window and
-//            the half transposes), 1.43 TB/s of stream; the wave's VALU
+//            the half transposes), 1.54 TB/s of stream; the wave's VALU
 //            cycles fill about 85 % of the time and LDS 60 %
 //   product  each block's coefficients against B^T u (FP32), its power-of-two
 //            scale applied to the sum; B once per block row at the end; blocks
@@ -544,9 +544,19 @@ __global__ void __launch_bounds__(kGemvThreads<NW>, kGemvMinWaves<NW>) gemv_kern
             bj += G;
             src += (uint64_t)G * NW;
             more = bj < bc1;
+            // The words are new on both ways (unset past the last block): were
+            // the old ones kept, the compiler would copy the loaded ones at
+            // once, and every block would wait for memory here (65536^2 at rate
+            // 8 2.86 ms so, 2.80 without; 4096^2 at rate 16, where the copies
+            // spilled as well, 34.3 and 31.7 us).
             const auto next = [&] {
-                if (more)
+                if (more) {
                     load_block_words<NW>(src, w);
+                } else {
+#pragma unroll
+                    for (int k = 0; k < NW; ++k)
+                        asm volatile("" : "=v"(w[k]));
+                }
             };
             uint32_t iv[16];
             if constexpr (Acc::kPerProduct) {
@@ -657,8 +667,8 @@ __global__ void __launch_bounds__(kGemvThreads<NW>, kGemvMinWaves<NW>) gemv_kern
 // 508 and 534 us with 16 waves and one workgroup a CU, 451, 461 and 508 so), so
 // that two workgroups fit a CU in LDS and 32 waves in 64 VGPRs each; 8 waves
 // for more, whose FP64 sums leave registers for 16 waves.  Per step of 16
-// block columns, each lane decodes one block of its wave's 4 x 16 tile (with
-// 8-wave workgroups the next step's block words are already in flight) and
+// block columns, each lane decodes one block of its wave's 4 x 16 tile (above 16
+// right-hand sides the next step's block words are already in flight) and
 // keeps its coefficients, scaled by the block's 2^(emax - 30), in registers;
 // then
 //   FP32 U   four quarters of 4 block columns: the quarter's lanes write their
@@ -899,11 +909,12 @@ __device__ __forceinline__ void mrhs_load_bx(const uint16_t* __restrict__ btb, u
 
 // X6: (half, group) B parts loaded ahead of their MFMAs, the first of them
 // before the decode (one, two or three ahead time the same at 65536^2, k = 64:
-// 7.29 / 7.27 / 7.28 ms; two take the fewest registers).
+// 7.29 / 7.27 / 7.28 ms when measured, and 6.34 for two now; two take the
+// fewest registers).
 constexpr int kX6Ahead = 2;
 
 // two workgroups per CU, i.e. W / 2 waves per SIMD: the register budget the
-// compiler must meet (64 VGPRs at 16 waves, 128 at 8)
+// compiler must meet (64 VGPRs at 16 waves, 80 at 12, 128 at 8)
 template <int NW, int MATH, int NT>
 __global__ void __launch_bounds__(64 * mrhs_waves(NT, NW), mrhs_waves(NT, NW) / 2)
     mrhs_kernel(const uint32_t* __restrict__ stream, const void* __restrict__ btu, uint32_t k, float* __restrict__ Y,
@@ -941,9 +952,9 @@ __global__ void __launch_bounds__(64 * mrhs_waves(NT, NW), mrhs_waves(NT, NW) / 
     const float* btf = static_cast<const float*>(btu);
     const uint16_t* btb = static_cast<const uint16_t*>(btu);
 
-    // 16-wave workgroups load each step's block words at the step (their
-    // registers hold no next step's words); smaller ones keep them in flight
-    // one step ahead
+    // the wide workgroups of one group of 16 right-hand sides load each step's
+    // block words at the step (their registers hold no next step's words); the
+    // others keep them in flight one step ahead
     constexpr bool kAhead = NT > 1;
     uint32_t w[NW];
     if constexpr (kAhead) {
@@ -1005,7 +1016,8 @@ __global__ void __launch_bounds__(64 * mrhs_waves(NT, NW), mrhs_waves(NT, NW) / 
                 mrhs_load_bx<NT>(btb, cb, i / NT, i % NT, lane, bx[i]);
         } else if constexpr (BF16U) {
             // the second half's operands load once the first half starts
-            // when 16 waves share the registers
+            // with one group of 16 (its workgroups share the registers among
+            // more waves)
             const uint32_t g = (uint32_t)lane >> 4, j = (uint32_t)lane & 15u;
 #pragma unroll
             for (int h = 0; h < (NT == 1 ? 1 : 2); ++h)
@@ -1065,11 +1077,11 @@ __global__ void __launch_bounds__(64 * mrhs_waves(NT, NW), mrhs_waves(NT, NW) / 
             }
         } else if constexpr (MATH == kMathF32) {
             // ---- four quarters of 4 block columns, two at a time (16384 x
-            // 16384, rate 8: 314 us; in four turns of one 324): the half's lanes write their blocks to
-            // their quarter's 16 x 16 tile (row 4t + r, a 4-float group per
-            // block column, the group index XORed with t so that the column
-            // reads below spread over the banks), then every lane reads its A
-            // operands
+            // 16384, rate 8: 314 us; in four turns of one 324): the half's
+            // lanes write their blocks to their quarter's 16 x 16 tile (row
+            // 4t + r, a 4-float group per block column, the group index XORed
+            // with t so that the column reads below spread over the banks),
+            // then every lane reads its A operands
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 // the tile is the wave's own: lanes read what other lanes of

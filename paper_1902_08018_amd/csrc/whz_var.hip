@@ -166,7 +166,7 @@ __device__ __forceinline__ void var_planes_from(const uint32_t* row, const Secti
         if ((uint32_t)P >= lo) {
             uint32_t xv;
             // the 32 bits ahead of every plane's window, beside its lookup: with
-            // few waves a SIMD the chain is what counts (186 -> 169 us at
+            // few waves a SIMD the chain is what counts (186 -> 162 us at
             // 8192^2 against one window read a plane)
             const uint32_t ahead = bits_ahead<T>(row, sec, c.S);
             const uint32_t ones = plane_bits<true, true>(sec, c, [ahead](uint32_t) { return ahead; }, xv);
