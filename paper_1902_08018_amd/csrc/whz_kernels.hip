@@ -952,20 +952,21 @@ __global__ void __launch_bounds__(64 * mrhs_waves(NT, NW), mrhs_waves(NT, NW) / 
     const float* btf = static_cast<const float*>(btu);
     const uint16_t* btb = static_cast<const uint16_t*>(btu);
 
-    // the wide workgroups of one group of 16 right-hand sides load each step's
-    // block words at the step (their registers hold no next step's words); the
-    // others keep them in flight one step ahead
-    constexpr bool kAhead = NT > 1;
+    // The next step's block words are in flight over the decode; with one group
+    // of 16 right-hand sides, whose workgroups share the registers among more
+    // waves, over the step's last MFMAs only, when the coefficients' registers
+    // are free (16384 x 16384 at rate 8: 8 FP32 vectors 306 us with the words
+    // loaded at their step, 302 so; 16 BF16 249 and 242).
     uint32_t w[NW];
-    if constexpr (kAhead) {
-        const bool valid = bi < bi_end && bc0 + c < bc1;
-        if (valid)
-            load_block_words<NW>(stream + ((uint64_t)bi * nbc + bc0 + c) * NW, w);
+    const auto load_step = [&](uint32_t cb) { // the lane's block words of the step at cb; zeros past the matrix
+        if (bi < bi_end && cb + c < bc1)
+            load_block_words<NW>(stream + ((uint64_t)bi * nbc + cb + c) * NW, w);
         else
 #pragma unroll
             for (int q = 0; q < NW; ++q)
                 w[q] = 0u; // decodes as a zero block
-    }
+    };
+    load_step(bc0);
 
     mf32x4 acc[NA];
     double sum[NA][4];
@@ -978,15 +979,6 @@ __global__ void __launch_bounds__(64 * mrhs_waves(NT, NW), mrhs_waves(NT, NW) / 
     for (uint32_t cb = bc0; cb < bc1; cb += 16) {
         // ---- this step's block words to the lane's LDS row; the next
         // step's in flight
-        if constexpr (!kAhead) {
-            const bool valid = bi < bi_end && cb + c < bc1;
-            if (valid)
-                load_block_words<NW>(stream + ((uint64_t)bi * nbc + cb + c) * NW, w);
-            else
-#pragma unroll
-                for (int q = 0; q < NW; ++q)
-                    w[q] = 0u;
-        }
 #pragma unroll
         for (int q = 0; q < NW; ++q)
             row[q * STRIDE] = w[q];
@@ -994,15 +986,8 @@ __global__ void __launch_bounds__(64 * mrhs_waves(NT, NW), mrhs_waves(NT, NW) / 
 #pragma unroll
         for (int q = 0; q < NW; ++q)
             cur[q] = w[q];
-        if constexpr (kAhead) {
-            const bool valid = bi < bi_end && cb + 16 + c < bc1;
-            if (valid)
-                load_block_words<NW>(stream + ((uint64_t)bi * nbc + cb + 16 + c) * NW, w);
-            else
-#pragma unroll
-                for (int q = 0; q < NW; ++q)
-                    w[q] = 0u;
-        }
+        if constexpr (NT > 1)
+            load_step(cb + 16);
         // ---- B operands in flight during the decode (block columns cb ..
         // cb + 15 lie inside the workspace: it spans whole steps)
         constexpr int AH = NARROW ? kMrhsNarrowAhead : kMrhsAhead<NT>;
@@ -1073,6 +1058,8 @@ __global__ void __launch_bounds__(64 * mrhs_waves(NT, NW), mrhs_waves(NT, NW) / 
                         acc[0] = __builtin_amdgcn_mfma_f32_4x4x1f32(a4[m], bq[slot][0][m], acc[0], 0, 0, 0);
                     if (q + AH < 4) // the quarter AH on into the slot just used
                         mrhs_load_bn(btf, cb, q + AH, lane, bq[slot][0]);
+                    if (q + AH == 3) // behind the last of the step's operands
+                        load_step(cb + 16);
                 }
             }
         } else if constexpr (MATH == kMathF32) {
@@ -1112,6 +1099,8 @@ __global__ void __launch_bounds__(64 * mrhs_waves(NT, NW), mrhs_waves(NT, NW) / 
                                 __builtin_amdgcn_mfma_f32_16x16x4f32(a4[m], bq[slot][n][m], acc[n], 0, 0, 0);
                     if (q + AH < 4) // the quarter after next into the slot just used
                         mrhs_load_bq<NT>(btf, cb + 4 * (q + AH), lane, bq[slot]);
+                    if (NT == 1 && q + AH == 3) // behind the last of the step's operands
+                        load_step(cb + 16);
                 }
             }
         } else if constexpr (X6) {
@@ -1195,6 +1184,8 @@ __global__ void __launch_bounds__(64 * mrhs_waves(NT, NW), mrhs_waves(NT, NW) / 
                 *reinterpret_cast<u32x2*>(piece_row(4 * (c >> 3) + t, r) + 4 * (((c & 7) >> 1) ^ t) + 2 * (c & 1)) =
                     u32x2{pack_bf16_rne(sc[4 * r], sc[4 * r + 1]), pack_bf16_rne(sc[4 * r + 2], sc[4 * r + 3])};
             wave_sync_lds();
+            if constexpr (NT == 1)
+                load_step(cb + 16);
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 const int at = (lane >> 2) & 3;
