@@ -65,6 +65,7 @@
 #include <unordered_map>
 #include <vector>
 
+#include "serve_plan.hpp"
 #include "serve_policy.hpp"
 #include "wh_ctx.hpp"
 #include "wh_internal.hpp"
@@ -153,23 +154,10 @@ std::vector<std::pair<uint32_t, uint32_t>> serve_chunks(const Matrix& m, uint64_
     return policy::chunk_rows(m.desc.rows, m.desc.cols, values);
 }
 
-// Workspace (doubles) the k = 1 or multi-RHS plans of the chunks need: FP64
-// slab partials, and B^T U for the multi-RHS kernel (the chunks run in
-// stream order and share it).
+// Workspace (doubles) of a matrix's slot.
 size_t slot_partials(const Matrix& m, const wh_ctx* ctx)
 {
-    size_t n = 0;
-    for (const auto& c : serve_chunks(m, ctx->serve_chunk_values)) {
-        const GemvPlan gp = whz_gemv_plan(m.desc.rate, m.desc.rows, m.desc.cols, c.first, c.second, ctx->num_cus);
-        if (gp.nslab > 1)
-            n = std::max(n, (size_t)gp.nslab * gp.part_rows());
-        for (uint32_t k = 16; k <= kMaxRhs; k += 16) { // the plan and workspace depend on k
-            const MrhsPlan mp = whz_mrhs_plan(m.desc.rate, m.desc.rows, m.desc.cols, c.first, c.second, ctx->num_cus, k, false,
-                                              &ctx->gemv_tune);
-            n = std::max(n, mrhs_workspace(mp, k).total);
-        }
-    }
-    return n;
+    return serve_workspace(m.desc, serve_chunks(m, ctx->serve_chunk_values), ctx->num_cus, ctx->gemv_tune);
 }
 
 // What a matrix's slot charges against the context's HBM budget.
@@ -259,23 +247,20 @@ wh_status build_slot(wh_ctx* ctx, MatServe& ms)
         model = std::max(model, model_chunk_ms(m, c));
         for (int b = 0; b < kNumBuckets; ++b) {
             const uint32_t k = kBuckets[b];
+            const ServePlan sp = serve_plan(m.desc, c, k, ctx->num_cus, ctx->gemv_tune);
+            if (sp.workspace > part_n) // it would write past the slot's workspace
+                return WH_ERR_DEVICE;
             hipGraph_t g = nullptr;
             if (hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal) != hipSuccess)
                 return WH_ERR_DEVICE;
-            hipError_t e;
-            if (k == 1) {
-                const GemvPlan gp = whz_gemv_plan(m.desc.rate, m.desc.rows, m.desc.cols, c.first, c.second, ctx->num_cus);
-                e = whz_gemv(m.desc.rate, gp, AccMode::Fp64, m.dptr, ms.U, ms.Y + c.first, ms.part, st);
-            } else {
-                const MrhsPlan mp = whz_mrhs_plan(m.desc.rate, m.desc.rows, m.desc.cols, c.first, c.second, ctx->num_cus, k, false,
-                                                  &ctx->gemv_tune);
-                e = whz_mrhs(m.desc.rate, mp, m.dptr, ms.U, m.desc.cols, k, ms.Y + c.first, m.desc.rows,
-                             ms.part, st);
-            }
+            const hipError_t e0 =
+                k == 1 ? whz_gemv(m.desc.rate, sp.plan, AccMode::Fp64, m.dptr, ms.U, ms.Y + c.first, ms.part, st)
+                       : whz_mrhs(m.desc.rate, sp.plan, m.dptr, ms.U, m.desc.cols, k, ms.Y + c.first, m.desc.rows,
+                                  ms.part, st);
             const hipError_t e2 = hipStreamEndCapture(st, &g);
-            if (e != hipSuccess || e2 != hipSuccess || !g)
+            if (e0 != hipSuccess || e2 != hipSuccess || !g)
                 return WH_ERR_DEVICE;
-            e = hipGraphInstantiate(&ms.exec[ci * kNumBuckets + b], g, nullptr, nullptr, 0);
+            const hipError_t e = hipGraphInstantiate(&ms.exec[ci * kNumBuckets + b], g, nullptr, nullptr, 0);
             (void)hipGraphDestroy(g);
             if (e != hipSuccess || hipGraphUpload(ms.exec[ci * kNumBuckets + b], st) != hipSuccess)
                 return WH_ERR_DEVICE;
