@@ -247,7 +247,7 @@ wh_status build_slot(wh_ctx* ctx, MatServe& ms)
         model = std::max(model, model_chunk_ms(m, c));
         for (int b = 0; b < kNumBuckets; ++b) {
             const uint32_t k = kBuckets[b];
-            const ServePlan sp = serve_plan(m.desc, c, k, ctx->num_cus, ctx->gemv_tune);
+            const ServePlan sp = serve_plan(m.desc, c, k, ctx->num_cus, ctx->gemv_tune, part_n);
             if (sp.workspace > part_n) // it would write past the slot's workspace
                 return WH_ERR_DEVICE;
             hipGraph_t g = nullptr;

@@ -22,30 +22,31 @@ struct ServePlan {
     size_t workspace;
 };
 
-inline ServePlan serve_plan(const wh_matrix_desc& d, const std::pair<uint32_t, uint32_t>& chunk, uint32_t k,
-                            int num_cus, const GemvTuning& tune)
-{
-    if (k == 1) {
-        const GemvPlan pl = whz_gemv_plan(d.rate, d.rows, d.cols, chunk.first, chunk.second, num_cus);
-        return ServePlan{pl, pl.nslab > 1 ? (size_t)pl.nslab * pl.part_rows() : 0};
-    }
-    const MrhsPlan pl =
-        whz_mrhs_plan(d.rate, d.rows, d.cols, chunk.first, chunk.second, num_cus, k, false, &tune);
-    return ServePlan{pl, mrhs_workspace(pl, k).total};
-}
-
-// The workspace (doubles) of a matrix's slot: the most any of its graphs
-// uses.  Graphs run one after another (one launch stream), so they share it.
-// The slab count depends on k in either direction (fewer right-hand sides
-// make partials cheaper), so no bucket stands for another.
+// The workspace (doubles) of a matrix's slot.  Its graphs run one after
+// another (one launch stream), so they share it.
 inline size_t serve_workspace(const wh_matrix_desc& d, const std::vector<std::pair<uint32_t, uint32_t>>& chunks,
                               int num_cus, const GemvTuning& tune)
 {
     size_t n = 0;
     for (const auto& c : chunks)
-        for (uint32_t k : policy::kBuckets)
-            n = std::max(n, serve_plan(d, c, k, num_cus, tune).workspace);
+        n = std::max(n, whz_serve_workspace(d.rate, d.cols, c.first, c.second, num_cus, &tune));
     return n;
+}
+
+// A graph's plan within a slot's workspace.  The slab count the planner likes
+// best depends on k in either direction (fewer right-hand sides make partials
+// cheaper), so every bucket's plan is held to the workspace on its own.
+inline ServePlan serve_plan(const wh_matrix_desc& d, const std::pair<uint32_t, uint32_t>& chunk, uint32_t k,
+                            int num_cus, const GemvTuning& tune, size_t workspace)
+{
+    if (k == 1) { // as without launch-shape overrides, which are wh_gemv's
+        const GemvPlan pl =
+            whz_gemv_plan(d.rate, d.rows, d.cols, chunk.first, chunk.second, num_cus, nullptr, workspace);
+        return ServePlan{pl, pl.nslab > 1 ? (size_t)pl.nslab * pl.part_rows() : 0};
+    }
+    const MrhsPlan pl =
+        whz_mrhs_plan(d.rate, d.rows, d.cols, chunk.first, chunk.second, num_cus, k, false, &tune, workspace);
+    return ServePlan{pl, mrhs_workspace(pl, k).total};
 }
 
 } // namespace wh

@@ -123,15 +123,24 @@ inline MrhsWorkspace mrhs_workspace(const MrhsPlan& pl, uint32_t k)
 
 bool whz_rate_supported(uint32_t rate);
 // for k right-hand sides, FP32 or BF16 U; `tune` (may be null) can fix the
-// column slab count and keep FP32 U on the FP32 MFMA
+// column slab count and keep FP32 U on the FP32 MFMA.  `most_workspace`: the
+// doubles of workspace the plan's own choice of slabs may need; a plan of one
+// slab is given whatever it needs
 MrhsPlan whz_mrhs_plan(uint32_t rate, uint32_t rows, uint32_t cols, uint32_t row_begin, uint32_t row_end, int num_cus, uint32_t k,
-                       bool bf16, const GemvTuning* tune = nullptr);
+                       bool bf16, const GemvTuning* tune = nullptr, size_t most_workspace = SIZE_MAX);
+// The doubles of workspace that serving is given for the graphs over rows
+// [row_begin, row_end).  What a slot holds is charged against the caller's
+// budget, so it decides which matrices are served: it comes from the fixed
+// rules for slab counts (one vector; 16, 32, 48 and 64), whatever the planners'
+// costs say, and the plans are chosen to fit it.
+size_t whz_serve_workspace(uint32_t rate, uint32_t cols, uint32_t row_begin, uint32_t row_end, int num_cus,
+                           const GemvTuning* tune);
 // `ws`: mrhs_workspace(pl, k).total doubles of device memory; U is BF16 when
 // the plan's math is MrhsMath::Bf16, else FP32
 hipError_t whz_mrhs(uint32_t rate, const MrhsPlan& pl, const void* stream, const void* U, uint32_t ldu, uint32_t k,
                     float* Y, uint32_t ldy, double* part, hipStream_t st);
 GemvPlan whz_gemv_plan(uint32_t rate, uint32_t rows, uint32_t cols, uint32_t row_begin, uint32_t row_end,
-                       int num_cus, const GemvTuning* tune = nullptr);
+                       int num_cus, const GemvTuning* tune = nullptr, size_t most_workspace = SIZE_MAX);
 // Slabs of block columns for a kernel whose `lanes` lanes sweep each block row
 // of a tile of `tile_rows` block rows together (the block-scaled FP8 GEMV).
 GemvPlan block_slab_plan(uint32_t cols, uint32_t row_begin, uint32_t row_end, int num_cus, uint32_t lanes,

@@ -152,6 +152,9 @@ uint32_t patch_group(uint32_t nbr, uint32_t nbc, uint32_t lanes)
     }
 }
 
+// The workgroup lanes that rule counts with.
+uint32_t rule_lanes(uint32_t rate) { return rate <= 16 ? 1024u : 768u; }
+
 // The slabs that rule gives groups of 2^lg lanes.  Where it splits the
 // columns, calls use the context's workspace and are not captured into graphs,
 // whatever the plan's own slabs are; where it does not, the plan has one slab.
@@ -162,11 +165,8 @@ uint32_t rule_slabs(uint32_t nbr, uint32_t nbc, uint32_t lanes, uint32_t lg)
     return set_slabs(pl, split_slabs((uint64_t)nbr * nbc, nbc, lanes, 1u << lg), 1u << lg);
 }
 
-// Whether a plan's partial sums fit wh_gemv_noalloc's scratch array.
-bool fits_scratch(uint32_t nslab, uint32_t nbr)
-{
-    return nslab <= 1 || (uint64_t)nslab * nbr * 4 * sizeof(double) <= WH_NOALLOC_SCRATCH_BYTES;
-}
+// Whether a plan's partial sums fit `most` doubles.
+bool fits_partials(uint32_t nslab, uint32_t nbr, uint64_t most) { return nslab <= 1 || (uint64_t)nslab * nbr * 4 <= most; }
 
 // The slab partials' price in the unit of gemv_shape_cost: the reduce kernel
 // (4 us) and ordering the workspace's users (3 us).
@@ -203,16 +203,16 @@ double gemv_shape_cost(uint32_t wgs, uint32_t iters, uint32_t resident)
 } // namespace
 
 GemvPlan whz_gemv_plan(uint32_t rate, uint32_t rows, uint32_t cols, uint32_t row_begin, uint32_t row_end,
-                       int num_cus, const GemvTuning* tune)
+                       int num_cus, const GemvTuning* tune, size_t most_workspace)
 {
     (void)rows;
     GemvPlan pl = range_plan(cols, row_begin, row_end);
+    const uint64_t most = std::min<uint64_t>(most_workspace, WH_NOALLOC_SCRATCH_BYTES / sizeof(double));
     const uint32_t lanes = gemv_wg_lanes(rate), max_lg = gemv_max_lg(lanes);
     pl.lanes = lanes;
     const uint32_t nbr = pl.bi_end - pl.bi_begin;
     uint32_t lg = patch_group(nbr, pl.nbc, lanes);
-    const uint32_t rule_lanes = rate <= 16 ? 1024u : 768u; // the rule's lanes decide what is refused
-    const uint32_t by_rule = rule_slabs(nbr, pl.nbc, rule_lanes, patch_group(nbr, pl.nbc, rule_lanes));
+    const uint32_t by_rule = rule_slabs(nbr, pl.nbc, rule_lanes(rate), patch_group(nbr, pl.nbc, rule_lanes(rate)));
     pl.uncapturable = by_rule > 1;
     const uint64_t blocks = (uint64_t)nbr * pl.nbc;
     const uint32_t per_cu = rate > 24 ? 1u : 2u; // workgroups (gemv_wg_lanes)
@@ -222,14 +222,14 @@ GemvPlan whz_gemv_plan(uint32_t rate, uint32_t rows, uint32_t cols, uint32_t row
         lg = 2;
         while ((1u << lg) < tune->lanes && lg < max_lg)
             ++lg;
-    } else if (!(tune && (tune->rows || tune->slabs)) && blocks <= (1ull << 27) && fits_scratch(by_rule, nbr)) {
+    } else if (!(tune && (tune->rows || tune->slabs)) && blocks <= (1ull << 27) && fits_partials(by_rule, nbr, most)) {
         // (the choice below keeps to plans that fit where the rule's does, so
         // wh_gemv_noalloc takes and refuses the calls that it would with it)
         double best = 1e300;
         if (pl.uncapturable) {
             for (uint32_t it = 1; it <= 16; ++it) {
                 const uint32_t nslab = ceil_div(pl.nbc, ((uint64_t)it) << lg);
-                if (!fits_scratch(nslab, nbr))
+                if (!fits_partials(nslab, nbr, most))
                     continue;
                 const double cost = gemv_shape_cost(ceil_div(nbr, lanes >> lg) * nslab, it, resident) +
                                     (nslab > 1 ? kSlabReduceCost : 0.0);
@@ -259,7 +259,7 @@ GemvPlan whz_gemv_plan(uint32_t rate, uint32_t rows, uint32_t cols, uint32_t row
     pl.ntiles = ceil_div(nbr, (uint64_t)(lanes >> lg) * rpg);
     const uint32_t G = 1u << lg;
     uint32_t nslab = per_lane              ? ceil_div(pl.nbc, (uint64_t)G * per_lane)
-                     : tune && tune->lanes ? split_slabs(blocks, pl.nbc, rule_lanes, G)
+                     : tune && tune->lanes ? split_slabs(blocks, pl.nbc, rule_lanes(rate), G)
                                            : by_rule;
     if (tune && tune->slabs)
         nslab = tune->slabs;
@@ -318,44 +318,68 @@ double mrhs_shape_cost(uint32_t nslab, uint32_t ntiles, uint32_t steps, uint64_t
     return 0.4 * rounds + 0.6 * even + (nslab > 1 ? 0.2 + (double)nslab * (double)per_slab * 8.0 / 21e6 : 0.0);
 }
 
+namespace {
+
+// The rows, columns and contraction of a multi-RHS plan; its slabs are to be set.
+MrhsPlan mrhs_range_plan(uint32_t cols, uint32_t row_begin, uint32_t row_end, uint32_t k, bool bf16,
+                         const GemvTuning* tune)
+{
+    MrhsPlan pl = range_plan(cols, row_begin, row_end);
+    pl.math = (uint32_t)mrhs_math(k, bf16, tune && tune->mrhs_fp32);
+    return pl;
+}
+
+uint32_t mrhs_tiles(uint32_t nbr, uint32_t waves) { return ceil_div(nbr, 4 * waves); }
+
+// The FP64 partials (slabs x k x rows) stay within 256 MiB: 8 slabs of up to
+// 64 right-hand sides over 65536 rows (at k = 64, 8 slabs take 7.27 ms where 2
+// took 7.60); short row ranges (few tiles, which need the slabs to fill the
+// device) keep theirs.
+uint32_t mrhs_slab_cap(uint64_t per_slab)
+{
+    return (uint32_t)std::max<uint64_t>(1, (32ull << 20) / std::max<uint64_t>(per_slab, 1));
+}
+
+// Slabs by a fixed rule: about two rounds of workgroups in a multiple of 8
+// slabs (65536^2 with up to 16 right-hand sides: 8 slabs 5.4 ms where 3 take
+// 6.2).
+uint32_t mrhs_rule_slabs(uint32_t ntiles, uint32_t steps, uint32_t cap, uint32_t resident)
+{
+    uint32_t nslab = ntiles ? ceil_div(2 * (uint64_t)resident, ntiles) : 1;
+    if (steps >= 8)
+        nslab = (nslab + 7) / 8 * 8;
+    return std::max(1u, std::min(std::min(nslab, cap), steps));
+}
+
+} // namespace
+
 MrhsPlan whz_mrhs_plan(uint32_t rate, uint32_t rows, uint32_t cols, uint32_t row_begin, uint32_t row_end,
-                       int num_cus, uint32_t k, bool bf16, const GemvTuning* tune)
+                       int num_cus, uint32_t k, bool bf16, const GemvTuning* tune, size_t most_workspace)
 {
     (void)rows;
     const uint32_t slabs = tune ? tune->mrhs_slabs : 0;
-    MrhsPlan pl{};
-    const MrhsMath math = mrhs_math(k, bf16, tune && tune->mrhs_fp32);
-    pl.math = (uint32_t)math;
-    pl.nbc = (cols + 3) / 4;
-    pl.bi_begin = row_begin / 4;
-    pl.bi_end = (row_end + 3) / 4;
-    pl.cols = cols;
-    pl.nrows = row_end - row_begin;
+    MrhsPlan pl = mrhs_range_plan(cols, row_begin, row_end, k, bf16, tune);
     const uint32_t nbr = pl.bi_end - pl.bi_begin;
-    const uint32_t tile_rows = 4u * (uint32_t)mrhs_waves((int)((k + 15) / 16), (int)rate / 2);
-    pl.ntiles = (nbr + tile_rows - 1) / tile_rows;
-    // the FP64 partials (slabs x k x rows) stay within 256 MiB: 8 slabs of up
-    // to 64 right-hand sides over 65536 rows (at k = 64, 8 slabs take 7.27 ms
-    // where 2 took 7.60); short row ranges (few tiles, which need the slabs to
-    // fill the device) keep theirs
+    pl.ntiles = mrhs_tiles(nbr, (uint32_t)mrhs_waves((int)((k + 15) / 16), (int)rate / 2));
     const uint64_t per_slab = (uint64_t)std::max<uint32_t>(k, 1) * nbr * 4;
-    const uint32_t cap = (uint32_t)std::max<uint64_t>(1, (32ull << 20) / std::max<uint64_t>(per_slab, 1));
+    const uint32_t cap = mrhs_slab_cap(per_slab);
     const uint32_t steps = (pl.nbc + 15) / 16, resident = 2u * (num_cus > 0 ? (uint32_t)num_cus : 256u);
-    // about two rounds of workgroups in a multiple of 8 slabs (65536^2 with up
-    // to 16 right-hand sides: 8 slabs 5.4 ms where 3 take 6.2), unless the cost
-    // above says that another count is 2 % better.  From sweeps over 22 shapes
-    // (us, this count and the chosen one): 48573 x 660 BF16 with 42 vectors 81 /
-    // 58, 4096^2 with 64 67 / 55, 30000 x 700 with 20 59 / 51, 300 x 40000 at
-    // rate 16 with 12 58 / 49, 1500 x 20000 BF16 with 64 76 / 65; none slower
-    uint32_t nslab = pl.ntiles ? ceil_div(2 * (uint64_t)resident, pl.ntiles) : 1;
-    if (steps >= 8)
-        nslab = (nslab + 7) / 8 * 8;
-    nslab = std::max(1u, std::min(std::min(nslab, cap), steps));
+    const auto fits = [&](uint32_t n) {
+        MrhsPlan p = pl;
+        set_slabs(p, n, 16);
+        return mrhs_workspace(p, k).total <= most_workspace;
+    };
+    // the rule's count, unless the cost above says that another one is 2 %
+    // better.  From sweeps over 22 shapes (us, the rule's count and the chosen
+    // one): 48573 x 660 BF16 with 42 vectors 81 / 58, 4096^2 with 64 67 / 55,
+    // 30000 x 700 with 20 59 / 51, 300 x 40000 at rate 16 with 12 58 / 49,
+    // 1500 x 20000 BF16 with 64 76 / 65; none slower
+    uint32_t nslab = mrhs_rule_slabs(pl.ntiles, steps, cap, resident);
     const auto cost_of = [&](uint32_t n) { return mrhs_shape_cost(n, pl.ntiles, steps, per_slab, resident); };
-    double best = 0.98 * cost_of(nslab);
+    double best = fits(nslab) ? 0.98 * cost_of(nslab) : 1e300;
     for (uint32_t it = 1; it < steps; it += std::max(1u, it / 16)) { // steps a slab
         const uint32_t n = ceil_div(steps, it);
-        if (n <= cap && cost_of(n) < best) {
+        if (n <= cap && cost_of(n) < best && fits(n)) {
             best = cost_of(n);
             nslab = n;
         }
@@ -366,13 +390,28 @@ MrhsPlan whz_mrhs_plan(uint32_t rate, uint32_t rows, uint32_t cols, uint32_t row
         nslab = slabs;
     if (nslab > steps)
         nslab = steps ? steps : 1;
-    uint32_t slab_bc = (pl.nbc + nslab - 1) / nslab;
-    slab_bc = (slab_bc + 15) / 16 * 16;
-    pl.slab_bc = slab_bc ? slab_bc : 16;
-    pl.nslab = (pl.nbc + pl.slab_bc - 1) / pl.slab_bc;
-    if (pl.nslab < 1)
-        pl.nslab = 1;
+    set_slabs(pl, nslab, 16);
     return pl;
+}
+
+size_t whz_serve_workspace(uint32_t rate, uint32_t cols, uint32_t row_begin, uint32_t row_end, int num_cus,
+                           const GemvTuning* tune)
+{
+    const GemvPlan one = range_plan(cols, row_begin, row_end);
+    const uint32_t nbr = one.bi_end - one.bi_begin, lanes = rule_lanes(rate);
+    const uint32_t by_rule = rule_slabs(nbr, one.nbc, lanes, patch_group(nbr, one.nbc, lanes));
+    size_t most = by_rule > 1 ? (size_t)by_rule * one.part_rows() : 0;
+    const uint32_t steps = (one.nbc + 15) / 16, resident = 2u * (num_cus > 0 ? (uint32_t)num_cus : 256u);
+    for (uint32_t k = 16; k <= kMaxRhs; k += 16) {
+        MrhsPlan pl = mrhs_range_plan(cols, row_begin, row_end, k, false, tune);
+        const uint32_t cap = mrhs_slab_cap((uint64_t)k * nbr * 4);
+        uint32_t nslab = mrhs_rule_slabs(mrhs_tiles(nbr, k <= 16 ? 16 : 8), steps, cap, resident);
+        if (tune && tune->mrhs_slabs)
+            nslab = std::max(1u, std::min(tune->mrhs_slabs, steps));
+        set_slabs(pl, nslab, 16);
+        most = std::max(most, mrhs_workspace(pl, k).total);
+    }
+    return most;
 }
 
 hipError_t whz_mrhs(uint32_t rate, const MrhsPlan& pl, const void* stream, const void* U, uint32_t ldu, uint32_t k,

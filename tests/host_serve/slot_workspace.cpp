@@ -73,7 +73,7 @@ int main(int argc, char** argv)
         const size_t have = serve_workspace(d, chunks, kCus, none);
         for (const auto& c : chunks)
             for (uint32_t k : policy::kBuckets) {
-                const size_t need = serve_plan(d, c, k, kCus, none).workspace;
+                const size_t need = serve_plan(d, c, k, kCus, none, have).workspace;
                 if (need <= have)
                     continue;
                 if (bad++ < 5)

@@ -39,3 +39,22 @@ def test_every_bucket_fits_the_slot(slots, seed, most_rows, most_values):
     r = subprocess.run([slots, "fit", str(seed), "20000", str(most_rows), str(most_values)], capture_output=True,
                        text=True, env={**os.environ, "ASAN_OPTIONS": "detect_leaks=0"}, timeout=120)
     assert r.returncode == 0, f"exit {r.returncode}:\n{r.stderr[-2000:]}"
+
+
+# (rate, rows, columns, values a chunk): bytes, from the rules for 1 (lanes of
+# the rate), 16 (16 waves) and 32, 48 and 64 (8 waves) right-hand sides: about
+# two rounds of workgroups in a multiple of 8 slabs, within 256 MiB.  A slot's
+# bytes decide what a budget admits, so they do not follow the planners' costs
+# (which would double the first one).
+SIZES = {(24, 18237, 28044, 1 << 28): 85499904, (8, 40000, 256, 1 << 28): 82018304,
+         (16, 43412, 168, 1 << 28): 66754560, (8, 1024, 1024, 1 << 28): 8781824,
+         (8, 65536, 65536, 1 << 28): 92274688, (32, 2048, 1024, 69632): 950272,
+         (4, 8981, 58363, 1 << 28): 96010240}
+
+
+@pytest.mark.parametrize("shape", list(SIZES))
+def test_slot_size(slots, shape):
+    r = subprocess.run([slots, "size", *map(str, shape)], capture_output=True, text=True,
+                       env={**os.environ, "ASAN_OPTIONS": "detect_leaks=0"}, timeout=60)
+    assert r.returncode == 0, r.stderr
+    assert int(r.stdout) == SIZES[shape]
