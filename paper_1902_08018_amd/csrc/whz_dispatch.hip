@@ -152,17 +152,34 @@ uint32_t patch_group(uint32_t nbr, uint32_t nbc, uint32_t lanes)
     }
 }
 
+// log2 of the groups a WH_GEMV_LANES value asks for.
+uint32_t group_of(uint32_t group_lanes, uint32_t lanes)
+{
+    uint32_t lg = 2;
+    while ((1u << lg) < group_lanes && lg < gemv_max_lg(lanes))
+        ++lg;
+    return lg;
+}
+
 // The workgroup lanes that rule counts with.
 uint32_t rule_lanes(uint32_t rate) { return rate <= 16 ? 1024u : 768u; }
 
-// The slabs that rule gives groups of 2^lg lanes.  Where it splits the
-// columns, calls use the context's workspace and are not captured into graphs,
-// whatever the plan's own slabs are; where it does not, the plan has one slab.
-uint32_t rule_slabs(uint32_t nbr, uint32_t nbc, uint32_t lanes, uint32_t lg)
+// The slabs that rule gives, under launch-shape overrides (`tune` may be null)
+// the ones they ask for.  Where it splits the columns, calls use the context's
+// workspace and are not captured into graphs, whatever the plan's own slabs
+// are; where it does not, the plan has one slab.
+uint32_t rule_slabs(uint32_t rate, uint32_t nbr, uint32_t nbc, const GemvTuning* tune)
 {
+    const uint32_t lanes = rule_lanes(rate);
+    uint32_t lg = patch_group(nbr, nbc, lanes);
+    if (tune && tune->lanes)
+        lg = group_of(tune->lanes, lanes);
+    uint32_t nslab = split_slabs((uint64_t)nbr * nbc, nbc, lanes, 1u << lg);
+    if (tune && tune->slabs)
+        nslab = std::min(tune->slabs, ceil_div(nbc, 1u << lg));
     GemvPlan pl{};
     pl.nbc = nbc;
-    return set_slabs(pl, split_slabs((uint64_t)nbr * nbc, nbc, lanes, 1u << lg), 1u << lg);
+    return set_slabs(pl, nslab, 1u << lg);
 }
 
 // Whether a plan's partial sums fit `most` doubles.
@@ -212,16 +229,14 @@ GemvPlan whz_gemv_plan(uint32_t rate, uint32_t rows, uint32_t cols, uint32_t row
     pl.lanes = lanes;
     const uint32_t nbr = pl.bi_end - pl.bi_begin;
     uint32_t lg = patch_group(nbr, pl.nbc, lanes);
-    const uint32_t by_rule = rule_slabs(nbr, pl.nbc, rule_lanes(rate), patch_group(nbr, pl.nbc, rule_lanes(rate)));
-    pl.uncapturable = by_rule > 1;
+    const uint32_t by_rule = rule_slabs(rate, nbr, pl.nbc, nullptr);
+    pl.uncapturable = rule_slabs(rate, nbr, pl.nbc, tune) > 1;
     const uint64_t blocks = (uint64_t)nbr * pl.nbc;
     const uint32_t per_cu = rate > 24 ? 1u : 2u; // workgroups (gemv_wg_lanes)
     const uint32_t resident = per_cu * (num_cus > 0 ? (uint32_t)num_cus : 256u);
     uint32_t rpg = 1, per_lane = 0; // blocks a lane and row; 0: not chosen yet
     if (tune && tune->lanes) {
-        lg = 2;
-        while ((1u << lg) < tune->lanes && lg < max_lg)
-            ++lg;
+        lg = group_of(tune->lanes, lanes);
     } else if (!(tune && (tune->rows || tune->slabs)) && blocks <= (1ull << 27) && fits_partials(by_rule, nbr, most)) {
         // (the choice below keeps to plans that fit where the rule's does, so
         // wh_gemv_noalloc takes and refuses the calls that it would with it)
@@ -398,8 +413,8 @@ size_t whz_serve_workspace(uint32_t rate, uint32_t cols, uint32_t row_begin, uin
                            const GemvTuning* tune)
 {
     const GemvPlan one = range_plan(cols, row_begin, row_end);
-    const uint32_t nbr = one.bi_end - one.bi_begin, lanes = rule_lanes(rate);
-    const uint32_t by_rule = rule_slabs(nbr, one.nbc, lanes, patch_group(nbr, one.nbc, lanes));
+    const uint32_t nbr = one.bi_end - one.bi_begin;
+    const uint32_t by_rule = rule_slabs(rate, nbr, one.nbc, nullptr);
     size_t most = by_rule > 1 ? (size_t)by_rule * one.part_rows() : 0;
     const uint32_t steps = (one.nbc + 15) / 16, resident = 2u * (num_cus > 0 ? (uint32_t)num_cus : 256u);
     for (uint32_t k = 16; k <= kMaxRhs; k += 16) {

@@ -7,7 +7,7 @@
 //            prints the shapes that fall short, exit status 3 if any
 //        slot_workspace size <rate> <rows> <cols> <chunk values>
 //            prints the workspace in bytes
-#include "whz_dispatch.hip"
+#include "planner.hpp"
 
 #include <cmath>
 #include <cstdio>
@@ -16,26 +16,6 @@
 #include <random>
 
 #include "serve_plan.hpp"
-
-namespace wh {
-#define X(k)                                                                                                         \
-    namespace nw##k {                                                                                                \
-    hipError_t decode_blocks(const void*, uint64_t, uint64_t, float*, hipStream_t) { return hipErrorUnknown; }       \
-    hipError_t decode_matrix(const void*, uint32_t, uint32_t, float*, hipStream_t) { return hipErrorUnknown; }       \
-    hipError_t encode(const float*, uint32_t, uint32_t, void*, uint32_t*, hipStream_t) { return hipErrorUnknown; }   \
-    hipError_t gemv(const GemvPlan&, AccMode, const void*, const float*, float*, double*, hipStream_t)               \
-    {                                                                                                                \
-        return hipErrorUnknown;                                                                                      \
-    }                                                                                                                \
-    hipError_t mrhs(const MrhsPlan&, const void*, const void*, uint32_t, uint32_t, float*, uint32_t, double*,        \
-                    hipStream_t)                                                                                     \
-    {                                                                                                                \
-        return hipErrorUnknown;                                                                                      \
-    }                                                                                                                \
-    }
-WH_FOR_EACH_NW(X)
-#undef X
-} // namespace wh
 
 using namespace wh;
 

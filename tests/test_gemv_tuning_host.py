@@ -1,0 +1,53 @@
+"""The fused GEMV's planner with launch-shape overrides (WH_GEMV_LANES,
+WH_GEMV_ROWS, WH_GEMV_SLABS), run on the host: tests/host_serve/gemv_plan.cpp.
+
+  capture   a call is kept out of graph capture where the overridden shape
+            splits the columns: forced to one slab it uses no workspace
+"""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+SRC = os.path.join(HERE, "host_serve", "gemv_plan.cpp")
+INC = os.path.join(os.path.dirname(HERE), "paper_1902_08018_amd", "csrc")
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    gxx = shutil.which("g++")
+    if not gxx:
+        pytest.skip("g++ not found")
+    out = str(tmp_path_factory.mktemp("plan") / "gemv_plan")
+    r = subprocess.run([gxx, "-std=c++17", "-O1", "-w", "-D__HIP_PLATFORM_AMD__", "-I", "/opt/rocm/include", "-I", INC,
+                        SRC, "-o", out], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+
+    def run(rate, rows, cols, lanes=0, rpg=0, slabs=0):
+        r = subprocess.run([out, *map(str, (rate, rows, cols, lanes, rpg, slabs))], capture_output=True, text=True)
+        assert r.returncode == 0
+        return dict(zip(("lanes", "rpg", "nslab", "slab_bc", "uncapturable"), map(int, r.stdout.split())))
+
+    return run
+
+
+@pytest.mark.parametrize("rate", [8, 16, 24, 32])
+@pytest.mark.parametrize("rows,cols", [(512, 8192), (256, 1024), (4096, 4096), (61, 100)])
+def test_capture_follows_the_forced_slabs(plan, rate, rows, cols):
+    assert plan(rate, rows, cols, slabs=1)["uncapturable"] == 0
+    for lanes in (4, 32, 256):
+        p = plan(rate, rows, cols, lanes=lanes)
+        assert p["uncapturable"] == (p["nslab"] > 1), (lanes, p)
+        assert plan(rate, rows, cols, lanes=lanes, slabs=1)["uncapturable"] == 0
+    p = plan(rate, rows, cols, slabs=3)
+    assert p["uncapturable"] == (p["nslab"] > 1)
+
+
+def test_capture_without_overrides(plan):
+    # one slab by cost, but several by the rule that decides: refused as before
+    p = plan(16, 256, 1024)
+    assert p["nslab"] == 1 and p["uncapturable"] == 1
+    p = plan(8, 61, 100)  # 25 block columns: one slab by the rule too
+    assert p["nslab"] == 1 and p["uncapturable"] == 0

@@ -1,0 +1,71 @@
+"""Graph capture of the fused GEMV whose plan has one column slab.
+
+  forced    WH_GEMV_SLABS=1 keeps the call from the context's workspace: it is
+            captured, and every replay equals the eager call
+  by cost   256 x 1024 has one slab by the planner's cost but several by the
+            rule that decides about capture: wh_gemv refuses, wh_gemv_noalloc
+            is captured
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_1902_08018_amd import synth, wh
+
+pytestmark = pytest.mark.gpu
+
+
+def replays_equal_eager(ctx, call, rows, cols):
+    u, y = torch.empty(cols, device="cuda"), torch.empty(rows, device="cuda")
+    us = [torch.from_numpy(synth.uniform(cols, seed=s)).cuda() for s in (1, 2, 3)]
+    u.copy_(us[0])
+    call(u, y)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        call(u, y)
+    for rep in range(6):
+        u.copy_(us[rep % 3])
+        g.replay()
+        torch.cuda.synchronize()
+        got = y.cpu().numpy().copy()
+        eager = torch.empty_like(y)
+        call(u, eager)
+        torch.cuda.synchronize()
+        assert np.array_equal(got.view(np.uint32), eager.cpu().numpy().view(np.uint32)), rep
+
+
+@pytest.mark.parametrize("rows,cols,rate", [(512, 8192, 8), (256, 1024, 16)])
+def test_one_forced_slab_is_captured(monkeypatch, rows, cols, rate):
+    monkeypatch.setenv("WH_GEMV_SLABS", "1")
+    ctx = wh.wh_create(0, 0)
+    try:
+        s = oracle.encode(synth.matrix(synth.MatrixSpec(rows, cols, 32, 8.0, seed=81)), rate)
+        mat = wh.wh_load_compressed(ctx, rows, cols, wh.WH_FMT_ZFP_FIXED_RATE, rate, s)
+        h = torch.empty(s.size, dtype=torch.uint8, pin_memory=True)
+        h.copy_(torch.from_numpy(s))
+        replays_equal_eager(ctx, lambda u, y: wh.wh_gemv(ctx, mat, u, y, 0, rows), rows, cols)
+        replays_equal_eager(ctx, lambda u, y: wh.wh_gemv_host(ctx, h, rows, cols, rate, u, y,
+                                                              flags=wh.WH_HOST_DIRECT), rows, cols)
+    finally:
+        wh.wh_destroy(ctx)
+
+
+def test_one_slab_by_cost(gpu_ctx):
+    rows, cols, rate = 256, 1024, 16
+    assert wh.wh_gemv_plan_info(rows, cols, 0, rows, rate=rate)["nslab"] == 1
+    s = oracle.encode(synth.matrix(synth.MatrixSpec(rows, cols, 32, 8.0, seed=82)), rate)
+    mat = wh.wh_load_compressed(gpu_ctx, rows, cols, wh.WH_FMT_ZFP_FIXED_RATE, rate, s)
+    replays_equal_eager(gpu_ctx, lambda u, y: wh.wh_gemv_noalloc(gpu_ctx, mat, u, y, 0, rows), rows, cols)
+    u, y = torch.ones(cols, device="cuda"), torch.empty(rows, device="cuda")
+    refused = None
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        try:
+            wh.wh_gemv(gpu_ctx, mat, u, y, 0, rows)
+        except wh.WhError as e:
+            refused = e.status
+        y.zero_()
+    assert refused == wh.WH_ERR_INVALID
+    wh.wh_unload(gpu_ctx, mat)
