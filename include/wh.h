@@ -118,7 +118,11 @@ const char *wh_status_str(wh_status st);
 
 /* Create a context on HIP device `hip_device`.  `hbm_budget_bytes` bounds
  * the device memory the serving loop may hold for request buffers (0 = 1 GiB
- * default).  No GPU / bad device -> WH_ERR_DEVICE.  The environment
+ * default).  No GPU / bad device -> WH_ERR_DEVICE.  The call allocates 4 MiB
+ * of device memory for the context's workspace (see wh_gemv), held until
+ * wh_destroy beside any larger block a later call needs; where that fails,
+ * the first call that needs a workspace allocates it.  It may be made while a
+ * stream is being captured into a graph.  The environment
  * variables WH_GEMV_LANES (4, 8, ..., 512 lanes per block row),
  * WH_GEMV_ROWS (1, 2 or 4 block rows per lane group) and WH_GEMV_SLABS
  * (column slabs), read here, fix the compressed GEMV's launch shape instead

@@ -246,15 +246,22 @@ wh_status wh_create(int hip_device, uint64_t hbm_budget_bytes, wh_ctx** out)
             return WH_ERR_DEVICE;
         }
         // the slab partials of calls up to about 10^8 matrix values, so that a
-        // context's first such call does not wait for an allocation (80 us);
-        // without it the first call allocates
-        if (hipMalloc(reinterpret_cast<void**>(&ctx->part_start), kPartialsAtStart * sizeof(double)) == hipSuccess) {
+        // context's first such call does not wait for an allocation (80 us,
+        // paid here instead); without it the first call allocates.  Relaxed
+        // for this thread: under a capture in global mode, on whatever stream
+        // and thread, an allocation would end that capture
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+        if (relaxed &&
+            hipMalloc(reinterpret_cast<void**>(&ctx->part_start), kPartialsAtStart * sizeof(double)) == hipSuccess) {
             ctx->part = ctx->part_start;
             ctx->part_cap = kPartialsAtStart;
         } else {
             (void)hipGetLastError();
             ctx->part_start = nullptr;
         }
+        if (relaxed)
+            (void)hipThreadExchangeStreamCaptureMode(&mode);
         // the host pipeline's copy stream is created on its first use: a
         // stream holds a hardware queue (HIP maps streams onto a few queues
         // round-robin), and most contexts never stream from the host

@@ -5,7 +5,11 @@
   by cost   256 x 1024 has one slab by the planner's cost but several by the
             rule that decides about capture: wh_gemv refuses, wh_gemv_noalloc
             is captured
+
+A context can be made while a capture is under way, on this thread or another.
 """
+import threading
+
 import numpy as np
 import pytest
 import torch
@@ -69,3 +73,38 @@ def test_one_slab_by_cost(gpu_ctx):
         y.zero_()
     assert refused == wh.WH_ERR_INVALID
     wh.wh_unload(gpu_ctx, mat)
+
+
+@pytest.mark.parametrize("other_thread", [False, True])
+def test_create_during_a_capture(gpu_ctx, other_thread):
+    x = torch.zeros(1000, device="cuda")
+    made = []
+
+    def create():
+        made.append(wh.wh_create(0, 0))
+
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        x.add_(1.0)
+        if other_thread:
+            t = threading.Thread(target=create)
+            t.start()
+            t.join()
+        else:
+            create()
+        x.add_(1.0)
+    for rep in range(4):
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.all(x == 2.0 * (rep + 1))
+    # the context's workspace is usable: a product that splits its columns
+    rows, cols, rate = 512, 8192, 8
+    s = oracle.encode(synth.matrix(synth.MatrixSpec(rows, cols, 32, 8.0, seed=83)), rate)
+    mat = wh.wh_load_compressed(made[0], rows, cols, wh.WH_FMT_ZFP_FIXED_RATE, rate, s)
+    u = synth.uniform(cols, seed=84)
+    y = torch.empty(rows, device="cuda")
+    wh.wh_gemv(made[0], mat, torch.from_numpy(u).cuda(), y, 0, rows)
+    torch.cuda.synchronize()
+    ref = oracle.gemv_fp64(s, rows, cols, rate, u)
+    assert np.linalg.norm(y.cpu().numpy() - ref) <= 1e-6 * np.linalg.norm(ref)
+    wh.wh_destroy(made[0])
