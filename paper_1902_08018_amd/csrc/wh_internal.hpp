@@ -26,8 +26,10 @@ constexpr uint32_t kGemvLanes = 512;
 constexpr uint32_t gemv_wg_lanes(uint32_t rate) { return rate <= 16 || rate > 24 ? 1024u : 768u; }
 // LDS of one workgroup when two share a CU
 constexpr uint32_t kLdsPerWorkgroupOfTwo = 160u * 1024u / 2u;
-// from 14 bits/value the row sums share the staging rows: one tile row
-constexpr bool gemv_one_tile_row(uint32_t rate) { return rate >= 14 && rate <= 16; }
+// Rates whose row sums share the staging rows, which needs one tile row: from
+// 14 bits/value, but for 20, whose 768-lane workgroups have just the room
+// (the kernels check this against their LDS).
+constexpr bool gemv_one_tile_row(uint32_t rate) { return rate >= 14 && rate != 20; }
 constexpr uint32_t gemv_max_lg(uint32_t lanes) { return lanes == 768u ? 8u : 9u; }
 constexpr int kGemvMaxRowsPerGroup = 4;
 constexpr uint32_t gemv_slots(uint32_t lg, uint32_t lanes) { return lg >= 6 ? lanes / 64 : lanes >> lg; }

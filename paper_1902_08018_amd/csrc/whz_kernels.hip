@@ -450,10 +450,10 @@ constexpr uint32_t kSlabVectors = NW >= 10 ? 64 : (NW == 6 || NW == 8 ? 128 : 38
 // what LDS holds beside a workgroup's staging rows
 template <int NW>
 constexpr int kGemvTables = kSecEntries * 4 + (int)kSlabVectors<NW> * 16 * (kCanCut<NW> ? 2 : 1);
-// From 14 bits/value a 1024-lane workgroup's staging rows and tables leave no
-// room for its own row-sum doubles within two workgroups' LDS; the sums then
-// go over the staging rows once every wave has decoded its blocks, which
-// needs one tile row per group (the planner's choice there).
+// Where a workgroup's staging rows and tables leave no room for its own row-sum
+// doubles within half a CU's LDS (which at rate 32, one workgroup a CU, they
+// exceed by themselves), the sums go over the staging rows once every wave has
+// decoded its blocks, which needs one tile row per group.
 template <int NW>
 constexpr bool kGemvSumsInStaging =
     kGemvThreads<NW> * (kStagedWords<NW> * 4 + 8) + kGemvTables<NW> > kLdsPerWorkgroupOfTwo;
@@ -468,6 +468,7 @@ __global__ void __launch_bounds__(kGemvThreads<NW>, kGemvMinWaves<NW>) gemv_kern
 {
     constexpr int THREADS = kGemvThreads<NW>, STRIDE = kStageStride<THREADS>;
     constexpr bool kShared = kGemvSumsInStaging<NW>;
+    static_assert(kShared == gemv_one_tile_row(2 * NW), "the planner's tile rows");
     __shared__ __align__(16) uint32_t lds[THREADS * kStagedWords<NW>];
     __shared__ __align__(16) uint32_t tab[kSecEntries];
     // the slab's B^T u (and u, for blocks that need the exact lift), or u for
@@ -1345,7 +1346,7 @@ hipError_t launch_gemv_t(const GemvPlan& pl, const uint32_t* s, const float* u, 
 {
     if (pl.lanes != (uint32_t)kGemvThreads<NW>) // a plan made for another rate
         return hipErrorInvalidValue;
-    if (kGemvSumsInStaging<NW> && pl.rpg != 1) // the row sums over the staging rows hold one tile row
+    if (gemv_one_tile_row(2 * NW) && pl.rpg != 1) // the row sums over the staging rows hold one tile row
         return hipErrorInvalidValue;
     hipLaunchKernelGGL((gemv_kernel<NW, Acc>), dim3(pl.ntiles * pl.nslab), dim3(kGemvThreads<NW>), 0, st, s, u, y,
                        part, pl.nbc, pl.bi_begin, pl.bi_end, pl.slab_bc, pl.nslab, pl.cols, pl.nrows, pl.lg, pl.rpg,

@@ -3,6 +3,8 @@ WH_GEMV_ROWS, WH_GEMV_SLABS), run on the host: tests/host_serve/gemv_plan.cpp.
 
   capture   a call is kept out of graph capture where the overridden shape
             splits the columns: forced to one slab it uses no workspace
+  rows      block rows per group are taken where the workgroup's LDS holds
+            their sums, and else left at one (a plan with more is no launch)
 """
 import os
 import shutil
@@ -51,3 +53,11 @@ def test_capture_without_overrides(plan):
     assert p["nslab"] == 1 and p["uncapturable"] == 1
     p = plan(8, 61, 100)  # 25 block columns: one slab by the rule too
     assert p["nslab"] == 1 and p["uncapturable"] == 0
+
+
+@pytest.mark.parametrize("rate", [2, 4, 6, 8, 10, 12, 14, 16, 20, 24, 32])
+@pytest.mark.parametrize("rpg", [2, 4])
+def test_rows_per_group(plan, rate, rpg):
+    # the rates whose staged blocks and tables leave room for the sums in half a CU's LDS
+    taken = rpg if rate <= 12 or rate == 20 else 1
+    assert plan(rate, 4096, 4096, lanes=64, rpg=rpg)["rpg"] == taken
