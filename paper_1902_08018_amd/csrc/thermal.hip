@@ -17,7 +17,12 @@
 namespace wh {
 namespace {
 
-constexpr int kThermalThreads = 512;
+// Lanes of a workgroup: 512 where that gives every CU one, else 64.  A small
+// system's time is that of its gathers in the CUs that have some, so it is
+// spread over as many as there are.  us a step, 64 / 256 / 512 lanes: 5,000
+// rows of 7 entries 2.9 / 3.7 / 4.4 (rows of 27 4.3 / 6.9 / 11.6), 60,000 of 5
+// 3.0 / 3.4 / 3.6, 100,000 of 5 3.7 / 3.8 / 3.7, 131,072 of 5 3.9 / 4.0 / 3.7.
+constexpr unsigned kThermalThreads = 512, kThermalThreadsSmall = 64;
 // entries of a row read together: the rows of a two-dimensional mesh have five
 constexpr int kThermalBatch = 5;
 
@@ -38,8 +43,8 @@ __global__ void __launch_bounds__(kThermalThreads) thermal_step_kernel(
     const float* __restrict__ val, const float* __restrict__ b, const float* __restrict__ T,
     const float* __restrict__ u, float* __restrict__ T_next)
 {
-    const uint64_t stride = (uint64_t)gridDim.x * kThermalThreads;
-    for (uint64_t i = (uint64_t)blockIdx.x * kThermalThreads + threadIdx.x; i < n; i += stride) {
+    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
         // entries outside [0, nnz) and columns outside [0, n) are skipped: a
         // malformed matrix gives wrong values, never a stray access
         const uint32_t p0 = row_ptr[i] < nnz ? row_ptr[i] : nnz;
@@ -74,10 +79,15 @@ __global__ void __launch_bounds__(kThermalThreads) thermal_step_kernel(
     }
 }
 
-unsigned thermal_grid(uint32_t n)
+struct ThermalGrid {
+    unsigned groups, threads;
+};
+
+ThermalGrid thermal_grid(uint32_t n, int num_cus)
 {
-    const uint64_t g = ((uint64_t)n + kThermalThreads - 1) / kThermalThreads;
-    return (unsigned)(g < (1u << 20) ? (g ? g : 1) : (1u << 20));
+    const unsigned threads = (uint64_t)n < (uint64_t)kThermalThreads * num_cus ? kThermalThreadsSmall : kThermalThreads;
+    const uint64_t g = ((uint64_t)n + threads - 1) / threads;
+    return ThermalGrid{(unsigned)(g < (1u << 20) ? (g ? g : 1) : (1u << 20)), threads};
 }
 
 } // namespace
@@ -96,7 +106,8 @@ extern "C" wh_status wh_thermal_step(wh_ctx* ctx, uint32_t n, uint32_t nnz, cons
         return WH_ERR_INVALID; // every row reads its neighbours' old values
     if (n == 0)
         return WH_OK;
-    hipLaunchKernelGGL(thermal_step_kernel, dim3(thermal_grid(n)), dim3(kThermalThreads), 0,
+    const ThermalGrid g = thermal_grid(n, ctx->num_cus);
+    hipLaunchKernelGGL(thermal_step_kernel, dim3(g.groups), dim3(g.threads), 0,
                        static_cast<hipStream_t>(stream), n, nnz, d_row_ptr, d_col, d_val, d_b, d_T, d_u, d_T_next);
     return device_error(ctx, hipGetLastError());
 }
@@ -116,8 +127,9 @@ extern "C" wh_status wh_thermal_run(wh_ctx* ctx, uint32_t n, uint32_t nnz, const
     // ping-pong between d_T and d_work; an odd count ends with a copy back
     float* cur = d_T;
     float* nxt = d_work;
+    const ThermalGrid g = thermal_grid(n, ctx->num_cus);
     for (uint32_t k = 0; k < steps; ++k) {
-        hipLaunchKernelGGL(thermal_step_kernel, dim3(thermal_grid(n)), dim3(kThermalThreads), 0, st, n, nnz,
+        hipLaunchKernelGGL(thermal_step_kernel, dim3(g.groups), dim3(g.threads), 0, st, n, nnz,
                            d_row_ptr, d_col, d_val, d_b, cur, d_U + (uint64_t)k * ldu, nxt);
         float* t = cur;
         cur = nxt;
