@@ -217,6 +217,29 @@ double gemv_shape_cost(uint32_t wgs, uint32_t iters, uint32_t resident)
     return std::max(work, longest);
 }
 
+// The same with rounds, where the columns are split: a workgroup's start costs
+// 1.2 blocks (2.4 where a CU holds one workgroup), a last round of at most one
+// workgroup a CU half of a full round (0.6 in workgroups of 12 waves) and less
+// the fewer they are, a fuller last round all of it; a tenth of the time goes as
+// if rounds had no edges.  The cost above alone gave some shapes up to 27 % more
+// time than the rule's slabs take (us, its choice and the rule's: 241 x 45201 at
+// rate 4 28.4 / 22.4, 188 x 54946 at rate 6 25.1 / 20.5, 52783 x 627 at rate 16
+// 52.6 / 44.9).  Where this one says that the rule's are 1 % cheaper they stand:
+// of 576 swept shapes (2^14 to 2^29 values, every rate, smooth and random data)
+// none is then more than 8 % slower than with the rule.  How much blocks of a
+// wave differ is not known here, and a few smooth matrices would do better with
+// the choice (143 x 53955 at rate 14: 25.1 us, the rule's 29.8).
+double gemv_rounds_cost(uint64_t wgs, uint32_t iters, uint32_t lanes, uint32_t num_cus, uint32_t per_cu)
+{
+    const uint64_t resident = (uint64_t)per_cu * num_cus, full = wgs / resident, rest = wgs % resident;
+    const double start = per_cu == 2 ? 1.2 : 2.4, alone = per_cu == 1 ? 1.0 : (lanes == 768u ? 0.6 : 0.5);
+    double last = rest == 0 ? 0.0 : 1.0;
+    if (rest > 0 && rest <= num_cus)
+        last = alone * (full ? 0.75 + 0.25 * (double)rest / num_cus : 1.0);
+    return (0.9 * ((double)full + last) + 0.1 * (double)wgs / (double)resident + 0.4) * (start + iters);
+}
+constexpr double kSlabReduceRounds = 1.7; // the slab partials' price in its unit
+
 } // namespace
 
 GemvPlan whz_gemv_plan(uint32_t rate, uint32_t rows, uint32_t cols, uint32_t row_begin, uint32_t row_end,
@@ -233,7 +256,7 @@ GemvPlan whz_gemv_plan(uint32_t rate, uint32_t rows, uint32_t cols, uint32_t row
     pl.uncapturable = rule_slabs(rate, nbr, pl.nbc, tune) > 1;
     const uint64_t blocks = (uint64_t)nbr * pl.nbc;
     const uint32_t per_cu = rate > 24 ? 1u : 2u; // workgroups (gemv_wg_lanes)
-    const uint32_t resident = per_cu * (num_cus > 0 ? (uint32_t)num_cus : 256u);
+    const uint32_t cus = num_cus > 0 ? (uint32_t)num_cus : 256u, resident = per_cu * cus;
     uint32_t rpg = 1, per_lane = 0; // blocks a lane and row; 0: not chosen yet
     if (tune && tune->lanes) {
         lg = group_of(tune->lanes, lanes);
@@ -265,6 +288,19 @@ GemvPlan whz_gemv_plan(uint32_t rate, uint32_t rows, uint32_t cols, uint32_t row
                 per_lane = it;
                 lg = g;
             }
+        }
+        if (pl.uncapturable && per_lane && lg == patch_lg) {
+            GemvPlan ruled = pl;
+            const uint32_t rule_n =
+                set_slabs(ruled, split_slabs(blocks, pl.nbc, rule_lanes(rate), 1u << lg), 1u << lg);
+            const uint32_t rule_it = ruled.slab_bc >> lg, n = ceil_div(pl.nbc, (uint64_t)per_lane << lg);
+            const uint32_t tiles = ceil_div(nbr, lanes >> lg);
+            const auto rounds = [&](uint32_t nslab, uint32_t it) {
+                return gemv_rounds_cost((uint64_t)tiles * nslab, it, lanes, cus, per_cu) +
+                       (nslab > 1 ? kSlabReduceRounds : 0.0);
+            };
+            if (n > 1 && fits_partials(rule_n, nbr, most) && rounds(rule_n, rule_it) < 0.99 * rounds(n, per_lane))
+                per_lane = rule_it;
         }
     }
     if (tune && tune->rows && gemv_slots(lg, lanes) * 4 * tune->rows <= lanes && !gemv_one_tile_row(rate))

@@ -5,6 +5,8 @@ WH_GEMV_ROWS, WH_GEMV_SLABS), run on the host: tests/host_serve/gemv_plan.cpp.
             splits the columns: forced to one slab it uses no workspace
   rows      block rows per group are taken where the workgroup's LDS holds
             their sums, and else left at one (a plan with more is no launch)
+  slabs     without overrides: the slab counts that were the faster ones where
+            the planner's cost and its fixed rule differ (us of either)
 """
 import os
 import shutil
@@ -61,3 +63,16 @@ def test_rows_per_group(plan, rate, rpg):
     # the rates whose staged blocks and tables leave room for the sums in half a CU's LDS
     taken = rpg if rate <= 12 or rate == 20 else 1
     assert plan(rate, 4096, 4096, lanes=64, rpg=rpg)["rpg"] == taken
+
+
+@pytest.mark.parametrize("rate,rows,cols,nslab", [
+    (4, 241, 45201, 236),    # 22.4; 28.4 with 707 slabs
+    (6, 188, 54946, 72),     # 20.5; 25.1 with 215
+    (16, 52783, 627, 7),     # 44.9; 52.6 with 5
+    (32, 10209, 1848, 20),   # 56.7; 66.7 with 15
+    (16, 4096, 4096, 64),    # 32.1; 38.7 with the rule's 43
+    (8, 10000, 10000, 63),   # 101.5; 108.5 with the rule's 105
+    (32, 26, 135831, 67),    # 26.8; 32.5 with the rule's 23
+])
+def test_slabs_of_cost_and_rule(plan, rate, rows, cols, nslab):
+    assert plan(rate, rows, cols)["nslab"] == nslab
