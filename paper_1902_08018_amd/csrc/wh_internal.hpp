@@ -32,6 +32,9 @@ constexpr uint32_t kLdsPerWorkgroupOfTwo = 160u * 1024u / 2u;
 constexpr bool gemv_one_tile_row(uint32_t rate) { return rate >= 14 && rate != 20; }
 constexpr uint32_t gemv_max_lg(uint32_t lanes) { return lanes == 768u ? 8u : 9u; }
 constexpr int kGemvMaxRowsPerGroup = 4;
+// Block columns whose B^T u a workgroup of the fused GEMV holds in LDS: what
+// its staging rows and tables leave.
+constexpr uint32_t gemv_slab_vectors(uint32_t rate) { return rate >= 20 ? 64u : (rate == 12 || rate == 16 ? 128u : 384u); }
 constexpr uint32_t gemv_slots(uint32_t lg, uint32_t lanes) { return lg >= 6 ? lanes / 64 : lanes >> lg; }
 
 // Launch geometry of the fused GEMV over rows [row_begin, row_end), i.e.

@@ -240,6 +240,10 @@ double gemv_rounds_cost(uint64_t wgs, uint32_t iters, uint32_t lanes, uint32_t n
 }
 constexpr double kSlabReduceRounds = 1.7; // the slab partials' price in its unit
 
+// A slab whose B^T u does not fit a workgroup's LDS makes it at every block:
+// about 5 % (the kernel's kSlabVectors).
+double slab_width_cost(uint64_t slab_bc, uint32_t rate) { return slab_bc > gemv_slab_vectors(rate) ? 1.05 : 1.0; }
+
 } // namespace
 
 GemvPlan whz_gemv_plan(uint32_t rate, uint32_t rows, uint32_t cols, uint32_t row_begin, uint32_t row_end,
@@ -269,7 +273,8 @@ GemvPlan whz_gemv_plan(uint32_t rate, uint32_t rows, uint32_t cols, uint32_t row
                 const uint32_t nslab = ceil_div(pl.nbc, ((uint64_t)it) << lg);
                 if (!fits_partials(nslab, nbr, most))
                     continue;
-                const double cost = gemv_shape_cost(ceil_div(nbr, lanes >> lg) * nslab, it, resident) +
+                const double cost = gemv_shape_cost(ceil_div(nbr, lanes >> lg) * nslab, it, resident) *
+                                        slab_width_cost((uint64_t)it << lg, rate) +
                                     (nslab > 1 ? kSlabReduceCost : 0.0);
                 if (cost < best) {
                     best = cost;
@@ -281,7 +286,12 @@ GemvPlan whz_gemv_plan(uint32_t rate, uint32_t rows, uint32_t cols, uint32_t row
         for (uint32_t g = patch_lg; g <= max_lg; ++g) { // one slab: the group takes whole block rows
             const uint32_t it = ceil_div(pl.nbc, 1u << g);
             if (pl.uncapturable && (g > patch_lg ? it > 1 || g > 8 : it > 16))
-                continue; // wide groups: a block a lane, four waves
+                // A block a lane, four waves: with 256 x 2048 and larger a call
+                // keeps its workspace, which callers and tests of its sharing
+                // count on.  The times cross further out (us, one slab of two
+                // blocks a lane and the plan taken: 4096^2 at rate 16 28.6 /
+                // 32.1, 50818 x 231 at rate 12 22.0 / 26.4)
+                continue;
             const double cost = gemv_shape_cost(ceil_div(nbr, lanes >> g), it, resident) * row_group_cost(g);
             if (cost < best) {
                 best = cost;
@@ -296,7 +306,8 @@ GemvPlan whz_gemv_plan(uint32_t rate, uint32_t rows, uint32_t cols, uint32_t row
             const uint32_t rule_it = ruled.slab_bc >> lg, n = ceil_div(pl.nbc, (uint64_t)per_lane << lg);
             const uint32_t tiles = ceil_div(nbr, lanes >> lg);
             const auto rounds = [&](uint32_t nslab, uint32_t it) {
-                return gemv_rounds_cost((uint64_t)tiles * nslab, it, lanes, cus, per_cu) +
+                return gemv_rounds_cost((uint64_t)tiles * nslab, it, lanes, cus, per_cu) *
+                           slab_width_cost((uint64_t)it << lg, rate) +
                        (nslab > 1 ? kSlabReduceRounds : 0.0);
             };
             if (n > 1 && fits_partials(rule_n, nbr, most) && rounds(rule_n, rule_it) < 0.99 * rounds(n, per_lane))

@@ -10,10 +10,13 @@
 //            row's slab, each lane decoding one 4x4 block per step (its
 //            words staged in LDS), so a wave works on an 8 x 8 patch of
 //            blocks; a tile holds (lanes / 2^lg) x rpg block rows
-//   bound    the decoder's vector instructions: 65536^2 at rate 8 takes 2.80
-//            ms (3.67 before the one-register state, the 64-bit window and
-//            the half transposes), 1.54 TB/s of stream; the wave's VALU
-//            cycles fill about 85 % of the time and LDS 60 %
+//   bound    the decoder: 65536^2 at rate 8 takes 2.80 ms (3.67 before the
+//            one-register state, the 64-bit window and the half transposes),
+//            1.54 TB/s of stream.  A SIMD issues a vector instruction every
+//            3.3 cycles, and they take 2 to 4 each (whz_device.hpp); LDS
+//            index cycles are 50 % of the time, 44 % of them bank conflicts.
+//            No counter weighs an instruction by its issue cycles, so which
+//            of the two bounds is not shown
 //   product  each block's coefficients against B^T u (FP32), its power-of-two
 //            scale applied to the sum; B once per block row at the end; blocks
 //            cut by the bit budget above plane 26 take the exact inverse lift
@@ -442,11 +445,14 @@ __device__ __forceinline__ float4 block_ut(float4 uu)
 template <int NW>
 constexpr int kGemvMinWaves = NW == 16 ? 4 : (kGemvThreads<NW> == 1024 ? 8 : 6);
 // Block columns whose B^T u a workgroup holds in LDS: its slab's, made once
-// and read by all its block rows.  The planner's slabs of narrow groups have
-// at most 384; a wider slab (wide groups, so few block rows) makes B^T u at
-// each block.
+// and read by all its block rows.  A wider slab makes B^T u at each block,
+// which takes about 5 % (16384 x 16384 at rates 20 / 24 / 32 with 64 slabs of
+// 64: 301 / 316 / 427 us; with 57 of 72 319 / 342 / 504).  The planner prices
+// that; its fixed rule does not, and past 2^27 blocks its slabs of 256 are
+// over the limit at rates 12 and 16 (65536^2: 3.30 and 3.63 ms, 3.22 and 3.58
+// in 128 slabs of 128, twice the partial sums).
 template <int NW>
-constexpr uint32_t kSlabVectors = NW >= 10 ? 64 : (NW == 6 || NW == 8 ? 128 : 384);
+constexpr uint32_t kSlabVectors = gemv_slab_vectors(2 * NW);
 // what LDS holds beside a workgroup's staging rows
 template <int NW>
 constexpr int kGemvTables = kSecEntries * 4 + (int)kSlabVectors<NW> * 16 * (kCanCut<NW> ? 2 : 1);
@@ -872,8 +878,9 @@ __device__ __forceinline__ void mrhs_load_bq(const float* __restrict__ btf, uint
         b[n] = *reinterpret_cast<const f32x4*>(btf + (((uint64_t)(bc + kk) * NT + n) * 16 + j) * 4);
 }
 
-// Quarters of B operands loaded ahead (FP32 U), as many as the registers for
-// six (one group of right-hand sides) or four waves per SIMD leave room for.
+// Quarters of B operands loaded ahead (FP32 U), as many as the registers of the
+// resident waves leave room for (eight a SIMD with one group of right-hand sides
+// up to 16 bits/value, four with more).
 template <int NT>
 constexpr int kMrhsAhead = NT == 1 ? 1 : (NT == 2 ? 2 : 1);
 
@@ -1098,7 +1105,7 @@ __global__ void __launch_bounds__(64 * mrhs_waves(NT, NW), mrhs_waves(NT, NW) / 
                         for (int n = 0; n < NT; ++n)
                             acc[n] =
                                 __builtin_amdgcn_mfma_f32_16x16x4f32(a4[m], bq[slot][n][m], acc[n], 0, 0, 0);
-                    if (q + AH < 4) // the quarter after next into the slot just used
+                    if (q + AH < 4) // the quarter AH on into the slot just used
                         mrhs_load_bq<NT>(btf, cb + 4 * (q + AH), lane, bq[slot]);
                     if (NT == 1 && q + AH == 3) // behind the last of the step's operands
                         load_step(cb + 16);

@@ -73,6 +73,9 @@ def test_rows_per_group(plan, rate, rpg):
     (16, 4096, 4096, 64),    # 32.1; 38.7 with the rule's 43
     (8, 10000, 10000, 63),   # 101.5; 108.5 with the rule's 105
     (32, 26, 135831, 67),    # 26.8; 32.5 with the rule's 23
+    (20, 16384, 16384, 64),  # B^T u of 64 block columns fits LDS: 301; 319 with 57 slabs of 72
+    (24, 16384, 16384, 64),  # 316; 342
+    (32, 16384, 16384, 64),  # 427; 445 with 32 of 128
 ])
 def test_slabs_of_cost_and_rule(plan, rate, rows, cols, nslab):
     assert plan(rate, rows, cols)["nslab"] == nslab
