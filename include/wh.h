@@ -192,11 +192,24 @@ wh_status wh_unload(wh_ctx *ctx, wh_mat m);
  *
  * Workspace: when the plan splits the columns into slabs (most large
  * compressed matrices, wh_gemv_plan_info), the FP64 slab partials live in a
- * workspace of the context's, grown (freed and reallocated) on demand.  Such
- * a call returns WH_ERR_INVALID while `stream` is being captured into a HIP
- * graph, since a later call could free the memory the graph would keep
- * using; wh_gemv_noalloc is the form to capture.  The same holds for
- * wh_gemv_batched and wh_gemv_host. */
+ * workspace of the context's: the 4 MiB of wh_create, or a larger block
+ * allocated (in place of the last such block) when a call needs it.
+ *
+ * Graph capture: a later call could free the block that a captured graph
+ * would keep using, so a call returns WH_ERR_INVALID while `stream` is being
+ * captured if its plan has several slabs.  It does so too where a fixed rule
+ * would have several, whatever the plan has (256 x 1024 at rate 16: one), so
+ * that which calls can be captured does not change with the planner;
+ * wh_gemv_plan_info does not tell these.  For a range of R x C blocks of a
+ * fixed-rate matrix (rounded up) the rule is: L = 1024 lanes (768 above 16
+ * bits/value); groups of G = 8 lanes (4 where C < 8), doubled up to 512 (256
+ * of 768) until R fills at least 90 % of its tiles of L / G block rows;
+ * several slabs where C > G * n, n = R * C / (2048 L) rounded to nearest,
+ * held to 3 .. 16 (past 2^27 blocks n = R * C / (8192 L), at most 48).
+ * WH_GEMV_LANES and WH_GEMV_SLABS, where set, take the place of G and of the
+ * slab count.  wh_gemv_noalloc is the form to capture.  wh_gemv_host follows
+ * the same rule for each of its chunks; wh_gemv_batched is always refused
+ * (but for the one vector that wh_gemv takes). */
 wh_status wh_gemv(wh_ctx *ctx, wh_mat m, const float *d_u, float *d_y, uint32_t row_begin, uint32_t row_end,
                   uint32_t flags, void *stream);
 
@@ -210,13 +223,13 @@ wh_status wh_gemv(wh_ctx *ctx, wh_mat m, const float *d_u, float *d_y, uint32_t 
  * wh_create on that GPU until the process ends.  A call whose plan needs more
  * (column slabs x the range's rows rounded up to whole block rows x 8 bytes;
  * wh_gemv_plan_info gives both) returns WH_ERR_SCRATCH and launches nothing:
- * 65536 x 65536 needs 32 MiB, and no matrix of up to 2^33 values more than
- * 44 MiB.  Calls whose work overlaps on one GPU (other
- * streams, other contexts) share that array and race; calls in order on one
- * stream are safe.  The array keeps the last call's contents; nothing in it
- * has to start at zero.  No hipMalloc, hipFree, event or memset is issued, so
- * the call can be captured into a graph (the graph then keeps using the
- * array). */
+ * 65536 x 65536 needs 32 MiB, and of the matrices of up to 2^33 values only
+ * some of more than 4 million rows need more than the array holds.  Calls
+ * whose work overlaps on one GPU (other streams, other contexts) share that
+ * array and race; calls in order on one stream are safe.  The array keeps the
+ * last call's contents; nothing in it has to start at zero.  No hipMalloc,
+ * hipFree, event or memset is issued, so the call can be captured into a
+ * graph (the graph then keeps using the array). */
 #define WH_NOALLOC_SCRATCH_BYTES (64ull << 20)
 wh_status wh_gemv_noalloc(wh_ctx *ctx, wh_mat m, const float *d_u, float *d_y, uint32_t row_begin,
                           uint32_t row_end, uint32_t flags, void *stream);

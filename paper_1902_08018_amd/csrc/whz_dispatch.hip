@@ -117,7 +117,8 @@ uint32_t set_slabs(GemvPlan& pl, uint32_t nslab, uint32_t width)
 //    groups only where a tile of 512 / G block rows would be mostly empty
 //    (few rows); narrower where a row has fewer than 8 block columns.
 //  * One block row per group and tile.
-//  * Column slabs of 1 to 16 blocks per lane and row, by gemv_shape_cost; or
+//  * Column slabs of 1 to 16 blocks per lane and row, by gemv_shape_cost (the
+//    fixed rule's below where gemv_rounds_cost favours them); or
 //    no slabs, with groups wide enough to take a whole block row at a block a
 //    lane, where that costs less (up to 1024 columns: no partial sums, no
 //    second kernel, no ordering of the workspace's users; 256 x 1024 at rate

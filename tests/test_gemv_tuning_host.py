@@ -8,7 +8,9 @@ WH_GEMV_ROWS, WH_GEMV_SLABS), run on the host: tests/host_serve/gemv_plan.cpp.
   slabs     without overrides: the slab counts that were the faster ones where
             the planner's cost and its fixed rule differ (us of either)
 """
+import math
 import os
+import random
 import shutil
 import subprocess
 
@@ -47,6 +49,30 @@ def test_capture_follows_the_forced_slabs(plan, rate, rows, cols):
         assert plan(rate, rows, cols, lanes=lanes, slabs=1)["uncapturable"] == 0
     p = plan(rate, rows, cols, slabs=3)
     assert p["uncapturable"] == (p["nslab"] > 1)
+
+
+def refused_under_capture(rows, cols, rate):
+    """The rule that include/wh.h states at wh_gemv."""
+    R, C = -(-rows // 4), -(-cols // 4)
+    L, most = (1024, 512) if rate <= 16 else (768, 256)
+    G = 8 if C >= 8 else 4
+    while G < most and 10 * R < 9 * -(-R // (L // G)) * (L // G):
+        G *= 2
+    n = min(16, max(3, (R * C + 1024 * L) // (2048 * L)))
+    if R * C > 2 ** 27:
+        n = min(48, R * C // (8192 * L))
+    return C > G * n
+
+
+def test_capture_rule_of_the_header(plan):
+    rng = random.Random(5)
+    for _ in range(300):
+        rows = round(math.exp(rng.uniform(0, math.log(3e6))))
+        cols = max(1, round(math.exp(rng.uniform(0, math.log(min(3e5, 2e10 / rows))))))
+        rate = rng.choice((2, 4, 6, 8, 10, 12, 14, 16, 20, 24, 32))
+        p = plan(rate, rows, cols)
+        assert p["uncapturable"] == refused_under_capture(rows, cols, rate), (rows, cols, rate)
+        assert p["uncapturable"] or p["nslab"] == 1
 
 
 def test_capture_without_overrides(plan):
